@@ -53,12 +53,13 @@ extern "C" {
 #define FLARE_E_UNSUPPORTED -9  /* model sizes this build has no kernels for                    */
 
 /* ---- arithmetic of the quadratic forms ---- */
-/* The split forms change the energy contraction d.beta.d of the single-species rows
- * (144-wide): the two-part forms (BF16, FP8) split the operands into a high and a low part
- * in a narrow format and recombine them in FP32 accumulators; the three-way BF16 form
- * splits d and beta into three BF16 parts each (together the 24 significant bits of the
- * FP32 value) and keeps six of the nine part products, so its error is that of FP32
- * arithmetic. Mixed-environment rows (544-wide) keep FP32 energy products in all forms.
+/* The FP32 form takes the products of FP32 operands to FP32 accuracy: on the single-species
+ * rows (144-wide) each operand as three BF16 parts, which together hold its 24 significant
+ * bits exactly, and six of the nine part products on the BF16 matrix cores with FP32
+ * accumulation. The split forms change the energy contraction d.beta.d of these rows: the
+ * two-part forms (BF16, FP8) split the operands into a high and a low part in a narrow
+ * format and recombine them in FP32 accumulators; the three-way BF16 form is the FP32
+ * form's. Mixed-environment rows (544-wide) keep FP32-accurate energy products in all forms.
  * The variance d.Sigma.d is computed as |L^T d|^2 with the FP64 Cholesky factor L of each
  * Sigma block, a sum of squares, whenever all Sigma blocks are positive definite (the split
  * forms require it; the FP32 form falls back to the full matrix otherwise): in the FP32
@@ -67,14 +68,14 @@ extern "C" {
  * near-cancelling variance (an environment close to the sparse set of Eq. 2) keeps FP64
  * accuracy in the form and only the FP32 rounding of the descriptors remains. Norms and
  * per-structure sums are FP64 in the split forms. */
-#define FLARE_FP32        0  /* FP32 matrix cores, FP32 accumulation                          */
+#define FLARE_FP32        0  /* FP32 operands and accumulation                                */
 #define FLARE_BF16_SPLIT  1  /* d and beta as BF16 hi + lo, three products; FP64 variance     */
 #define FLARE_FP8_SPLIT   2  /* OCP e4m3 hi + lo, power-of-two scales; FP64 variance          */
 #define FLARE_BF16X6_SPLIT 3 /* d and beta as three BF16 parts, six products (FP32 error);
                                 FP64 variance                                                  */
 #define FLARE_VAR_FP32   16  /* OR-ed with a split form: the variance through the FP32 factor
-                                on FP32 matrix cores (FP64 sums) as in the FP32 form, instead
-                                of FP64: faster, with the FP32 form's variance error           */
+                                with FP32-accurate products (FP64 sums) as in the FP32 form,
+                                instead of FP64: faster, with the FP32 form's variance error           */
 
 /* ---- device status bits (flare_status) ---- */
 #define FLARE_FLAG_NONFINITE  1  /* a position was NaN/inf                                     */

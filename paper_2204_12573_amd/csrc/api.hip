@@ -167,21 +167,6 @@ void bf16x3_fragments(const std::vector<double>& M, uint16_t* out /* [5][9][3][6
         }
 }
 
-// FP32 fragments of an n x n matrix M (row-major, leading dimension ld) for
-// v_mfma_f32_16x16x4_f32 B operands: [K chunk n/16][column block n/16][lane 64][t 4],
-// element M[16 kc + 4 (lane / 16) + t][16 cb + lane % 16].
-std::vector<float> f32_fragments(const double* M, int ld, int n) {
-  const int nc = n / 16;
-  std::vector<float> f((size_t)nc * nc * 64 * 4);
-  for (int kc = 0; kc < nc; ++kc)
-    for (int cb = 0; cb < nc; ++cb)
-      for (int lane = 0; lane < 64; ++lane)
-        for (int t = 0; t < 4; ++t)
-          f[(((size_t)kc * nc + cb) * 64 + lane) * 4 + t] =
-              (float)M[(size_t)(kc * 16 + 4 * (lane / 16) + t) * ld + cb * 16 + lane % 16];
-  return f;
-}
-
 // FP64 fragments of an n x n lower-triangular factor L (row-major) for
 // v_mfma_f64_16x16x4_f64 B operands: [cb][kc][t 4][lane 64], element
 // L[16 kc + 4 (lane / 16) + t][16 cb + lane % 16] (blocks with kc < cb are zero).
@@ -315,24 +300,11 @@ int flare_model_create(flare_model** out, int n_species, int n_rad, int l_max, d
   m->var64 = precision != FLARE_FP32 && !(flags & FLARE_VAR_FP32);
   m->r_cut = r_cut;
   CHK(hipGetDevice(&m->device));
-  // beta and Sigma of each single-species bucket's 144-wide block in fragment order
-  for (int b = 0; b < 4; ++b) {
-    const int sp = b & 1;                          // central species
-    const int st = b < 2 ? 0 : ND - ND1;           // the block inside the packed 544 vector
-    std::vector<float> f0 = f32_fragments(beta_host + (size_t)sp * ND * ND + (size_t)st * ND + st, ND, ND1);
-    std::vector<float> f1 = f32_fragments(sigma_host + (size_t)sp * ND * ND + (size_t)st * ND + st, ND, ND1);
-    f0.insert(f0.end(), f1.begin(), f1.end());
-    const int rc = upload((void**)&m->Wf[b], f0.data(), f0.size() * sizeof(float));
-    if (rc != FLARE_OK) {
-      flare_model_destroy(m);
-      return rc;
-    }
-  }
   // Cholesky factors of the Sigma blocks: V = |L^T d|^2, a sum of squares that does not
-  // cancel, and the zero upper triangle of L skips 36 of the 81 16x16 blocks of the
+  // cancel, and the zero upper triangle of L skips 16 of the 45 32x16 blocks of the
   // 144-wide variance pass. The split forms need them; the FP32 form uses them when every
   // block is positive definite and keeps the full Sigma otherwise.
-  const int nkc = ND1 / 16, ncb = ND1 / 16;
+  const int ncb = ND1 / 16;
   std::vector<std::vector<double>> L1(4), Lx(NS);
   bool chol = true;
   for (int b = 0; b < 4 && chol; ++b) {
@@ -350,19 +322,6 @@ int flare_model_create(flare_model** out, int n_species, int n_rad, int l_max, d
     return FLARE_E_ARG;
   }
   m->vchol = chol;
-  if (chol) {
-    for (int b = 0; b < 4; ++b) {
-      // FP32 fragments of L replace the Sigma part (part 1) of Wf
-      std::vector<float> f = f32_fragments(L1[b].data(), ND1, ND1);
-      hipError_t e = hipMemcpy(m->Wf[b] + (size_t)nkc * ncb * 64 * 4, f.data(), f.size() * sizeof(float),
-                               hipMemcpyHostToDevice);
-      if (e != hipSuccess) {
-        set_error(std::string("model upload: ") + hipGetErrorString(e));
-        flare_model_destroy(m);
-        return FLARE_E_HIP;
-      }
-    }
-  }
   // the mixed buckets: beta, Sigma (and L) of the central species over all 544 components,
   // row n of each stored part = column n of the matrix
   for (int sp = 0; sp < NS; ++sp) {
@@ -400,18 +359,24 @@ int flare_model_create(flare_model** out, int n_species, int n_rad, int l_max, d
       }
     }
   }
-  if (precision == FLARE_BF16X6_SPLIT) {
-    for (int b = 0; b < 4; ++b) {
-      const int s = b & 1;
-      const int st = b < 2 ? 0 : ND - ND1;
-      std::vector<double> beta = sub_block(beta_host + (size_t)s * ND * ND, st, ND1);
-      std::vector<uint16_t> frag((size_t)5 * ncb * 3 * 64 * 8);
-      bf16x3_fragments(beta, frag.data());
-      const int rc = upload((void**)&m->W6[b], frag.data(), frag.size() * sizeof(uint16_t));
-      if (rc != FLARE_OK) {
-        flare_model_destroy(m);
-        return rc;
-      }
+  // single-species buckets: beta (FP32 and three-way BF16 forms) and, unless the variance
+  // runs in FP64, the factor (or Sigma), each in three BF16 parts
+  for (int b = 0; b < 4; ++b) {
+    const int s = b & 1;
+    const int st = b < 2 ? 0 : ND - ND1;
+    std::vector<uint16_t> frag((size_t)5 * ncb * 3 * 64 * 8);
+    int rc = FLARE_OK;
+    if (precision == FLARE_FP32 || precision == FLARE_BF16X6_SPLIT) {
+      bf16x3_fragments(sub_block(beta_host + (size_t)s * ND * ND, st, ND1), frag.data());
+      rc = upload((void**)&m->W6[b], frag.data(), frag.size() * sizeof(uint16_t));
+    }
+    if (rc == FLARE_OK && !m->var64) {
+      bf16x3_fragments(chol ? L1[b] : sub_block(sigma_host + (size_t)s * ND * ND, st, ND1), frag.data());
+      rc = upload((void**)&m->V6[b], frag.data(), frag.size() * sizeof(uint16_t));
+    }
+    if (rc != FLARE_OK) {
+      flare_model_destroy(m);
+      return rc;
     }
   }
   if (precision == FLARE_BF16_SPLIT || precision == FLARE_FP8_SPLIT) {
@@ -476,10 +441,10 @@ int flare_model_info(const flare_model* m, int* precision, int* variance_cholesk
 int flare_model_destroy(flare_model* m) {
   if (!m) return FLARE_OK;
   for (int b = 0; b < 4; ++b) {
-    if (m->Wf[b]) (void)hipFree(m->Wf[b]);
     if (m->Wb[b]) (void)hipFree(m->Wb[b]);
     if (m->W8[b]) (void)hipFree(m->W8[b]);
     if (m->W6[b]) (void)hipFree(m->W6[b]);
+    if (m->V6[b]) (void)hipFree(m->V6[b]);
     if (m->L64[b]) (void)hipFree(m->L64[b]);
   }
   for (int k = 0; k < 2; ++k) {
@@ -1068,11 +1033,12 @@ int flare_memory_bytes(const flare_model* m, const flare_state* s, long long* by
   ARG(bytes, "null pointer");
   long long b = 0;
   if (m) {
-    b += (4LL * 2 * ND1 * ND1 + 2LL * 2 * ND * ND) * sizeof(float);   // Wf, Wx
+    b += 2LL * 2 * ND * ND * sizeof(float);                              // Wx
     if (m->vchol) b += 2LL * ND * ND * sizeof(float);                    // Lx
     if (m->precision == FLARE_BF16_SPLIT) b += 4LL * 5 * 9 * 2 * 64 * 8 * sizeof(uint16_t);
     if (m->precision == FLARE_FP8_SPLIT) b += 4LL * 5 * 9 * 2 * 64 * sizeof(uint64_t);
-    if (m->precision == FLARE_BF16X6_SPLIT) b += 4LL * 5 * 9 * 3 * 64 * 8 * sizeof(uint16_t);
+    for (int k = 0; k < 4; ++k)
+      b += ((m->W6[k] ? 1LL : 0LL) + (m->V6[k] ? 1LL : 0LL)) * 5 * 9 * 3 * 64 * 8 * sizeof(uint16_t);
     if (m->var64) b += (4LL * ND1 * ND1 + 2LL * ND * ND) * sizeof(double);
   }
   if (s) b += s->fixed_bytes + (long long)s->red_w.bytes();

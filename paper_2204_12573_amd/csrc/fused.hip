@@ -7,9 +7,15 @@
 //      straight into an LDS tile [128][148] (the padding makes the 16-byte fragment reads
 //      below conflict-free); nothing goes to HBM. The tile holds the unnormalised d~: the
 //      products are linear in the row, so the epilogue applies 1/|d~|^2 once;
-//   2. quadratic forms on the FP32 matrix cores (v_mfma_f32_16x16x4_f32): Y = D W for
-//      W = Sigma_b then W = beta_b, A fragments from LDS, B fragments streamed from L2 in a
-//      fragment-major copy of W (one contiguous 1 KB load per 16x16 block and K chunk);
+//   2. quadratic forms Y = D W for W = L (the variance's Cholesky factor, or Sigma) then
+//      W = beta: in the FP32 and three-way BF16 forms on v_mfma_f32_16x16x32_bf16 with both
+//      operands in three exact BF16 parts and six part products (FP32 error or less: 2-norm
+//      error of e against 64 bits 1.3e-7 -> 1.0e-7, of F 1.0e-6 -> 9e-7 on 1.0 M atoms), A
+//      parts split from the FP32 tile in LDS, B parts streamed from L2 in a fragment-major
+//      copy of W. Against v_mfma_f32_16x16x4_f32 the matrix work of a 32-row sub-tile falls
+//      from 32.3 to 14.2 k cycles and its instructions run beside the other wave's vector
+//      work, which the FP32 ones do not: 784 -> 616 us a launch on 1.0 M atoms with the
+//      batched epilogue below, 56 -> 35 us on 80 atoms;
 //   3. epilogue, with Y~ = d~ W: V_i = Y~ . d~ / |d~|^2 (or |Z~|^2/|d~|^2 in the split form),
 //      e_i = Y~ . d~ / |d~|^2, g_i = de_i/dd~_i = (2/|d~|^2)(Y~ - e_i d~) written into the
 //      tile;
@@ -19,7 +25,6 @@
 //      u = G^ c from the gradient tile in LDS and write the per-pair terms w (adjoint.h):
 //      neither g nor c goes to HBM. The forces variant runs with every wave on its own 32-row
 //      sub-tiles (k_fused144_w): each of the steps touches only the wave's own rows.
-// Inside a 16-wide K chunk, k-step t of lane group q uses k = 4q + t for A and B alike.
 #include <type_traits>
 
 #include "adjoint.h"
@@ -34,7 +39,7 @@ typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 constexpr int FT = 256;       // threads
 constexpr int FR = 128;       // rows per tile
 constexpr int AS = ND1 + 4;   // LDS row stride of the tile (floats)
-constexpr int NKC = ND1 / 16; // 9 K chunks
+constexpr int NKC = ND1 / 16; // 9 K chunks (FP64 variance)
 constexpr int NCB = ND1 / 16; // 9 column blocks
 
 struct FusedArgs {
@@ -42,17 +47,17 @@ struct FusedArgs {
   const int* aor;        // atom of row, -1 for padding
   int nbk;
   int row0[4], row1[4];
-  const float4* Wf[4];   // per bucket [part 2][kc 9][cb 9][lane 64]
   const uint4* Wb[4];    // split form: beta as [ks 5][cb 9][hi/lo 2][lane 64] x 8 bf16
   const uint64_t* W8[4]; // FP8 split form: s_b beta as [ks 5][cb 9][hi/lo' 2][lane 64] x 8 e4m3
   float bscale[4];       // FP8 split form: s_b per bucket (a power of two)
-  const uint4* W6[4];    // three-way BF16 form: beta as [ks 5][cb 9][part 3][lane 64] x 8 bf16
+  const uint4* W6[4];    // FP32 and three-way BF16 forms: beta as [ks 5][cb 9][part 3][lane 64] x 8 bf16
+  const uint4* V6[4];    // variance outside FP64: the Cholesky factor L of Sigma (or Sigma), as W6
   const double* L64[4];  // split forms: the Cholesky factor L in FP64, [cb 9][kc 9][t 4][lane 64]
   const float* D_in;     // optional [rows][144] given vectors (replace the descriptor phase; no
                          // normalisation: the forms are those of the vectors as given)
   int n_given;           // with D_in: rows 0 .. n_given - 1 are the given vectors
   int mode;              // bit 0: energy + gradient (beta), bit 1: variance (Sigma)
-  int vchol;             // part 1 of Wf holds the Cholesky factor L: V = |L^T d|^2
+  int vchol;             // V6 holds the Cholesky factor L: V = |L^T d|^2
   float* G;              // [tiles][144][128]: g, when the forces are not formed here
   float4* f_own;         // per row: sum of its own pair terms (written when the forces are formed here)
   float* nrm;            // per atom
@@ -66,65 +71,11 @@ struct FusedArgs {
   int dstart[4];         // first component of each bucket's block in the 544 vector
 };
 
-// TRI: W = L lower-triangular, blocks of chunk kc with column block j > kc vanish. The
-// chunks then run from the last (all 9 column blocks) to the first (1 block), so the
-// loads of the next chunk are always covered by the larger MFMA work of the current one.
-template <int PART, bool TRI = false>
-__device__ __forceinline__ void mfma_pass(const float* As, const float4* __restrict__ W, int wave, int lane,
-                                          f4 (&acc)[2][NCB]) {
-  const int l16 = lane & 15, grp = lane >> 4;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < NCB; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
-  const float4* Wp = W + (size_t)PART * NKC * NCB * 64 + lane;
-  float4 bA[NCB], bB[NCB];
-  constexpr int K0 = TRI ? NKC - 1 : 0;
-#pragma unroll
-  for (int j = 0; j < NCB; ++j)
-    if (!TRI || j <= K0) bA[j] = Wp[(K0 * NCB + j) * 64];
-#pragma unroll
-  for (int it = 0; it < NKC; ++it) {
-    const int kc = TRI ? NKC - 1 - it : it;      // chunk of this iteration
-    const int kn = TRI ? kc - 1 : kc + 1;        // chunk of the next
-    float4* cur = (it & 1) ? bB : bA;
-    float4* nxt = (it & 1) ? bA : bB;
-    if (it + 1 < NKC) {
-#pragma unroll
-      for (int j = 0; j < NCB; ++j)
-        if (!TRI || j <= kn) nxt[j] = Wp[(kn * NCB + j) * 64];
-    }
-    float4 a[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-      a[i] = *reinterpret_cast<const float4*>(&As[(wave * 32 + i * 16 + l16) * AS + kc * 16 + 4 * grp]);
-    // keep the next chunk's loads ahead of this chunk's MFMAs (the scheduler would
-    // otherwise sink them next to their use to shorten live ranges)
-    __builtin_amdgcn_sched_barrier(0);
-    // k-step outermost: consecutive MFMAs write different accumulators, so none waits
-    // for the previous result
-#define FQ_STEP(C)                                                                           \
-  _Pragma("unroll") for (int j = 0; j < NCB; ++j) {                                         \
-    if (TRI && j > kc) continue; /* lower-triangular W: rows k < column j vanish */         \
-    _Pragma("unroll") for (int i = 0; i < 2; ++i)                                           \
-      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i].C, cur[j].C, acc[i][j], 0, 0, 0); \
-  }
-    FQ_STEP(x)
-    FQ_STEP(y)
-    FQ_STEP(z)
-    FQ_STEP(w)
-#undef FQ_STEP
-  }
-}
-
 // Split form of the energy pass on v_mfma_f32_16x16x32_bf16: D = D_hi + D_lo and
 // beta = beta_hi + beta_lo in BF16, Y = D_hi beta_hi + D_hi beta_lo + D_lo beta_hi with FP32
 // accumulation (the dropped D_lo beta_lo is ~2^-16 relative). K = 144 runs as five 32-wide
 // steps; in the last one lane groups 2-3 (k = 144..159) feed zeros and the stored beta is
 // zero there. Lane (m, q) supplies A[m][32t + 8q .. +7] and B[32t + 8q .. +7][n].
-// The variance pass of the split form stays on FP32 cores with the Cholesky factor L of
-// Sigma: V = |L^T d|^2 turns the possibly near-cancelling d^T Sigma d into a sum of
-// squares whose error follows the rounding of d, not the size of the cancelled terms.
 constexpr int NKS = 5;
 
 typedef float f2v __attribute__((ext_vector_type(2)));
@@ -257,9 +208,34 @@ __device__ __forceinline__ void load_a8(const float* As, int wave, int l16, int 
 // Steps (ks, jg) in order. One register buffer of B fragments: the products run B part 2
 // first and part 0 last, and each part's fragments for the next step are loaded as soon as
 // its last product here is issued; the next K step's A values are loaded at the start of a
-// K step's last group.
+// K step's last group. The scheduler may move vector and LDS work across the loads but not
+// the products: it would sink each load next to its use (1 % of the kernel at 1.0 M atoms).
+// TRI: W is lower-triangular, so of K step ks (rows 32 ks .. 32 ks + 31) only the column
+// blocks j <= 2 ks + 1 are non-zero: 29 of the 45 blocks, in 11 of the 15 groups. The K
+// steps then run from the last (9 blocks) to the first (2 blocks).
+template <bool TRI>
+struct X6Steps {
+  static constexpr int N = TRI ? 11 : 15;
+  int ks[N] = {}, jg[N] = {};
+  constexpr X6Steps() {
+    int n = 0;
+    for (int k = 0; k < NKS; ++k)
+      for (int g = 0; g < NCB / 3; ++g) {
+        const int q = TRI ? NKS - 1 - k : k;
+        if (TRI && 3 * g > 2 * q + 1) continue;
+        ks[n] = q;
+        jg[n] = g;
+        ++n;
+      }
+  }
+};
+template <bool TRI>
+constexpr bool x6_live(int ks, int j) { return !TRI || j <= 2 * ks + 1; }
+
+template <bool TRI>
 __device__ __forceinline__ void mfma_pass_bf16x6(const float* As, const uint4* __restrict__ W, int wave,
                                                  int lane, f4 (&acc)[2][NCB]) {
+  constexpr X6Steps<TRI> st;
   const int l16 = lane & 15, grp = lane >> 4;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -273,45 +249,46 @@ __device__ __forceinline__ void mfma_pass_bf16x6(const float* As, const uint4* _
   for (int jj = 0; jj < 3; ++jj)
 #pragma unroll
     for (int pt = 0; pt < 3; ++pt)
-      b[jj][pt] = __builtin_bit_cast(bf8, Wp[(jj * 3 + pt) * 64]);
+      b[jj][pt] = __builtin_bit_cast(bf8, Wp[((st.ks[0] * NCB + jj) * 3 + pt) * 64]);
 #pragma unroll
-  for (int i = 0; i < 2; ++i) load_a8(As, wave, l16, grp, i, 0, araw[i]);
+  for (int i = 0; i < 2; ++i) load_a8(As, wave, l16, grp, i, st.ks[0], araw[i]);
 #pragma unroll
-  for (int ks = 0; ks < NKS; ++ks) {
+  for (int n = 0; n < X6Steps<TRI>::N; ++n) {
+    const int ks = st.ks[n], jg = st.jg[n];
+    if (n == 0 || st.ks[n] != st.ks[n - 1]) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) split8x3(araw[i], a[0][i], a[1][i], a[2][i]);
+      for (int i = 0; i < 2; ++i) split8x3(araw[i], a[0][i], a[1][i], a[2][i]);
+    }
+    const bool more = n + 1 < X6Steps<TRI>::N;
+    const int nks = more ? st.ks[n + 1] : ks, njg = more ? st.jg[n + 1] : jg;
+    if (more && nks != ks) {
 #pragma unroll
-    for (int jg = 0; jg < NCB / 3; ++jg) {
-      // the next step
-      const bool same = jg + 1 < NCB / 3;
-      const int nks = same ? ks : ks + 1, njg = same ? jg + 1 : 0;
-      const bool more = nks < NKS;
-      if (more && !same) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) load_a8(As, wave, l16, grp, i, nks, araw[i]);
-      }
+      for (int i = 0; i < 2; ++i) load_a8(As, wave, l16, grp, i, nks, araw[i]);
+    }
 #define X6_PROD(PA, PB)                                                                       \
   _Pragma("unroll") for (int jj = 0; jj < 3; ++jj) {                                          \
+    if (!x6_live<TRI>(ks, 3 * jg + jj)) continue;                                             \
     _Pragma("unroll") for (int i = 0; i < 2; ++i) acc[i][3 * jg + jj] =                       \
         __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[PA][i], b[jj][PB], acc[i][3 * jg + jj], 0, 0, 0); \
   }
 #define X6_NEXT(PT)                                                                           \
   if (more) {                                                                                 \
-    _Pragma("unroll") for (int jj = 0; jj < 3; ++jj)                                          \
+    __builtin_amdgcn_sched_barrier(0x186);                                                    \
+    _Pragma("unroll") for (int jj = 0; jj < 3; ++jj) if (x6_live<TRI>(nks, 3 * njg + jj))     \
       b[jj][PT] = __builtin_bit_cast(bf8, Wp[((nks * NCB + 3 * njg + jj) * 3 + PT) * 64]);     \
+    __builtin_amdgcn_sched_barrier(0x186);                                                    \
   }
-      X6_PROD(0, 2)
-      X6_NEXT(2)
-      X6_PROD(1, 1)
-      X6_PROD(0, 1)
-      X6_NEXT(1)
-      X6_PROD(2, 0)
-      X6_PROD(1, 0)
-      X6_PROD(0, 0)
-      X6_NEXT(0)
+    X6_PROD(0, 2)
+    X6_NEXT(2)
+    X6_PROD(1, 1)
+    X6_PROD(0, 1)
+    X6_NEXT(1)
+    X6_PROD(2, 0)
+    X6_PROD(1, 0)
+    X6_PROD(0, 0)
+    X6_NEXT(0)
 #undef X6_PROD
 #undef X6_NEXT
-    }
   }
 }
 
@@ -525,20 +502,35 @@ __device__ __forceinline__ void var_pass_f64(const float* As, const double* __re
     for (int r = 0; r < 4; ++r) out[i][r] = sum16d(ss[i][r]);
 }
 
-// Row-dots Y_row . d_row of the 8 rows a lane touches; all 16 lanes of a group get the sum.
-__device__ __forceinline__ void row_dots(const float* As, const f4 (&acc)[2][NCB], int wave, int lane,
-                                         float (&out)[2][4]) {
+// The d values of the four rows 4 grp + r of row block i in the lane's nine columns, loaded
+// together, and the row-dots Y_row . d_row (all 16 lanes of a group get the sums).
+__device__ __forceinline__ void block_dots(const float* As, const f4 (&acc)[2][NCB], int wave, int lane, int i,
+                                           float (&d)[4][NCB], float (&out)[4]) {
   const int l16 = lane & 15, grp = lane >> 4;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int r = 0; r < 4; ++r) {
+    const float* p = As + (wave * 32 + i * 16 + 4 * grp + r) * AS + l16;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const float* d = As + (wave * 32 + i * 16 + 4 * grp + r) * AS + l16;
-      float s = 0.f;
+    for (int j = 0; j < NCB; ++j) d[r][j] = p[j * 16];
+  }
 #pragma unroll
-      for (int j = 0; j < NCB; ++j) s += acc[i][j][r] * d[j * 16];
-      out[i][r] = sum16(s);
-    }
+  for (int r = 0; r < 4; ++r) {
+    float s = 0.f;
+#pragma unroll
+    for (int j = 0; j < NCB; ++j) s += acc[i][j][r] * d[r][j];
+    out[r] = sum16(s);
+  }
+}
+
+// Of the eight row values that all 16 lanes of a group hold, value (i, r) for lane l16 =
+// 4 i + r: one lane per row then forms and stores the row's result, instead of one lane
+// walking its eight rows.
+template <class T>
+__device__ __forceinline__ T row_value(const T (&v)[2][4], int l16) {
+  T x = v[0][0];
+#pragma unroll
+  for (int k = 1; k < 8; ++k) x = l16 == k ? v[k >> 2][k & 3] : x;
+  return x;
 }
 
 // Atom of a row (-1: padding); for given vectors (GIVEN) row r < n_given is "atom" r.
@@ -549,20 +541,20 @@ __device__ __forceinline__ int atom_of(const FusedArgs& a, int row) {
 
 // Model operands of the bucket that holds rows [row0, row0 + 128).
 struct TileModel {
-  const float4* Wf;
   const uint4* Wb;
   const uint64_t* W8;
   const uint4* W6;
+  const uint4* V6;
   const double* L64;
   float bsc;
   int dstart;
 };
 __device__ __forceinline__ TileModel tile_model(const FusedArgs& a, int row0) {
-  TileModel m{a.Wf[0], a.Wb[0], a.W8[0], a.W6[0], a.L64[0], a.bscale[0], a.dstart[0]};
+  TileModel m{a.Wb[0], a.W8[0], a.W6[0], a.V6[0], a.L64[0], a.bscale[0], a.dstart[0]};
 #pragma unroll
   for (int k = 1; k < 4; ++k)   // static indexing keeps the argument arrays out of scratch
     if (k < a.nbk && row0 >= a.row0[k] && row0 < a.row1[k])
-      m = TileModel{a.Wf[k], a.Wb[k], a.W8[k], a.W6[k], a.L64[k], a.bscale[k], a.dstart[k]};
+      m = TileModel{a.Wb[k], a.W8[k], a.W6[k], a.V6[k], a.L64[k], a.bscale[k], a.dstart[k]};
   return m;
 }
 
@@ -659,51 +651,45 @@ __device__ __forceinline__ void forms_phase(const FusedArgs& a, float* As, const
     // split forms: V = |L^T d~|^2 / |d~|^2 with FP64 products, sums and division
     double vv[2][4];
     var_pass_f64(As, tm.L64, wave, lane, vv);
-    if (l16 == 0) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int rl = wave * 32 + i * 16 + grp + 4 * r;     // FP64 accumulator layout
-          const int atom = rs.atom[rl];
-          const double n2 = rs.nrm2[rl];
-          if (atom >= 0) {
-            const float v = n2 > 0.0 ? (float)(vv[i][r] / n2) : 0.f;
-            a.v_int[atom] = v;
-            a.v_row[row0 + rl] = v;
-          }
-        }
+    const double x = row_value(vv, l16);
+    if (l16 < 8) {
+      const int rl = wave * 32 + (l16 >> 2) * 16 + grp + 4 * (l16 & 3);     // FP64 accumulator layout
+      const int atom = rs.atom[rl];
+      const double n2 = rs.nrm2[rl];
+      if (atom >= 0) {
+        const float v = n2 > 0.0 ? (float)(x / n2) : 0.f;
+        a.v_int[atom] = v;
+        a.v_row[row0 + rl] = v;
+      }
     }
   } else if (a.mode & 2) {
     if (a.vchol) {
-      // Z = D L on FP32 cores, L lower-triangular
-      mfma_pass<1, true>(As, tm.Wf, wave, lane, acc);
+      // Z = D L, L lower-triangular
+      mfma_pass_bf16x6<true>(As, tm.V6, wave, lane, acc);
       row_sumsq<PREC != FLARE_FP32>(acc, dots);
     } else {
-      mfma_pass<1>(As, tm.Wf, wave, lane, acc);
-      row_dots(As, acc, wave, lane, dots);
+      mfma_pass_bf16x6<false>(As, tm.V6, wave, lane, acc);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        float d[4][NCB];
+        block_dots(As, acc, wave, lane, i, d, dots[i]);
+      }
     }
-    if (l16 == 0) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int rl = wave * 32 + i * 16 + 4 * grp + r;
-          const int atom = rs.atom[rl];
-          const float nv = nrm_s[rl];
-          if (atom >= 0) {
-            const float v = nv > 0.f ? dots[i][r] / (nv * nv) : 0.f;
-            a.v_int[atom] = v;
-            a.v_row[row0 + rl] = v;
-          }
-        }
+    const float x = row_value(dots, l16);
+    if (l16 < 8) {
+      const int rl = wave * 32 + (l16 >> 2) * 16 + 4 * grp + (l16 & 3);
+      const int atom = rs.atom[rl];
+      const float nv = nrm_s[rl];
+      if (atom >= 0) {
+        const float v = nv > 0.f ? x / (nv * nv) : 0.f;
+        a.v_int[atom] = v;
+        a.v_row[row0 + rl] = v;
+      }
     }
   }
   if (a.mode & 1) {
     if (PREC == FLARE_BF16_SPLIT) {
       mfma_pass_bf16<0>(As, tm.Wb, wave, lane, acc);
-    } else if (PREC == FLARE_BF16X6_SPLIT) {
-      mfma_pass_bf16x6(As, tm.W6, wave, lane, acc);
     } else if (PREC == FLARE_FP8_SPLIT) {
       mfma_pass_fp8(As, rsc_s, tm.W8, wave, lane, acc);
       // undo the power-of-two scales: Y~ = acc / (16 s_r s_b), exact
@@ -716,27 +702,36 @@ __device__ __forceinline__ void forms_phase(const FusedArgs& a, float* As, const
           for (int j = 0; j < NCB; ++j) acc[i][j][r] *= inv;
         }
     } else {
-      mfma_pass<0>(As, tm.Wf, wave, lane, acc);
+      mfma_pass_bf16x6<false>(As, tm.W6, wave, lane, acc);
     }
-    row_dots(As, acc, wave, lane, dots);
+    // e = Y~ . d~ / |d~|^2, g = (2/|d~|^2) (Y~ - e d~): each lane's d values come in one
+    // batch of loads per row block and are overwritten with g from registers (read and
+    // written one by one they cost an LDS latency each, 72 per sub-tile)
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 2; ++i) {
+      float d[4][NCB];
+      block_dots(As, acc, wave, lane, i, d, dots[i]);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int rl = wave * 32 + i * 16 + 4 * grp + r;
-        const int atom = rs.atom[rl];
         const float inv2 = rs.inv2[rl];
-        const float e = dots[i][r] * inv2;        // e = Y~ . d~ / |d~|^2
-        if (l16 == 0 && atom >= 0) {
-          a.e_int[atom] = e;
-          a.e_row[row0 + rl] = e;
-        }
-        const float s2 = 2.f * inv2;              // g = (2/|d~|^2) (Y~ - e d~)
-        float* d = As + rl * AS + l16;
-        // each lane reads its own d-elements before overwriting them with g
+        const float e = dots[i][r] * inv2;
+        const float s2 = 2.f * inv2;
+        dots[i][r] = e;
+        float* p = As + rl * AS + l16;
 #pragma unroll
-        for (int j = 0; j < NCB; ++j) d[j * 16] = s2 * (acc[i][j][r] - e * d[j * 16]);
+        for (int j = 0; j < NCB; ++j) p[j * 16] = s2 * (acc[i][j][r] - e * d[r][j]);
       }
+    }
+    const float e = row_value(dots, l16);
+    if (l16 < 8) {
+      const int rl = wave * 32 + (l16 >> 2) * 16 + 4 * grp + (l16 & 3);
+      const int atom = rs.atom[rl];
+      if (atom >= 0) {
+        a.e_int[atom] = e;
+        a.e_row[row0 + rl] = e;
+      }
+    }
   }
 }
 
@@ -883,10 +878,10 @@ void forms_given_144(flare_state* s, int bucket, int n, const float* d, float* e
   a.nbk = 1;
   a.row0[0] = 0;
   a.row1[0] = rows;
-  a.Wf[0] = reinterpret_cast<const float4*>(m->Wf[bucket]);
   a.Wb[0] = reinterpret_cast<const uint4*>(m->Wb[bucket]);
   a.W8[0] = m->W8[bucket];
   a.W6[0] = reinterpret_cast<const uint4*>(m->W6[bucket]);
+  a.V6[0] = reinterpret_cast<const uint4*>(m->V6[bucket]);
   a.L64[0] = m->L64[bucket];
   a.bscale[0] = m->beta_scale[bucket];
   a.vchol = m->vchol ? 1 : 0;
@@ -910,10 +905,10 @@ void fused_quadratic_forms(flare_state* s, int mode, float* d_out) {
     const int padded = (s->bucket_count[k] + TILE_ROWS - 1) / TILE_ROWS * TILE_ROWS;
     a.row0[k] = s->bucket_row0[k];
     a.row1[k] = s->bucket_row0[k] + padded;
-    a.Wf[k] = reinterpret_cast<const float4*>(s->model->Wf[k]);
     a.Wb[k] = reinterpret_cast<const uint4*>(s->model->Wb[k]);
     a.W8[k] = s->model->W8[k];
     a.W6[k] = reinterpret_cast<const uint4*>(s->model->W6[k]);
+    a.V6[k] = reinterpret_cast<const uint4*>(s->model->V6[k]);
     a.L64[k] = s->model->L64[k];
     a.bscale[k] = s->model->beta_scale[k];
   }

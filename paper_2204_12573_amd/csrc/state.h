@@ -78,31 +78,29 @@ struct flare_model {
   int precision = FLARE_FP32;     // arithmetic form of the energy pass (FLARE_FP32 .. FLARE_BF16X6_SPLIT)
   int flags = 0;                  // the precision argument as given (form | FLARE_VAR_FP32)
   bool var64 = false;             // variance on the FP64 matrix cores (split forms without FLARE_VAR_FP32)
-  // variances from Cholesky factors (part 1 of Wf and Wxf holds L)
+  // variances from Cholesky factors (V6 and Lx hold L)
   bool vchol = false;
   double r_cut = 0.0;
-  // Single-species buckets: beta (part 0) and Sigma or its Cholesky factor L (part 1) of
-  // the central species, restricted to the bucket's 144-wide block, in MFMA fragment
-  // order [part 2][K chunk 9][column block 9][lane 64] float4: element t of lane l of
-  // (kc, cb) is M[16 kc + 4 (l / 16) + t][16 cb + l % 16] (see fused.hip).
-  float* Wf[4] = {};
   // Mixed buckets (4: H centre, 5: Pt centre): beta then Sigma of the central species over
   // all 544 components, [2][544][544] with row n = column n of the matrix (see qform.hip);
   // with Cholesky factors, Lx holds L in the same form.
   float* Wx[2] = {};
   float* Lx[2] = {};
   // BF16 split form (precision FLARE_BF16_SPLIT), single-species buckets: beta as
-  // [K step 5][column block 9][hi/lo 2][lane 64] x 8 bf16 (K padded 144 -> 160). In this
-  // form the Sigma part of Wf holds the Cholesky factor L of Sigma (Sigma = L L^T).
+  // [K step 5][column block 9][hi/lo 2][lane 64] x 8 bf16 (K padded 144 -> 160).
   uint16_t* Wb[4] = {};
   // FP8 split form (precision FLARE_FP8_SPLIT): s_b * beta as [K step 5][column block 9]
   // [hi, lo' 2][lane 64] x 8 OCP e4m3 bytes, converted on the device by the same
   // instruction the kernel uses for d; lo' = fp8(16 (x - hi)). s_b = 2^k keeps |s_b beta| <= 16.
   uint64_t* W8[4] = {};
   float beta_scale[4] = {1.f, 1.f, 1.f, 1.f};
-  // Three-way BF16 form (precision FLARE_BF16X6_SPLIT): beta as [K step 5][column block 9]
-  // [part 3][lane 64] x 8 bf16, parts x0 + x1 + x2 = FP32 value.
+  // FP32 and three-way BF16 forms, single-species buckets: beta of the central species,
+  // restricted to the bucket's 144-wide block, as [K step 5][column block 9][part 3][lane 64]
+  // x 8 bf16, parts x0 + x1 + x2 = FP32 value (K padded 144 -> 160).
   uint16_t* W6[4] = {};
+  // Variances outside FP64 (the FP32 form, FLARE_VAR_FP32): the Cholesky factor L of the
+  // bucket's block of Sigma rounded to FP32 (Sigma itself without factors), as W6.
+  uint16_t* V6[4] = {};
   // Split forms: Cholesky factors in FP64 for the variance on the FP64 matrix cores, in
   // fragment order [column block][K chunk][k-step 4][lane 64]: element L[16 kc + 4 (lane / 16)
   // + t][16 cb + lane % 16]. Single-species buckets: the factor of the bucket's 144 x 144
