@@ -38,17 +38,57 @@ __global__ __launch_bounds__(TA) void k_adjoint144(SlotView v, const int* __rest
 // the row (G^ from the row's 544 gradient components: (H,H) and (Pt,Pt) blocks doubled on
 // the diagonal, the (H,Pt) block shared by both orders), and the row's slots are split
 // over the lanes (k = L, L + 16, ...), each pair reading u of its neighbour species from LDS.
-// Rows [r0, r0 + gridDim.x * MROWS) of the mixed class; G holds the chunk's gradients
-// (row r - r0).
+// Rows [r0, r0 + gridDim.x * MROWS) of the mixed class. The row's gradient g = (2/|d~|)
+// (y - e d) is formed here from the chunk's D and Y (row r - r0) and kept in LDS (35 KB a
+// work-group, three a CU; g used to be written by a kernel of its own and gathered from L2:
+// 16 us of 39 for 13 k rows); with it the row's e and, given the column pairs' shares P, V.
+constexpr int GSTRIDE = ND + 4;
+struct MixedForms {
+  const float* D;
+  const float* Y;
+  const float* P;        // V shares [rows][17], or null
+  const float* nrm;
+  float* e_int;
+  float* v_int;
+  float* e_row;          // of the mixed class's rows
+  float* v_row;
+};
 __global__ __launch_bounds__(MTHREADS) void k_adjoint_mixed(SlotView v, int rows1, int r0,
-                                                            const int* __restrict__ atom_of_row,
-                                                            const float* __restrict__ G, float4* __restrict__ f_own) {
+                                                            const int* __restrict__ atom_of_row, MixedForms q,
+                                                            float4* __restrict__ f_own) {
   __shared__ __attribute__((aligned(16))) float cs[MROWS * MSTRIDE];
+  __shared__ __attribute__((aligned(16))) float gs[MROWS * GSTRIDE];
   const int rl = threadIdx.x >> 4, L = threadIdx.x & 15;
   const int local = blockIdx.x * MROWS + rl;
   const int row = r0 + local;
   const int R = rows1 + row;
   const int i = atom_of_row[row];
+  if (i >= 0) {
+    float4 d[NQ4], y[NQ4];
+    const float e = mixed_row_energy(reinterpret_cast<const float4*>(q.D + (size_t)local * ND),
+                                     reinterpret_cast<const float4*>(q.Y + (size_t)local * ND), L, d, y);
+    const float nv = q.nrm[i];
+    const float s2 = nv > 0.f ? 2.f / nv : 0.f;
+    float4* g4 = reinterpret_cast<float4*>(gs + rl * GSTRIDE);
+#pragma unroll
+    for (int k = 0; k < NQ4; ++k) {
+      const int P4 = L + 16 * k;
+      if (P4 < ND / 4)
+        g4[P4] = make_float4(s2 * (y[k].x - e * d[k].x), s2 * (y[k].y - e * d[k].y), s2 * (y[k].z - e * d[k].z),
+                             s2 * (y[k].w - e * d[k].w));
+    }
+    if (L == 0) {
+      q.e_int[i] = e;
+      q.e_row[row] = e;
+    }
+    if (q.P) {
+      const float var = mixed_row_variance(q.P + (size_t)local * (ND / 32), L);
+      if (L == 0) {
+        q.v_int[i] = var;
+        q.v_row[row] = var;
+      }
+    }
+  }
   float c[NLM];
 #pragma unroll
   for (int lm = 0; lm < NLM; ++lm) c[lm] = 0.f;
@@ -61,7 +101,7 @@ __global__ __launch_bounds__(MTHREADS) void k_adjoint_mixed(SlotView v, int rows
 #pragma unroll
   for (int lm = 0; lm < NLM; ++lm) u[lm] = 0.f;
   if (i >= 0) {
-    const float* g = G + (size_t)local * ND;
+    const float* g = gs + rl * GSTRIDE;
     const int sa = L >> 3, na = L & 7;
 #pragma unroll 2
     for (int b = 0; b < 2 * NR; ++b) {
@@ -123,11 +163,13 @@ void adjoint_rows144(flare_state* s) {
   if (s->rows1 > 0) k_adjoint144<<<s->rows1 / 128, TA, 0, s->stream>>>(v, s->atom_of_row1, s->G1, s->f_own);
 }
 
-void adjoint_mixed_chunk(flare_state* s, int r0, int nr) {
+void adjoint_mixed_chunk(flare_state* s, int r0, int nr, bool want_v) {
   const SlotView v = slot_view(s);
   StageTimer tm(s, FLARE_T_FORCEX);
+  MixedForms q{s->Dx, s->Yx, want_v ? s->Px : nullptr, s->nrm, s->e_int, s->v_int, s->e_row + s->rows1,
+               s->v_row + s->rows1};
   if (nr > 0)
-    k_adjoint_mixed<<<nr / MROWS, MTHREADS, 0, s->stream>>>(v, s->rows1, r0, s->atom_of_rowx, s->Gx, s->f_own);
+    k_adjoint_mixed<<<nr / MROWS, MTHREADS, 0, s->stream>>>(v, s->rows1, r0, s->atom_of_rowx, q, s->f_own);
 }
 
 }  // namespace flare

@@ -145,26 +145,27 @@ void bf16_fragments(const std::vector<double>& M, uint16_t* out /* [5][9][2][64]
         }
 }
 
-// Three-way BF16 fragments of one 144-block: B[k][n] = M[k][n] rounded to FP32, then
-// x0 = bf16(x), x1 = bf16(x - x0), x2 = bf16(x - x0 - x1) (both remainders exact in FP32).
-// Layout [ks 5][cb 9][part 3][lane 64][8], K padded to 160 with zeros.
-void bf16x3_fragments(const std::vector<double>& M, uint16_t* out /* [5][9][3][64][8] */) {
-  const int nks = 5, ncb = ND1 / 16;
-  for (int ks = 0; ks < nks; ++ks)
-    for (int cb = 0; cb < ncb; ++cb)
-      for (int lane = 0; lane < 64; ++lane)
-        for (int t = 0; t < 8; ++t) {
-          const int k = ks * 32 + 8 * (lane / 16) + t, n = cb * 16 + lane % 16;
-          const float v = k < ND1 ? (float)M[(size_t)k * ND1 + n] : 0.f;
-          const uint16_t x0 = bf16_rne(v);
-          const float r1 = v - bf16_to_f32(x0);
-          const uint16_t x1 = bf16_rne(r1);
-          const uint16_t x2 = bf16_rne(r1 - bf16_to_f32(x1));
-          const size_t base = ((((size_t)ks * ncb + cb) * 3) * 64 + lane) * 8 + t;
-          out[base] = x0;
-          out[base + 64 * 8] = x1;
-          out[base + 2 * 64 * 8] = x2;
-        }
+// Three-way BF16 fragments of an n x n matrix M (row-major, leading dimension ld) as B
+// operands of v_mfma_f32_16x16x32_bf16: B[k][n] = M[k][n] rounded to FP32, then x0 = bf16(x),
+// x1 = bf16(x - x0), x2 = bf16(x - x0 - x1) (both remainders exact in FP32). Layout
+// [K step][column block][part 3][lane 64][8], K padded to whole 32-wide steps with zeros.
+std::vector<uint16_t> bf16x3_fragments(const double* M, int ld, int n) {
+  const int nks = (n + 31) / 32, ncb = n / 16;
+  std::vector<uint16_t> out((size_t)nks * ncb * 3 * 64 * 8, 0);
+  for (int k = 0; k < n; ++k)
+    for (int cb = 0; cb < ncb; ++cb) {
+      uint16_t* p = &out[(((size_t)(k / 32) * ncb + cb) * 3 * 64 + 16 * (k % 32 / 8)) * 8 + k % 8];
+      for (int c = 0; c < 16; ++c, p += 8) {
+        const float v = (float)M[(size_t)k * ld + cb * 16 + c];
+        const uint16_t x0 = bf16_rne(v);
+        const float r1 = v - bf16_to_f32(x0);
+        const uint16_t x1 = bf16_rne(r1);
+        p[0] = x0;
+        p[64 * 8] = x1;
+        p[2 * 64 * 8] = bf16_rne(r1 - bf16_to_f32(x1));
+      }
+    }
+  return out;
 }
 
 // FP64 fragments of an n x n lower-triangular factor L (row-major) for
@@ -240,9 +241,9 @@ static void state_arrays(flare_state* s, F&& f) {
   f((void**)&s->f_own, R * 16);
   f((void**)&s->G1, R * ND1 * 4);
   f((void**)&s->Dx, X * ND * 4);
-  f((void**)&s->Gx, X * ND * 4);
   f((void**)&s->Yx, X * ND * 4);
-  f((void**)&s->Px, X * 4 * 4);
+  f((void**)&s->Px, X * 17 * 4);
+  f((void**)&s->D6x, X * ND * 6);
   f((void**)&s->Px64, X * 9 * 8);
   f((void**)&s->slice_len, (SL + 1) * 4);
   f((void**)&s->slice_base, (SL + 1) * 4);
@@ -322,19 +323,16 @@ int flare_model_create(flare_model** out, int n_species, int n_rad, int l_max, d
     return FLARE_E_ARG;
   }
   m->vchol = chol;
-  // the mixed buckets: beta, Sigma (and L) of the central species over all 544 components,
-  // row n of each stored part = column n of the matrix
+  // the mixed buckets: beta and, unless the variance runs in FP64, L (or Sigma) of the
+  // central species over all 544 components
   for (int sp = 0; sp < NS; ++sp) {
-    const int parts = chol ? 3 : 2;
-    std::vector<float> w((size_t)parts * ND * ND);
-    for (int part = 0; part < parts; ++part) {
-      const double* M = part == 0 ? beta_host + (size_t)sp * ND * ND
-                                  : part == 1 ? sigma_host + (size_t)sp * ND * ND : Lx[sp].data();
-      for (int n = 0; n < ND; ++n)
-        for (int k = 0; k < ND; ++k) w[((size_t)part * ND + n) * ND + k] = (float)M[(size_t)k * ND + n];
+    const size_t at = (size_t)sp * ND * ND;
+    std::vector<uint16_t> frag = bf16x3_fragments(beta_host + at, ND, ND);
+    int rc = upload((void**)&m->Wx6[sp], frag.data(), frag.size() * sizeof(uint16_t));
+    if (rc == FLARE_OK && !m->var64) {
+      frag = bf16x3_fragments(chol ? Lx[sp].data() : sigma_host + at, ND, ND);
+      rc = upload((void**)&m->Vx6[sp], frag.data(), frag.size() * sizeof(uint16_t));
     }
-    int rc = upload((void**)&m->Wx[sp], w.data(), (size_t)2 * ND * ND * sizeof(float));
-    if (rc == FLARE_OK && chol) rc = upload((void**)&m->Lx[sp], w.data() + (size_t)2 * ND * ND, (size_t)ND * ND * sizeof(float));
     if (rc != FLARE_OK) {
       flare_model_destroy(m);
       return rc;
@@ -364,14 +362,15 @@ int flare_model_create(flare_model** out, int n_species, int n_rad, int l_max, d
   for (int b = 0; b < 4; ++b) {
     const int s = b & 1;
     const int st = b < 2 ? 0 : ND - ND1;
-    std::vector<uint16_t> frag((size_t)5 * ncb * 3 * 64 * 8);
+    const size_t at = (size_t)s * ND * ND + (size_t)st * ND + st;
     int rc = FLARE_OK;
     if (precision == FLARE_FP32 || precision == FLARE_BF16X6_SPLIT) {
-      bf16x3_fragments(sub_block(beta_host + (size_t)s * ND * ND, st, ND1), frag.data());
+      const std::vector<uint16_t> frag = bf16x3_fragments(beta_host + at, ND, ND1);
       rc = upload((void**)&m->W6[b], frag.data(), frag.size() * sizeof(uint16_t));
     }
     if (rc == FLARE_OK && !m->var64) {
-      bf16x3_fragments(chol ? L1[b] : sub_block(sigma_host + (size_t)s * ND * ND, st, ND1), frag.data());
+      const std::vector<uint16_t> frag =
+          chol ? bf16x3_fragments(L1[b].data(), ND1, ND1) : bf16x3_fragments(sigma_host + at, ND, ND1);
       rc = upload((void**)&m->V6[b], frag.data(), frag.size() * sizeof(uint16_t));
     }
     if (rc != FLARE_OK) {
@@ -448,8 +447,8 @@ int flare_model_destroy(flare_model* m) {
     if (m->L64[b]) (void)hipFree(m->L64[b]);
   }
   for (int k = 0; k < 2; ++k) {
-    if (m->Wx[k]) (void)hipFree(m->Wx[k]);
-    if (m->Lx[k]) (void)hipFree(m->Lx[k]);
+    if (m->Wx6[k]) (void)hipFree(m->Wx6[k]);
+    if (m->Vx6[k]) (void)hipFree(m->Vx6[k]);
     if (m->Lx64[k]) (void)hipFree(m->Lx64[k]);
   }
   delete m;
@@ -681,10 +680,10 @@ static void mixed_rows(flare_state* s, float* d_out, bool want_e, bool want_v, b
   for (int r0 = 0; r0 < s->rowsx; r0 += s->mix_cap) {
     const int nr = std::min(s->mix_cap, s->rowsx - r0);
     desc_mixed_chunk(s, r0, nr, d_out);
-    forms_mixed_chunk(s, r0, nr, want_e || want_f, want_v);
-    if (want_f) adjoint_mixed_chunk(s, r0, nr);
+    forms_mixed_chunk(s, r0, nr, want_e || want_f, want_v, !want_f);
+    if (want_f) adjoint_mixed_chunk(s, r0, nr, want_v && !s->model->var64);
   }
-  // with one chunk the workspace keeps the gradients of these positions for a later backward
+  // with one chunk the workspace keeps beta d of these positions for a later backward
   if ((want_e || want_f) && s->rowsx <= s->mix_cap) s->gx_gen = s->pos_gen;
 }
 
@@ -786,7 +785,7 @@ int flare_forces(flare_state* s, const double* cell_scale, float* fx, float* fy,
     // the 144-wide rows from the gradients the energies left resident, the mixed rows
     // recomputed chunk by chunk
     adjoint_rows144(s);
-    if (s->gx_gen == s->pos_gen) adjoint_mixed_chunk(s, 0, s->rowsx);
+    if (s->gx_gen == s->pos_gen) adjoint_mixed_chunk(s, 0, s->rowsx, false);
     else mixed_rows(s, nullptr, true, false, true);
     s->w_gen = s->pos_gen;
   }
@@ -1033,8 +1032,8 @@ int flare_memory_bytes(const flare_model* m, const flare_state* s, long long* by
   ARG(bytes, "null pointer");
   long long b = 0;
   if (m) {
-    b += 2LL * 2 * ND * ND * sizeof(float);                              // Wx
-    if (m->vchol) b += 2LL * ND * ND * sizeof(float);                    // Lx
+    for (int k = 0; k < 2; ++k)
+      b += ((m->Wx6[k] ? 1LL : 0LL) + (m->Vx6[k] ? 1LL : 0LL)) * 3 * ND * ND * sizeof(uint16_t);
     if (m->precision == FLARE_BF16_SPLIT) b += 4LL * 5 * 9 * 2 * 64 * 8 * sizeof(uint16_t);
     if (m->precision == FLARE_FP8_SPLIT) b += 4LL * 5 * 9 * 2 * 64 * sizeof(uint64_t);
     for (int k = 0; k < 4; ++k)

@@ -9,6 +9,7 @@
 // (fused.hip).
 // Pair geometry: positions are FP64; Delta = (x_j - x_i) + s*L is formed in FP64 and
 // rounded to FP32 before the basis is evaluated.
+#include "bf16x3.h"
 #include "mixed.h"
 #include "state.h"
 
@@ -19,10 +20,11 @@ namespace {
 // One mixed row per 16 lanes (mixed.h): channel densities into LDS, then the 136 B2
 // channel pairs spread over the row's lanes (pair P = L + 16q), the norm summed in FP64
 // across the lanes, and the normalised row written as float4 per pair: into the chunk's
-// workspace D (row - r0) and, when exporting, into d_out at the atom's caller index.
+// workspace D (row - r0), in three BF16 parts into D6 (the quadratic forms' operand) and, when exporting, into d_out at the atom's caller index.
 __global__ __launch_bounds__(MTHREADS) void k_desc_mixed(SlotView v, int rows1, int r0,
                                                          const int* __restrict__ atom_of_row,
                                                          const int* __restrict__ perm, float* __restrict__ D,
+                                                         uint4* __restrict__ D6,
                                                          float* __restrict__ nrm_out, float* __restrict__ d_out) {
   __shared__ __attribute__((aligned(16))) float cs[MROWS * MSTRIDE];
   const int rl = threadIdx.x >> 4, L = threadIdx.x & 15;
@@ -72,6 +74,7 @@ __global__ __launch_bounds__(MTHREADS) void k_desc_mixed(SlotView v, int rows1, 
     if (P < NPAIR) {
       const float4 o = make_float4(d[q].x * scale, d[q].y * scale, d[q].z * scale, d[q].w * scale);
       out[P] = o;
+      store_d6(D6, local, P, o);
       if (ext) ext[P] = o;
     }
   }
@@ -143,7 +146,7 @@ void desc_mixed_chunk(flare_state* s, int r0, int nr, float* d_out) {
   const SlotView v = slot_view(s);
   StageTimer tm(s, FLARE_T_DESCX);
   if (nr > 0)
-    k_desc_mixed<<<nr / MROWS, MTHREADS, 0, s->stream>>>(v, s->rows1, r0, s->atom_of_rowx, s->perm, s->Dx, s->nrm,
+    k_desc_mixed<<<nr / MROWS, MTHREADS, 0, s->stream>>>(v, s->rows1, r0, s->atom_of_rowx, s->perm, s->Dx, s->D6x, s->nrm,
                                                          d_out);
 }
 

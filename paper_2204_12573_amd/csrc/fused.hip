@@ -28,13 +28,11 @@
 #include <type_traits>
 
 #include "adjoint.h"
+#include "bf16x3.h"
 #include "state.h"
 
 namespace flare {
 namespace {
-
-typedef float f4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 
 constexpr int FT = 256;       // threads
 constexpr int FR = 128;       // rows per tile
@@ -77,17 +75,6 @@ struct FusedArgs {
 // steps; in the last one lane groups 2-3 (k = 144..159) feed zeros and the stored beta is
 // zero there. Lane (m, q) supplies A[m][32t + 8q .. +7] and B[32t + 8q .. +7][n].
 constexpr int NKS = 5;
-
-typedef float f2v __attribute__((ext_vector_type(2)));
-typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
-typedef unsigned int u4v __attribute__((ext_vector_type(4)));
-
-// two FP32 values to a packed BF16 pair (round to nearest even), and back
-__device__ __forceinline__ unsigned int pk_bf16(float a, float b) {
-  return __builtin_bit_cast(unsigned int, __builtin_convertvector((f2v){a, b}, bf2));
-}
-__device__ __forceinline__ float bf16_lo(unsigned int p) { return __builtin_bit_cast(float, p << 16); }
-__device__ __forceinline__ float bf16_hi(unsigned int p) { return __builtin_bit_cast(float, p & 0xffff0000u); }
 
 __device__ __forceinline__ void split8(const float* p, bool zero, bf8& hi, bf8& lo) {
   float v[8];
@@ -165,34 +152,9 @@ __device__ __forceinline__ void mfma_pass_bf16(const float* As, const uint4* __r
   }
 }
 
-// Three-way BF16 form of both passes: x = x0 + x1 + x2 holds all 24 significant bits of
-// an FP32 value exactly (x0 and x1 round the remainder of the previous parts to 8 bits,
-// the remainders are exact in FP32, and the last one fits 8 bits), and the same for the
-// model matrix. Of the nine part
-// products the six with a part-index sum <= 2 are formed on v_mfma_f32_16x16x32_bf16
-// (exact products, FP32 accumulation); the dropped x1 w2 + x2 w1 + x2 w2 are below
-// 2^-23 |x||w|, the size of an FP32 rounding. K = 144 runs as five 32-wide steps
-// as in the two-way form; column blocks go in groups of three so that the six products
-// of a block are five other MFMAs apart.
-// x0 = bf16(v), x1 = bf16(v - x0), x2 = v - x0 - x1: the last remainder has at most 8
-// significant bits, so its BF16 pattern is the upper half of its FP32 pattern (exact)
-__device__ __forceinline__ void split8x3(const float4 (&u)[2], bf8& x0, bf8& x1, bf8& x2) {
-  const float v[8] = {u[0].x, u[0].y, u[0].z, u[0].w, u[1].x, u[1].y, u[1].z, u[1].w};
-  u4v p0, p1, p2;
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    p0[t] = pk_bf16(v[2 * t], v[2 * t + 1]);
-    const float ra = v[2 * t] - bf16_lo(p0[t]), rb = v[2 * t + 1] - bf16_hi(p0[t]);
-    p1[t] = pk_bf16(ra, rb);
-    const float sa = ra - bf16_lo(p1[t]), sb = rb - bf16_hi(p1[t]);
-    p2[t] = __builtin_amdgcn_perm(__builtin_bit_cast(unsigned int, sb), __builtin_bit_cast(unsigned int, sa),
-                                  0x07060302u);
-  }
-  x0 = __builtin_bit_cast(bf8, p0);
-  x1 = __builtin_bit_cast(bf8, p1);
-  x2 = __builtin_bit_cast(bf8, p2);
-}
-
+// Three-way BF16 products of the FP32 and three-way BF16 forms (bf16x3.h), model and rows in
+// three parts. K = 144 runs as five 32-wide steps as in the two-way form; column blocks go in
+// groups of three so that the six products of a block are five other MFMAs apart.
 // A operand of K step ks for row block i: 8 FP32 values (zeros past K = 144)
 __device__ __forceinline__ void load_a8(const float* As, int wave, int l16, int grp, int i, int ks,
                                         float4 (&u)[2]) {

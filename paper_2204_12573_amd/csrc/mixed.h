@@ -37,6 +37,28 @@ __device__ __forceinline__ void mixed_channel_density(const SlotView& v, int R, 
   });
 }
 
+// The 16 lanes of a mixed row hold its 136 groups of four components as group L + 16 q of
+// lane L. Energy of the row from its descriptor d and y = beta d, in a fixed order (all 16
+// lanes get the sum).
+constexpr int NQ4 = (ND / 4 + 15) / 16;    // 9
+__device__ __forceinline__ float mixed_row_energy(const float4* __restrict__ d4, const float4* __restrict__ y4, int L,
+                                                  float4 (&d)[NQ4], float4 (&y)[NQ4]) {
+#pragma unroll
+  for (int k = 0; k < NQ4; ++k) {
+    const int P4 = L + 16 * k;
+    d[k] = P4 < ND / 4 ? d4[P4] : make_float4(0.f, 0.f, 0.f, 0.f);
+    y[k] = P4 < ND / 4 ? y4[P4] : make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  float e = 0.f;
+#pragma unroll
+  for (int k = 0; k < NQ4; ++k) e += (d[k].x * y[k].x + d[k].y * y[k].y) + (d[k].z * y[k].z + d[k].w * y[k].w);
+  return sum16(e);
+}
+// Variance of the row from the shares of its 17 column pairs.
+__device__ __forceinline__ float mixed_row_variance(const float* __restrict__ p, int L) {
+  return sum16(p[L] + (L == 0 ? p[16] : 0.f));
+}
+
 // Channels (a, b) of packed B2 pair P of a 544-wide row: (H,H) pairs 0..35 (na <= nb,
 // row-major), (H,Pt) pairs 36..99 (row-major, a = H channel), (Pt,Pt) pairs 100..135.
 __device__ __forceinline__ void mixed_pair_channels(int P, int& a, int& b) {

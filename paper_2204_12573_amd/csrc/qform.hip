@@ -1,252 +1,304 @@
 // Mapped quadratic forms of the mixed-environment rows (paper, Eq. 1 and Eq. 2 after the
 // exact mapping of Section V.B): for the 544-wide descriptor rows D of a bucket,
-//   Y = D beta_s (dense GEMM on the FP32 matrix cores, FP32 accumulate), e_i = Y_i . D_i,
+//   Y = D beta_s (FP32-accurate products in three BF16 parts, see bf16x3.h), e_i = Y_i . D_i,
 //   V_i = D_i . Sigma_s D_i, or |L_s^T D_i|^2 with the Cholesky factor of Sigma_s,
-//   g_i = (2/|d~_i|) (Y_i - e_i d_i)  (de_i/dd~_i, used by the adjoint; k_qform_finish).
-// A launch covers column tiles of 272: the beta part first, then the Sigma part; each
-// tile writes its partial row sums, the beta tiles also Y.
-//
-// Tiling: a work-group of 4 waves owns 64 RB rows; each wave owns RB 16-row blocks x CB
-// 16-column blocks, accumulated by v_mfma_f32_16x16x4_f32. Three work-groups share a CU
-// (LDS allows three; the B fragments are read in groups of four column blocks so that the
-// registers allow three waves per SIMD as well). K advances in
-// chunks of 16 staged in LDS (double-buffered). Inside a chunk the four k-steps are
-// interleaved so that each lane reads its four k-values of A and of B with one
-// 128-bit LDS load: k-step t, lane group g uses k = 4g + t (the same map for A and B,
-// which is all a sum over k requires). LDS rows are padded to 20 floats, which spreads
-// the eight 16-byte reads of each lane octet over distinct banks.
+//   g_i = (2/|d~_i|) (Y_i - e_i d_i)  (de_i/dd~_i, formed from Y and D by the adjoint kernel).
+// The rows come in fragment order (D6), already split by the kernel that forms them, and
+// so do the model matrices: [K step 17][column block 34][part 3][lane 64] x 8 bf16. Columns
+// go in pairs of 16-wide blocks: pair m is columns 32 m .. 32 m + 31, and of a lower-
+// triangular factor only the K steps >= m of it are non-zero. Two kernels share the work:
+//   k_forms544      many rows: a work-group of four waves takes 128 rows x 4 or 5 column
+//                   pairs, 32 rows a wave; the matrix fragments of a K step are shared
+//                   through LDS (copied there by the loads themselves, two buffers), the
+//                   row fragments go to registers one K step ahead
+//   k_forms544_few  few rows: a wave takes one 16-row block x one column pair on its own,
+//                   three K steps of fragments in flight, no LDS and no barrier
+// Both form every product, partial sum and row in the same order, so a row's results do
+// not depend on which of them ran.
 #include <algorithm>
-#include <type_traits>
 
+#include "bf16x3.h"
+#include "mixed.h"
 #include "state.h"
 
 namespace flare {
 namespace {
 
-typedef float f4 __attribute__((ext_vector_type(4)));
-
 constexpr int NTQ = 256;
-constexpr int KC = 16;          // K chunk
-constexpr int LDSW = KC + 4;    // padded LDS row (floats)
+constexpr int XNB = ND / 16;                 // 34 column blocks
+constexpr int XNP = ND / 32;                 // 17 column pairs
+constexpr int XTILES = 4;                    // column tiles of the many-row kernel
+constexpr int XTP = 5;                       // pairs of its widest tile
+// Up to FEW_ROWS one wave per 16 rows and column pair: each reads 9 KB a K step through L2 for
+// 12 products, so its time grows with the rows once the 1,024 SIMDs are filled. Energies and
+// variances in us, few-row against many-row kernel: 27 : 32 for 2,176 rows, 36 : 32 for 3,072.
+constexpr int FEW_ROWS = 2560;
 
-
-struct QArgs {
-  const float* D;        // [rows][KD]
-  const int* aor;        // atom of row (-1 padding)
-  float* Y;              // [rows][KD]      beta-part products
-  float* P;              // [rows][4]       partial row sums of each column tile
-  int mode;              // bit 0: beta part, bit 1: Sigma part
-  int sumsq;             // Sigma part given as its Cholesky factor L: V = |d L|^2
-  int nbk;               // buckets in this launch
-  int row0[4];           // first row of each bucket (padded to TM)
-  int row1[4];           // one past its last padded row
-  const float* W[4];     // [(parts)*KD][KD] row n = column n of [beta | Sigma]
-  const float* L[4];     // sumsq: [KD][KD] row n = column n of the Cholesky factor of Sigma
+struct XArgs {
+  const uint4* D6;       // rows in fragment order
+  const float* D;        // the same rows in FP32, [rows][544] (V from the full Sigma)
+  const int* aor;        // atom of row (-1: padding), or null: rows 0 .. n_given - 1 are given
+  int n_given;
+  int rows;              // padded rows (a multiple of 128)
+  int split_row;         // rows >= split_row belong to the second bucket (Pt centre)
+  int mode;              // bit 0: beta part, bit 1: variance part
+  int tri;               // the variance part is the Cholesky factor L: V = |d L|^2
+  const uint4* W[2];     // per bucket: beta
+  const uint4* V[2];     // per bucket: L or Sigma
+  float* Y;              // [rows][544] D beta
+  float* P;              // [rows][17] V partials of the column pairs
 };
 
-template <int KD, int CB, int RB>
-__global__ __launch_bounds__(NTQ, 3) void k_qform(QArgs q) {
-  constexpr int TM = 4 * RB * 16;              // rows per work-group
-  constexpr int NC = CB * 16;                  // columns per work-group
-  constexpr int NCHUNK = KD / KC;
-  static_assert(KD % KC == 0, "K must be a multiple of the chunk");
-  __shared__ __attribute__((aligned(16))) float As[2][TM * LDSW];
-  __shared__ __attribute__((aligned(16))) float Bs[2][NC * LDSW];
+// acc += a b over one K step: the six part products, smallest first
+__device__ __forceinline__ void mfma6(const bf8 (&a)[3], const bf8 (&b)[3], f4& acc) {
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[2], acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], b[1], acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[1], acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[2], b[0], acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], b[0], acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[0], acc, 0, 0, 0);
+}
 
-  const int tile = blockIdx.x;
-  const int ntile = blockIdx.y;
-  const int row0 = tile * TM;
-  // column tiles: the beta part first (if any), then the Sigma part, from L when sumsq
-  const int nbeta = (q.mode & 1) ? KD / NC : 0;
-  const bool lpart = q.sumsq && ntile >= nbeta;
-  // bucket of this tile (static indexing keeps the argument arrays out of scratch)
-  const float* Wb = lpart ? q.L[0] : q.W[0];
-#pragma unroll
-  for (int k = 1; k < 4; ++k)
-    if (k < q.nbk && row0 >= q.row0[k] && row0 < q.row1[k]) Wb = lpart ? q.L[k] : q.W[k];
-  const int ct = lpart ? ntile - nbeta : ntile;
-  const float* __restrict__ W = Wb + (size_t)ct * NC * KD;
-  const float* __restrict__ D = q.D;
+// Rows are filled from the start of their bucket: a 16-row block without an atom in its
+// first row holds padding only.
+__device__ __forceinline__ bool block_empty(const XArgs& q, int row0) {
+  return q.aor ? q.aor[row0] < 0 : row0 >= q.n_given;
+}
 
-  const int t = threadIdx.x;
-  const int lane = t & 63, wave = t >> 6;
+// Results of one column pair m of one 16-row block (lane (l16, grp): column 16 j + l16 of the
+// pair, rows 4 grp + r): Y, or the pair's share of V.
+__device__ __forceinline__ void store_pair(const XArgs& q, bool beta, int row0, int m, int lane, const f4 (&acc)[2]) {
   const int l16 = lane & 15, grp = lane >> 4;
-
-  // global -> register staging of one K chunk: A TM*KC/4 float4, B NC*KC/4 float4 (the
-  // last B round is partial); kept in named registers (an indexed array ends in scratch)
-  constexpr int A_F4 = TM * KC / 4;
-  constexpr int B_F4 = NC * KC / 4;
-  static_assert(A_F4 == NTQ, "one A float4 per thread");
-  static_assert(B_F4 > 4 * NTQ && B_F4 <= 5 * NTQ, "four full B rounds and a partial one");
-  float4 ra, rb0, rb1, rb2, rb3, rb4;
-  const bool b4 = t + 4 * NTQ < B_F4;
-  auto bsrc = [&](int u, int k0) {
-    const int idx = t + u * NTQ;
-    return reinterpret_cast<const float4*>(W + (size_t)(idx >> 2) * KD + k0 + (idx & 3) * 4);
-  };
-  auto bdst = [&](int u, int buf) {
-    const int idx = t + u * NTQ;
-    return reinterpret_cast<float4*>(&Bs[buf][(idx >> 2) * LDSW + (idx & 3) * 4]);
-  };
-#define QF_GLOAD(chunk)                                                                       \
-  do {                                                                                        \
-    const int k0_ = (chunk) * KC;                                                             \
-    ra = *reinterpret_cast<const float4*>(D + (size_t)(row0 + (t >> 2)) * KD + k0_ + (t & 3) * 4); \
-    rb0 = *bsrc(0, k0_);                                                                      \
-    rb1 = *bsrc(1, k0_);                                                                      \
-    rb2 = *bsrc(2, k0_);                                                                      \
-    rb3 = *bsrc(3, k0_);                                                                      \
-    if (b4) rb4 = *bsrc(4, k0_);                                                              \
-  } while (0)
-
-#define QF_LSTORE(buf)                                                                        \
-  do {                                                                                        \
-    *reinterpret_cast<float4*>(&As[buf][(t >> 2) * LDSW + (t & 3) * 4]) = ra;                 \
-    *bdst(0, buf) = rb0;                                                                      \
-    *bdst(1, buf) = rb1;                                                                      \
-    *bdst(2, buf) = rb2;                                                                      \
-    *bdst(3, buf) = rb3;                                                                      \
-    if (b4) *bdst(4, buf) = rb4;                                                              \
-  } while (0)
-
-  f4 acc[RB][CB];
 #pragma unroll
-  for (int i = 0; i < RB; ++i)
-#pragma unroll
-    for (int j = 0; j < CB; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
-
-  // with W = L (row n of W = column n of L, zero for k < n) the chunks k < first column vanish
-  const int c0 = lpart ? (ct * NC) / KC : 0;
-  QF_GLOAD(c0);
-  QF_LSTORE(c0 & 1);
-  __syncthreads();
-  // the main loop once without the triangular skip (beta tiles) and once with it (L tiles),
-  // so that the beta tiles' MFMAs carry no per-block test
-  auto main_loop = [&](auto lp) {
-  constexpr bool LP = decltype(lp)::value;
-  for (int c = c0; c < NCHUNK; ++c) {
-    const int buf = c & 1;
-    if (c + 1 < NCHUNK) QF_GLOAD(c + 1);
-    float4 a[RB];
-#pragma unroll
-    for (int i = 0; i < RB; ++i)
-      a[i] = *reinterpret_cast<const float4*>(&As[buf][(wave * RB * 16 + i * 16 + l16) * LDSW + 4 * grp]);
-    // B fragments in groups of four column blocks, each group used for all four k-steps
-    // (consecutive MFMAs still write different accumulators), so only a group is live
-#pragma unroll
-    for (int j0 = 0; j0 < CB; j0 += 4) {
-      float4 bg[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (j0 + u < CB) bg[u] = *reinterpret_cast<const float4*>(&Bs[buf][((j0 + u) * 16 + l16) * LDSW + 4 * grp]);
-#define QF_STEP(C)                                                                              \
-  _Pragma("unroll") for (int u = 0; u < 4; ++u) {                                              \
-    const int j = j0 + u;                                                                      \
-    if (j >= CB || (LP && c < ct * CB + j)) continue;                                          \
-    _Pragma("unroll") for (int i = 0; i < RB; ++i)                                             \
-      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i].C, bg[u].C, acc[i][j], 0, 0, 0);   \
-  }
-      QF_STEP(x)
-      QF_STEP(y)
-      QF_STEP(z)
-      QF_STEP(w)
-#undef QF_STEP
-    }
-    if (c + 1 < NCHUNK) QF_LSTORE(buf ^ 1);
-    __syncthreads();
-  }
-  };
-  if (lpart) main_loop(std::true_type{});
-  else main_loop(std::false_type{});
-
-  // ---- epilogue: lane holds Y[row = 4*grp + r][col = 16*j + l16] of each block ----
-  // A tile lies wholly in the beta part or wholly in the Sigma / L part (272 divides 544).
-  // The D values of a row dot are loaded together before they are used (no test between a
-  // load and its use); the factor's part needs none (a sum of squares).
-  const bool has_e = q.mode & 1;
-  const int col_base = ntile * NC;
-  const bool beta_tile = has_e && col_base < KD;
-  const bool squares = !beta_tile && q.sumsq;
-  const int kbase = beta_tile ? col_base : col_base - (has_e ? KD : 0);   // the tile's first column of D
-#pragma unroll
-  for (int i = 0; i < RB; ++i) {
-    float ps[4] = {0.f, 0.f, 0.f, 0.f};
-    if (squares) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int j = 0; j < CB; ++j) ps[r] += acc[i][j][r] * acc[i][j][r];
+  for (int r = 0; r < 4; ++r) {
+    const int row = row0 + 4 * grp + r;
+    const size_t at = (size_t)row * ND + 32 * m + l16;
+    if (beta) {
+      q.Y[at] = acc[0][r];
+      q.Y[at + 16] = acc[1][r];
     } else {
-      float dv[4][CB];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float* drow = D + (size_t)(row0 + wave * RB * 16 + i * 16 + 4 * grp + r) * KD + kbase + l16;
-#pragma unroll
-        for (int j = 0; j < CB; ++j) dv[r][j] = drow[j * 16];
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int j = 0; j < CB; ++j) ps[r] += acc[i][j][r] * dv[r][j];
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) ps[r] = sum16(ps[r]);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int row = row0 + wave * RB * 16 + i * 16 + 4 * grp + r;
-      if (l16 == 0) q.P[(size_t)row * 4 + ntile] = ps[r];
-      if (beta_tile) {
-        float* yrow = q.Y + (size_t)row * KD;
-#pragma unroll
-        for (int j = 0; j < CB; ++j) yrow[col_base + j * 16 + l16] = acc[i][j][r];
-      }
+      float s = q.tri ? fmaf(acc[1][r], acc[1][r], acc[0][r] * acc[0][r])
+                      : fmaf(acc[1][r], q.D[at + 16], acc[0][r] * q.D[at]);
+      s = sum16(s);
+      if (l16 == 0) q.P[(size_t)row * XNP + m] = s;
     }
   }
 }
 
-#undef QF_GLOAD
-#undef QF_LSTORE
+// One wave: 16 rows x one column pair. Fragments of three K steps are in flight (36
+// registers each); the waves of a work-group take neighbouring row blocks of one pair, so
+// its matrix fragments come from L1. Bound by the latency of the first loads: 17 K steps of
+// 12 products are 3.3 k cycles. 256 rows: 6 us, 1 k rows: 10 us; the many-row kernel needs 17
+// steps of 1,920 cycles and a barrier whatever the rows (the FP32 one took 62 us).
+__global__ __launch_bounds__(NTQ) void k_forms544_few(XArgs q) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int nrb = q.rows >> 4;
+  const int task = blockIdx.x * 4 + wave;
+  const int rb = task % nrb;
+  int m = task / nrb;
+  const int nbeta = (q.mode & 1) ? XNP : 0;
+  if (m >= nbeta + ((q.mode & 2) ? XNP : 0)) return;
+  const bool beta = m < nbeta;
+  if (!beta) m -= nbeta;
+  const int row0 = rb * 16;
+  if (block_empty(q, row0)) return;
+  const int bk = row0 >= q.split_row ? 1 : 0;
+  const uint4* __restrict__ W = (beta ? (bk ? q.W[1] : q.W[0]) : (bk ? q.V[1] : q.V[0])) + (size_t)2 * m * 3 * 64 + lane;
+  const uint4* __restrict__ A = q.D6 + (size_t)rb * XKS * 3 * 64 + lane;
+  constexpr int PD = 3;
+  bf8 a[PD][3], b[PD][2][3];
+  auto load = [&](int ks, int u) {
+    const int k = min(ks, XKS - 1);
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      a[u][t] = __builtin_bit_cast(bf8, A[(k * 3 + t) * 64]);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) b[u][j][t] = __builtin_bit_cast(bf8, W[(((size_t)k * XNB + j) * 3 + t) * 64]);
+    }
+  };
+  f4 acc[2] = {f4{0.f, 0.f, 0.f, 0.f}, f4{0.f, 0.f, 0.f, 0.f}};
+  const int ks0 = !beta && q.tri ? m : 0;
+#pragma unroll
+  for (int u = 0; u < PD; ++u) load(ks0 + u, u);
+  for (int ks = ks0; ks < XKS; ks += PD) {
+#pragma unroll
+    for (int u = 0; u < PD; ++u) {
+      if (ks + u < XKS) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) mfma6(a[u], b[u][j], acc[j]);
+      }
+      load(ks + u + PD, u);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  store_pair(q, beta, row0, m, lane, acc);
+}
 
-// Finish the split path (544-wide rows): sum the partial row-dots, form g.
-__global__ __launch_bounds__(256) void k_qform_finish(int rows, int mode, int ntiles,
-                                                      const float* __restrict__ D,
-                                                      const float* __restrict__ Y,
-                                                      const float* __restrict__ P,
-                                                      const int* __restrict__ aor, int n_given,
-                                                      const float* __restrict__ nrm,
-                                                      float* __restrict__ G,
-                                                      float* __restrict__ e_int,
-                                                      float* __restrict__ v_int,
-                                                      float* __restrict__ e_row,
-                                                      float* __restrict__ v_row) {
-  // one wave per row
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
+typedef __attribute__((address_space(1))) const void gvoid;
+typedef __attribute__((address_space(3))) void lvoid;
+
+// 128 rows x up to five column pairs. Per K step a wave forms 2 x 10 blocks x 6 products
+// (1,920 cycles of its SIMD's matrix core) from 6 KB of row fragments of its own and 30 KB
+// of matrix fragments in LDS; two work-groups a CU. Energies and variances of 13,440 rows:
+// 70 us, 47 % of the SIMD cycles matrix work (the work-groups' unequal lengths leave 1.5 of 2
+// waves on a SIMD on average), against 140 us on FP32 matrix instructions.
+__global__ __launch_bounds__(NTQ, 2) void k_forms544(XArgs q) {
+  __shared__ __attribute__((aligned(16))) uint4 Bs[2][XTP * 2 * 3 * 64];
+  // Work-group g runs on XCD g % 8, which takes every eighth row tile. Its tiles go column
+  // tile by column tile, the longest first (a factor's later columns have fewer K steps), so
+  // that the second round of work-groups on a CU is the short ones: row tile by row tile
+  // left 1.1 of the 2 waves a SIMD can hold on average, 86 us for 13 k rows.
+  const int x = blockIdx.x & 7, nrt = q.rows >> 7;
+  const int nrx = (nrt - x + 7) >> 3;
+  if (nrx <= 0) return;
+  const int order = (blockIdx.x >> 3) / nrx;
+  const int rt = x + 8 * ((blockIdx.x >> 3) % nrx);
+  bool beta = (q.mode & 1) != 0;
+  int ct = order;
+  if (q.mode == 3) {             // beta 0, variance 0, beta 1, 2, 3, variance 1, 2, 3
+    beta = order == 0 || (order >= 2 && order <= 4);
+    ct = order < 2 ? 0 : (order <= 4 ? order - 1 : order - 4);
+  }
+  if (order >= XTILES * (q.mode == 3 ? 2 : 1)) return;
+  const int m0 = ct == 0 ? 0 : 4 * ct + 1;          // pairs 0-4, 5-8, 9-12, 13-16
+  const int np = ct == 0 ? 5 : 4;
+  const int row0 = rt * 128;
+  if (block_empty(q, row0)) return;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int bk = row0 >= q.split_row ? 1 : 0;
+  const uint4* __restrict__ W = (beta ? (bk ? q.W[1] : q.W[0]) : (bk ? q.V[1] : q.V[0])) + (size_t)2 * m0 * 3 * 64;
+  const bool tri = !beta && q.tri;
+  const int ks0 = tri ? m0 : 0;
+  const int wrow = row0 + wave * 32;
+  const bool idle = block_empty(q, wrow);           // padding rows only: copies, no products
+  const uint4* __restrict__ A = q.D6 + (size_t)(wrow >> 4) * XKS * 3 * 64 + lane;
+  f4 acc[2][XTP][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int p = 0; p < XTP; ++p)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[i][p][j] = f4{0.f, 0.f, 0.f, 0.f};
+  // the K step's fragments are contiguous in W and in LDS; wave w copies every fourth 1 KB
+  auto copy_b = [&](int ks, int buf) {
+    const uint4* src = W + (size_t)ks * XNB * 3 * 64 + lane;
+    for (int f = wave; f < np * 6; f += 4)
+      __builtin_amdgcn_global_load_lds((gvoid*)(src + f * 64), (lvoid*)(&Bs[buf][f * 64]), 16, 0, 0);
+  };
+  bf8 a[2][3], an[2][3];
+  auto load_a = [&](int ks, bf8 (&x)[2][3]) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int t = 0; t < 3; ++t) x[i][t] = __builtin_bit_cast(bf8, A[((size_t)(i * XKS + ks) * 3 + t) * 64]);
+  };
+  // all waves' copies of the next K step have landed before any wave reads them (the copies
+  // count as vector memory operations, which a barrier alone does not wait for)
+  auto copies_done = [] {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+  };
+  copy_b(ks0, ks0 & 1);
+  load_a(ks0, a);
+  copies_done();
+  for (int ks = ks0; ks < XKS; ++ks) {
+    const int buf = ks & 1;
+    const int kn = min(ks + 1, XKS - 1);
+    if (ks + 1 < XKS) copy_b(kn, buf ^ 1);
+    load_a(kn, an);
+    if (!idle) {
+      // the next pair's fragments are read from LDS while this pair's products run
+      bf8 bA[2][3], bB[2][3];
+      auto load_b = [&](int p, bf8 (&b)[2][3]) {
+        const int pp = min(p, np - 1);
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int t = 0; t < 3; ++t) b[j][t] = __builtin_bit_cast(bf8, Bs[buf][((2 * pp + j) * 3 + t) * 64 + lane]);
+      };
+      load_b(0, bA);
+#pragma unroll
+      for (int p = 0; p < XTP; ++p) {
+        bf8 (&b)[2][3] = (p & 1) ? bB : bA;
+        load_b(p + 1, (p & 1) ? bA : bB);
+        __builtin_amdgcn_sched_barrier(0);
+        if (p >= np || (tri && ks < m0 + p)) continue;
+        // the four blocks' products in turn (each accumulator's in the order of mfma6)
+#define X_PROD(PA, PB)                                                                                  \
+  _Pragma("unroll") for (int i = 0; i < 2; ++i) _Pragma("unroll") for (int j = 0; j < 2; ++j)          \
+      acc[i][p][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i][PA], b[j][PB], acc[i][p][j], 0, 0, 0);
+        X_PROD(0, 2)
+        X_PROD(1, 1)
+        X_PROD(0, 1)
+        X_PROD(2, 0)
+        X_PROD(1, 0)
+        X_PROD(0, 0)
+#undef X_PROD
+      }
+    }
+    copies_done();
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int t = 0; t < 3; ++t) a[i][t] = an[i][t];
+  }
+  if (idle) return;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    if (i == 1 && block_empty(q, wrow + 16)) break;
+#pragma unroll
+    for (int p = 0; p < XTP; ++p)
+      if (p < np) store_pair(q, beta, wrow + 16 * i, m0 + p, lane, acc[i][p]);
+  }
+}
+
+void launch_forms544(const XArgs& q, hipStream_t st) {
+  const int parts = ((q.mode & 1) ? 1 : 0) + ((q.mode & 2) ? 1 : 0);
+  if (q.rows <= FEW_ROWS) {
+    const int tasks = (q.rows / 16) * XNP * parts;
+    k_forms544_few<<<(tasks + 3) / 4, NTQ, 0, st>>>(q);
+  } else {
+    const int per_xcd = (q.rows / 128 + 7) / 8;      // row tiles of the fullest XCD
+    k_forms544<<<8 * per_xcd * XTILES * parts, NTQ, 0, st>>>(q);
+  }
+}
+
+// Given vectors in fragment order (rows past n: zeros, as their FP32 copies).
+__global__ __launch_bounds__(NTQ) void k_split544(int rows, const float* __restrict__ D, uint4* __restrict__ D6) {
+  const int idx = blockIdx.x * NTQ + threadIdx.x;      // (row, packed group of four)
+  if (idx >= rows * (ND / 4)) return;
+  const int row = idx / (ND / 4), P = idx % (ND / 4);
+  store_d6(D6, row, P, reinterpret_cast<const float4*>(D)[idx]);
+}
+
+// e_i = Y_i . D_i and V_i from the column pairs' shares (fixed orders), 16 lanes a row, for
+// the calls without forces (with them the adjoint kernel forms both on its way to g).
+__global__ __launch_bounds__(256) void k_forms544_finish(int rows, int mode, const float* __restrict__ D,
+                                                         const float* __restrict__ Y, const float* __restrict__ P,
+                                                         const int* __restrict__ aor, int n_given,
+                                                         float* __restrict__ e_int, float* __restrict__ v_int,
+                                                         float* __restrict__ e_row, float* __restrict__ v_row) {
+  const int row = blockIdx.x * 16 + (threadIdx.x >> 4);
+  const int L = threadIdx.x & 15;
   if (row >= rows) return;
   const int atom = aor ? aor[row] : (row < n_given ? row : -1);   // no table: given vectors
   if (atom < 0) return;
-  const float* p = P + (size_t)row * 4;
-  const bool has_e = mode & 1, has_v = mode & 2;
-  const int half = ntiles / ((has_e && has_v) ? 2 : 1);
-  float e = 0.f, v = 0.f;
-  if (has_e) {
-    for (int k = 0; k < half; ++k) e += p[k];
+  if (mode & 2) {
+    const float v = mixed_row_variance(P + (size_t)row * XNP, L);
+    if (L == 0) {
+      v_int[atom] = v;
+      v_row[row] = v;
+    }
   }
-  if (has_v) {
-    const int first = has_e ? half : 0;
-    for (int k = first; k < first + half; ++k) v += p[k];
+  if (mode & 1) {
+    float4 d[NQ4], y[NQ4];
+    const float e = mixed_row_energy(reinterpret_cast<const float4*>(D + (size_t)row * ND),
+                                     reinterpret_cast<const float4*>(Y + (size_t)row * ND), L, d, y);
+    if (L == 0) {
+      e_int[atom] = e;
+      e_row[row] = e;
+    }
   }
-  if (lane == 0) {
-    if (has_e) e_int[atom] = e, e_row[row] = e;
-    if (has_v) v_int[atom] = v, v_row[row] = v;
-  }
-  if (!has_e) return;
-  const float nv = nrm[atom];
-  const float s2 = nv > 0.f ? 2.f / nv : 0.f;
-  const float* d = D + (size_t)row * ND;
-  const float* y = Y + (size_t)row * ND;
-  float* g = G + (size_t)row * ND;
-  for (int k = lane; k < ND; k += 64) g[k] = s2 * (y[k] - e * d[k]);
 }
 
 // Variance of the mixed rows in the split forms, in FP64: V_i = |L_s^T d_i|^2 with the FP64
@@ -377,49 +429,46 @@ void var544_f64(flare_state* s, const float* D, int rows, int split_row, const i
 }  // namespace
 
 // Quadratic forms of the mixed-environment rows [r0, r0 + nr) (544-wide, one chunk of the
-// workspace: Dx row r - r0), split over four column tiles. In the split forms the variance
-// runs in FP64 (var544_f64) and the tiles cover beta only.
-void forms_mixed_chunk(flare_state* s, int r0, int nr, bool want_e, bool want_v) {
+// workspace: Dx row r - r0). In the split forms the variance runs in FP64 (var544_f64) and
+// the products cover beta only. With finish, e and V leave here; otherwise the adjoint kernel
+// of the same chunk writes them.
+void forms_mixed_chunk(flare_state* s, int r0, int nr, bool want_e, bool want_v, bool finish) {
   if ((!want_e && !want_v) || nr == 0) return;
   StageTimer tm(s, FLARE_T_QFORMX);
   const flare_model* m = s->model;
   const int* aor = s->atom_of_rowx + r0;
   float* e_row = s->e_row + s->rows1 + r0;
   float* v_row = s->v_row + s->rows1 + r0;
+  const int split = s->bucket_row0[5] - r0;
   if (want_v && m->var64) {
-    var544_f64(s, s->Dx, nr, s->bucket_row0[5] - r0, aor, 0, s->v_int, v_row);
+    var544_f64(s, s->Dx, nr, split, aor, 0, s->v_int, v_row);
     want_v = false;
     if (!want_e) return;
   }
-  const int mode = (want_e ? 1 : 0) | (want_v ? 2 : 0);
-  QArgs q{};
-  q.mode = mode;
-  q.nbk = 2;
-  for (int k = 0; k < 2; ++k) {
-    const int bk = 4 + k;
-    const int padded = (s->bucket_count[bk] + TILE_ROWS - 1) / TILE_ROWS * TILE_ROWS;
-    q.row0[k] = s->bucket_row0[bk] - r0;     // chunk-local rows
-    q.row1[k] = s->bucket_row0[bk] + padded - r0;
-    q.W[k] = m->Wx[k] + ((mode & 1) ? 0 : (size_t)ND * ND);
-  }
-  // with Cholesky factors the Sigma columns come from L (V = |d L|^2)
-  q.sumsq = m->vchol ? 1 : 0;
-  for (int k = 0; k < 2; ++k) q.L[k] = m->Lx[k];
+  XArgs q{};
+  q.D6 = s->D6x;
   q.D = s->Dx;
   q.aor = aor;
+  q.rows = nr;
+  q.split_row = split;
+  q.mode = (want_e ? 1 : 0) | (want_v ? 2 : 0);
+  q.tri = m->vchol ? 1 : 0;
+  for (int k = 0; k < 2; ++k) {
+    q.W[k] = reinterpret_cast<const uint4*>(m->Wx6[k]);
+    q.V[k] = reinterpret_cast<const uint4*>(m->Vx6[k]);
+  }
   q.Y = s->Yx;
   q.P = s->Px;
-  const int parts = ((mode & 1) ? 1 : 0) + ((mode & 2) ? 1 : 0);
-  const int ntiles = 2 * parts;   // 272 columns per tile
-  k_qform<ND, 17, 1><<<dim3(nr / 64, ntiles), NTQ, 0, s->stream>>>(q);
-  k_qform_finish<<<(nr + 3) / 4, 256, 0, s->stream>>>(nr, mode, ntiles, s->Dx, s->Yx, s->Px, aor, 0, s->nrm, s->Gx,
-                                                      s->e_int, s->v_int, e_row, v_row);
+  launch_forms544(q, s->stream);
+  if (finish)
+    k_forms544_finish<<<(nr + 15) / 16, 256, 0, s->stream>>>(nr, q.mode, s->Dx, s->Yx, s->Px, aor, 0, s->e_int,
+                                                             s->v_int, e_row, v_row);
 }
 
 // Quadratic forms of given 544-wide vectors (rows 0 .. n-1) with the model of mixed bucket
 // `bucket` (4: H centre, 5: Pt centre): e_r = d_r^T beta_s d_r, v_r = d_r^T Sigma_s d_r, by
 // the same kernels as the descriptor path. The vectors are copied into the state's padded
-// row buffer Dx (zeros past n); scratch: Yx, Px, Px64, Gx, e_row, v_row, nrm.
+// row buffer Dx (zeros past n); scratch: D6x, Yx, Px, Px64, e_row, v_row.
 int forms_given_544(flare_state* s, int bucket, int n, const float* d, float* e, float* v) {
   const flare_model* m = s->model;
   for (int c0 = 0; c0 < n; c0 += s->mix_cap) {
@@ -430,30 +479,31 @@ int forms_given_544(flare_state* s, int bucket, int n, const float* d, float* e,
     if (err == hipSuccess && rows > nc)
       err = hipMemsetAsync(s->Dx + (size_t)nc * ND, 0, (size_t)(rows - nc) * ND * sizeof(float), s->stream);
     if (err != hipSuccess) return (int)err;
+    k_split544<<<(rows * (ND / 4) + NTQ - 1) / NTQ, NTQ, 0, s->stream>>>(rows, s->Dx, s->D6x);
     // every row of the chunk has the model of `bucket`: the Pt-centre factor from row 0 for
     // bucket 5, the H-centre one throughout for bucket 4
     const int split = bucket == 5 ? 0 : rows;
-    QArgs q{};
-    q.nbk = 1;
-    q.row0[0] = 0;
-    q.row1[0] = rows;
-    q.W[0] = m->Wx[bucket - 4];
-    q.L[0] = m->Lx[bucket - 4];
-    q.sumsq = m->vchol ? 1 : 0;
+    XArgs q{};
+    q.D6 = s->D6x;
     q.D = s->Dx;
-    q.aor = nullptr;
+    q.n_given = nc;
+    q.rows = rows;
+    q.split_row = split;
+    q.mode = 3;
+    q.tri = m->vchol ? 1 : 0;
+    for (int k = 0; k < 2; ++k) {
+      q.W[k] = reinterpret_cast<const uint4*>(m->Wx6[k]);
+      q.V[k] = reinterpret_cast<const uint4*>(m->Vx6[k]);
+    }
     q.Y = s->Yx;
     q.P = s->Px;
-    int mode = 3;
     if (m->var64) {
       var544_f64(s, s->Dx, rows, split, nullptr, nc, v + c0, s->v_row);
-      mode = 1;
+      q.mode = 1;
     }
-    q.mode = mode;
-    const int ntiles = 2 * (mode == 3 ? 2 : 1);
-    k_qform<ND, 17, 1><<<dim3(rows / 64, ntiles), NTQ, 0, s->stream>>>(q);
-    k_qform_finish<<<(rows + 3) / 4, 256, 0, s->stream>>>(rows, mode, ntiles, s->Dx, s->Yx, s->Px, nullptr, nc,
-                                                          s->nrm, s->Gx, e + c0, v + c0, s->e_row, s->v_row);
+    launch_forms544(q, s->stream);
+    k_forms544_finish<<<(rows + 15) / 16, 256, 0, s->stream>>>(rows, q.mode, s->Dx, s->Yx, s->Px, nullptr, nc, e + c0,
+                                                               v + c0, s->e_row, s->v_row);
   }
   return 0;
 }

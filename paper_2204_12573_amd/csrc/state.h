@@ -78,14 +78,15 @@ struct flare_model {
   int precision = FLARE_FP32;     // arithmetic form of the energy pass (FLARE_FP32 .. FLARE_BF16X6_SPLIT)
   int flags = 0;                  // the precision argument as given (form | FLARE_VAR_FP32)
   bool var64 = false;             // variance on the FP64 matrix cores (split forms without FLARE_VAR_FP32)
-  // variances from Cholesky factors (V6 and Lx hold L)
+  // variances from Cholesky factors (V6 and Vx6 hold L)
   bool vchol = false;
   double r_cut = 0.0;
-  // Mixed buckets (4: H centre, 5: Pt centre): beta then Sigma of the central species over
-  // all 544 components, [2][544][544] with row n = column n of the matrix (see qform.hip);
-  // with Cholesky factors, Lx holds L in the same form.
-  float* Wx[2] = {};
-  float* Lx[2] = {};
+  // Mixed buckets (4: H centre, 5: Pt centre), over all 544 components: beta of the central
+  // species and (Vx6, unless the variance runs in FP64) its Cholesky factor L of Sigma, or
+  // Sigma without factors, as [K step 17][column block 34][part 3][lane 64] x 8 bf16, parts
+  // x0 + x1 + x2 = FP32 value (see qform.hip).
+  uint16_t* Wx6[2] = {};
+  uint16_t* Vx6[2] = {};
   // BF16 split form (precision FLARE_BF16_SPLIT), single-species buckets: beta as
   // [K step 5][column block 9][hi/lo 2][lane 64] x 8 bf16 (K padded 144 -> 160).
   uint16_t* Wb[4] = {};
@@ -125,7 +126,7 @@ struct flare_state {
   long long v_gen = -1;      // positions the variances were computed for
   long long g_gen = -1;      // positions the energy gradients were computed for
   long long w_gen = -1;      // positions the per-pair adjoint terms were computed for
-  long long gx_gen = -1;     // positions the mixed rows' gradients in the workspace are for
+  long long gx_gen = -1;     // positions the mixed rows' D and Y in the workspace are for
                              // (only when all mixed rows fit one chunk)
   long long fixed_bytes = 0; // device bytes of the fixed-size arrays
   int n_atoms = 0;
@@ -209,9 +210,9 @@ struct flare_state {
   float* G1 = nullptr;                  // [row_cap / 128][144][128] gradients (energies without forces)
   // mixed rows, one chunk of mix_cap rows at a time
   float* Dx = nullptr;                  // [mix_cap][544] descriptors
-  float* Gx = nullptr;                  // gradients
   float* Yx = nullptr;                  // D beta
-  float* Px = nullptr;                  // [mix_cap][4] partial row sums of the column tiles
+  float* Px = nullptr;                  // [mix_cap][17] variance partials of the column pairs
+  uint4* D6x = nullptr;                 // the descriptors in three BF16 parts, fragment order (bf16x3.h)
   double* Px64 = nullptr;               // [mix_cap][9] FP64 variance partials (split forms)
 
   // ---- sliced pair layout (capacity slot_cap) ----
@@ -283,11 +284,11 @@ void pair_geometry(flare_state* s);
 constexpr int FORMS_DESCRIPTORS = 8;
 void fused_quadratic_forms(flare_state* s, int mode, float* d_out);
 // mixed rows [r0, r0 + nr) of the 544-wide class (nr <= mix_cap, r0 a multiple of mix_cap),
-// in the chunk workspace Dx/Yx/Gx/Px: descriptors (and their export to caller order),
+// in the chunk workspace Dx/D6x/Yx/Px: descriptors (and their export to caller order),
 // quadratic forms, adjoint terms
 void desc_mixed_chunk(flare_state* s, int r0, int nr, float* d_out);
-void forms_mixed_chunk(flare_state* s, int r0, int nr, bool want_e, bool want_v);
-void adjoint_mixed_chunk(flare_state* s, int r0, int nr);
+void forms_mixed_chunk(flare_state* s, int r0, int nr, bool want_e, bool want_v, bool finish);
+void adjoint_mixed_chunk(flare_state* s, int r0, int nr, bool want_v);
 // |d~| of every atom in caller order
 void export_norms(flare_state* s, float* norm_out);
 // quadratic forms of given vectors with the model of one bucket (fused.hip, qform.hip)
