@@ -190,14 +190,13 @@ template <class F>
 static void state_arrays(flare_state* s, F&& f) {
   const size_t n = (size_t)s->max_atoms, P = (size_t)s->max_pairs, R = (size_t)s->row_cap;
   const size_t SL = (size_t)s->slice_cap, SC = (size_t)s->slot_cap, BC = (size_t)s->bin_cap;
-  const size_t NC = (size_t)s->cell_cap, TC = (size_t)s->task_cap, X = (size_t)s->mix_cap;
+  const size_t TC = (size_t)s->task_cap, X = (size_t)s->mix_cap;
   const size_t keys = (size_t)list_key_count() * s->nblk_cap + 1;
-  const size_t scan_n = std::max({BC + 1, n + 1, keys, SL + 1});
+  const size_t scan_n = std::max({BC + 1, n + 1 + keys, SL + 1});
   f((void**)&s->perm, n * 4);
   f((void**)&s->sp, n * 4);
   f((void**)&s->sid, n * 4);
   f((void**)&s->bin, n * 4);
-  f((void**)&s->envmask, n * 4);
   f((void**)&s->bucket, n * 4);
   f((void**)&s->row_of, n * 4);
   f((void**)&s->nl_cnt, n * 4);
@@ -219,16 +218,13 @@ static void state_arrays(flare_state* s, F&& f) {
   f((void**)&s->nl_j, P * 4);
   f((void**)&s->nl_s, P * 4);
   f((void**)&s->nl_rev, P * 4);
-  f((void**)&s->d_grids, NC * sizeof(CellGrid));
-  f((void**)&s->d_struct_off, (NC + 1) * 4);
+  f((void**)&s->d_stage, s->h_stage_bytes);
   f((void**)&s->bin_count, (BC + 1) * 4);
   f((void**)&s->bin_start, (BC + 1) * 4);
   f((void**)&s->bin_fill, (BC + 1) * 4);
   f((void**)&s->blk_bucket, keys * 4);
   f((void**)&s->blk_bucket_scan, (keys + 1) * 4);
   f((void**)&s->scan_scratch, scan_scratch_ints((long long)scan_n) * 4);
-  f((void**)&s->d_tasks, TC * sizeof(RedTask));
-  f((void**)&s->d_first_task, (NC + 1) * 4);
   f((void**)&s->red_e, TC * 2 * 8);
   f((void**)&s->red_s, TC * 4);
   f((void**)&s->atom_of_row1, (R + 1) * 4);
@@ -253,8 +249,7 @@ static void state_arrays(flare_state* s, F&& f) {
   f((void**)&s->slot_d0, SC * 16);
   f((void**)&s->geom, SC * 16);
   f((void**)&s->w_in, SC * 16);
-  f((void**)&s->d_status, 64);
-  f((void**)&s->d_layout, (size_t)list_layout_words() * 4 + 64);
+  f((void**)&s->d_status, 64 + (size_t)list_layout_words() * 4 + 64);
 }
 
 extern "C" {
@@ -495,13 +490,13 @@ int flare_state_create(flare_state** out, const flare_model* model, int max_atom
   s->task_cap = s->cell_cap + max_atoms / 2048 + 1;
   s->nblk_cap = (max_atoms + 255) / 256;
   s->mix_cap = std::min(s->row_cap, MIX_ROWS);
+  s->h_stage_bytes = (size_t)s->cell_cap * sizeof(CellGrid) + 2 * ((size_t)s->cell_cap + 1) * sizeof(int) +
+                     (size_t)s->task_cap * sizeof(RedTask) + 64;
   hipError_t e = hipGetDevice(&s->device);
   state_arrays(s, [&](void** p, size_t bytes) {
     if (e == hipSuccess) e = hipMalloc(p, bytes ? bytes : 4);
     if (e == hipSuccess) s->fixed_bytes += (long long)(bytes ? bytes : 4);
   });
-  s->h_stage_bytes = (size_t)s->cell_cap * sizeof(CellGrid) + 2 * ((size_t)s->cell_cap + 1) * sizeof(int) +
-                     (size_t)s->task_cap * sizeof(RedTask) + 64;
   if (e == hipSuccess) e = hipHostMalloc((void**)&s->h_info, 256, hipHostMallocDefault);
   if (e == hipSuccess) e = hipHostMalloc((void**)&s->h_stage, s->h_stage_bytes, hipHostMallocDefault);
   if (e == hipSuccess) e = hipMemsetAsync(s->d_status, 0, 64, s->stream);

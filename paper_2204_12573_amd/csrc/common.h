@@ -112,8 +112,11 @@ __device__ __forceinline__ double sum16d(double v) {
 
 // ---- device-wide exclusive scan (scan.hip) ----
 size_t scan_scratch_ints(long long n);
-// out[0..n] = exclusive prefix of in[0..n-1], out[n] = total. in and out may alias only
-// if distinct buffers are not required (they may not alias).
+// out[0..n] = exclusive prefix of in[0..n-1], out[n] = total. in and out may not alias.
 void scan_exclusive(const int* in, int* out, int n, int* scratch, hipStream_t st);
+// Two scans in the same launches (scratch for the sum of both lengths); the first one raises
+// flag in *status when its total passes 2^31 - 1.
+void scan_exclusive2(const int* in0, int* out0, int n0, const int* in1, int* out1, int n1, int* scratch, int* status,
+                     int flag, hipStream_t st);
 
 }  // namespace flare

@@ -37,12 +37,12 @@ enum {
   LY_SLICES = 15,    // 32-row slices of both classes
   LY_SLOTS32 = 16,   // groups of 32 slots (the slice_base total)
   LY_FLAGS = 17,     // 1: more pairs than the capacity, 2: more slots than the capacity
-  LY_BUILD = 18,     // the build's own status word (input and consistency checks)
-  LY_STATUS = 19,    // the caller-visible status word raised since it was last read
-  LY_N = 20
+  LY_STATUS = 18,    // the caller-visible status word raised since it was last read
+  LY_N = 19
 };
 constexpr int BUILD_ASYMMETRIC = 256;   // a pair without its reverse (internal error)
-constexpr int BUILD_OVERFLOW = 512;     // the int32 prefix of the pair counts overflowed
+constexpr int BUILD_OVERFLOW = 512;     // more pairs than an int32 prefix holds
+constexpr int BUILD_DENSE = 1024;       // some atom has more pairs than PAIR_CACHE
 
 __device__ inline int floor_div(int u, int n) { return u >= 0 ? u / n : -((-u + n - 1) / n); }
 
@@ -113,26 +113,12 @@ __global__ __launch_bounds__(NT) void k_bin_scatter(int n, const CallerRec* __re
   sorted[start[b] + atomicAdd(&fill[b], 1)] = a;
 }
 
-// Inside each bin, order atoms by caller index (the scatter order is racy).
-__global__ __launch_bounds__(NT) void k_bin_sort(int nbins, const int* __restrict__ start,
-                                                 int* __restrict__ sorted) {
-  const int b = blockIdx.x * NT + threadIdx.x;
-  if (b >= nbins) return;
-  const int lo = start[b], hi = start[b + 1];
-  for (int k = lo + 1; k < hi; ++k) {
-    int v = sorted[k];
-    int m = k - 1;
-    while (m >= lo && sorted[m] > v) {
-      sorted[m + 1] = sorted[m];
-      --m;
-    }
-    sorted[m + 1] = v;
-  }
-}
-
-// Internal order: one caller record (a 64-byte line) per atom, gathered in bin order; the
-// species rides in w.w, so that a neighbour's position and species are one load.
+// Internal order: bins in order, inside a bin by caller index (the scatter order is racy: an
+// atom's place is the number of smaller indices among its bin's atoms). One caller record (a
+// 64-byte line) per atom; the species rides in w.w, so that a neighbour's position and
+// species are one load.
 __global__ __launch_bounds__(NT) void k_to_internal(int n, const int* __restrict__ sorted,
+                                                    const int* __restrict__ start,
                                                     const CallerRec* __restrict__ rec,
                                                     const int32_t* __restrict__ species,
                                                     int* __restrict__ perm, int* __restrict__ inv_perm,
@@ -140,15 +126,18 @@ __global__ __launch_bounds__(NT) void k_to_internal(int n, const int* __restrict
                                                     int* __restrict__ sid, int* __restrict__ bin,
                                                     double4* __restrict__ w, float4* __restrict__ wf,
                                                     double* __restrict__ off) {
-  const int i = blockIdx.x * NT + threadIdx.x;
-  if (i >= n) return;
-  const int a = sorted[i];
+  const int t = blockIdx.x * NT + threadIdx.x;
+  if (t >= n) return;
+  const int a = sorted[t];
+  const CallerRec r = rec[a];
+  const int lo = start[r.bin], hi = start[r.bin + 1];
+  int i = lo;
+  for (int k = lo; k < hi; ++k) i += sorted[k] < a ? 1 : 0;
   perm[i] = a;
   inv_perm[a] = i;
   const int s = species[a];
   const int sc = (s < 0 || s >= NS) ? 0 : s;
   sp[i] = sc;
-  const CallerRec r = rec[a];
   sid[i] = r.cell;
   bin[i] = r.bin;
   w[i] = make_double4(r.wx, r.wy, r.wz, (double)sc);
@@ -169,51 +158,318 @@ constexpr int NCK = 64;
 constexpr int NKEY = NBUCKET * NCK;
 __device__ inline int row_key(int b, int c) { return b * NCK + (NCK - 1 - min(c, NCK - 1)); }
 
-// Per-block counts of each sort key, blk[key * nblk + block] (key < 0: no row).
-__device__ inline void block_key_counts(int key, int* __restrict__ blk, int nblk) {
-  __shared__ int cnt[NKEY];
-  for (int k = threadIdx.x; k < NKEY; k += NT) cnt[k] = 0;
-  __syncthreads();
-  if (key >= 0) atomicAdd(&cnt[key], 1);
-  __syncthreads();
-  for (int k = threadIdx.x; k < NKEY; k += NT) blk[(size_t)k * nblk + blockIdx.x] = cnt[k];
+// The pair search, 16 lanes an atom. The stencil bins of one (z, y) row and one x image are
+// neighbours in the bin order, so their atoms are one contiguous range: a segment. The lanes
+// take 16 segments at a time (nine cover a stencil of one bin each way away from the box
+// edges), add up their lengths, and then walk the candidates of all of them together, 16 at a
+// time; the accepted ones keep the order (z, y, x, bin, place) through a ballot. emit(k, j,
+// shift) receives pair k of the atom. The FP32 copies decide every candidate whose FP32
+// distance is outside [lo2, hi2) (the band holds the FP32 error, so the decision is the FP64
+// one), the FP64 test the rest. Returns the pair count and the species seen.
+// (One thread an atom, walking 27 bins through dependent loads, took 58 us for 80 atoms and
+// 244 us for 1.0 M.)
+constexpr int SA = NT / 16;                  // atoms per work-group at 16 lanes an atom
+
+struct PairSearch {
+  const CellGrid* grids;
+  const int* sid;
+  const int* bin;
+  const double4* w;
+  const float4* wf;
+  const int* bstart;
+  double rl2;
+  float lo2, hi2;
+};
+
+template <int SL, class Emit>
+__device__ __forceinline__ void search_atom(const PairSearch& q, int i, int& cnt_out, int& mask_out, Emit emit) {
+#pragma clang fp contract(off)
+  const int l = threadIdx.x & (SL - 1);
+  const int sub0 = (threadIdx.x & 63) & ~(SL - 1);       // first lane of the group in its wave
+  const CellGrid* g = q.grids + q.sid[i];
+  const int nbx = g->nb[0], nby = g->nb[1], nbz = g->nb[2];
+  const int local = q.bin[i] - g->bin_base;
+  const int bx = local % nbx;
+  const int by = (local / nbx) % nby;
+  const int bz = local / (nbx * nby);
+  const int kx = g->K[0], ky = g->K[1], kz = g->K[2], base = g->bin_base;
+  const double Lx = g->L[0], Ly = g->L[1], Lz = g->L[2];
+  const float lx = (float)Lx, ly = (float)Ly, lz = (float)Lz;
+  const float4 wi = q.wf[i];
+  const int sx0 = floor_div(bx - kx, nbx);               // images of the x row: sx0 .. sx0 + nsx - 1
+  const int nsx = floor_div(bx + kx, nbx) - sx0 + 1;
+  const int rows_y = 2 * ky + 1;
+  const int nseg = (2 * kz + 1) * rows_y * nsx;
+  int cnt = 0, mask = 0;
+  for (int e0 = 0; e0 < nseg; e0 += SL) {
+    // this lane's segment: first atom, length, image
+    const int e = e0 + l;
+    int j0 = 0, len = 0, shift = 0;
+    if (e < nseg) {
+      const int row = e / nsx, sx = sx0 + (e - row * nsx);
+      const int rz = row / rows_y;
+      const int uz = bz + rz - kz, uy = by + (row - rz * rows_y) - ky;
+      const int sz = floor_div(uz, nbz), sy = floor_div(uy, nby);
+      const int b0 = base + ((uz - sz * nbz) * nby + (uy - sy * nby)) * nbx;
+      j0 = q.bstart[b0 + max(bx - kx - sx * nbx, 0)];
+      len = q.bstart[b0 + min(bx + kx - sx * nbx, nbx - 1) + 1] - j0;
+      shift = pack_shift(sx, sy, sz);
+    }
+    int incl = len;
+#pragma unroll
+    for (int d = 1; d < SL; d <<= 1) {
+      const int t = __shfl_up(incl, d, SL);
+      if (l >= d) incl += t;
+    }
+    const int excl = incl - len;
+    const int total = __shfl(incl, SL - 1, SL);
+    for (int c0 = 0; c0 < total; c0 += SL) {
+      const int c = c0 + l;
+      // the candidate's segment: the last one that starts at or before it
+      int k = 0;
+#pragma unroll
+      for (int d = SL / 2; d > 0; d >>= 1)
+        if (__shfl(excl, k + d, SL) <= c) k += d;
+      const int j = __shfl(j0, k, SL) + (c - __shfl(excl, k, SL));
+      const int sh = __shfl(shift, k, SL);
+      bool in = false;
+      int sp = 0;
+      if (c < total) {
+        int sx, sy, sz;
+        unpack_shift(sh, sx, sy, sz);
+        const float4 wj = q.wf[j];
+        const float fx = (wj.x - wi.x) + (float)sx * lx;
+        const float fy = (wj.y - wi.y) + (float)sy * ly;
+        const float fz = (wj.z - wi.z) + (float)sz * lz;
+        const float r2f = fx * fx + fy * fy + fz * fz;
+        in = r2f < q.lo2;
+        if (!in && r2f < q.hi2) {
+          const double4 wd = q.w[j], wi64 = q.w[i];
+          const double dx = (wd.x - wi64.x) + (double)sx * Lx;
+          const double dy = (wd.y - wi64.y) + (double)sy * Ly;
+          const double dz = (wd.z - wi64.z) + (double)sz * Lz;
+          in = dx * dx + dy * dy + dz * dz < q.rl2;
+        }
+        in = in && !(sh == 0 && j == i);
+        sp = wj.w != 0.f ? 1 : 0;
+      }
+      const unsigned hits = (unsigned)(__ballot(in) >> sub0) & ((1u << SL) - 1u);
+      const unsigned pt = (unsigned)(__ballot(in && sp == 1) >> sub0) & ((1u << SL) - 1u);
+      if (in) emit(cnt + __popc(hits & ((1u << l) - 1u)), j, sh);
+      mask |= (pt ? 2 : 0) | (hits != pt ? 1 : 0);
+      cnt += __popc(hits);
+    }
+  }
+  cnt_out = cnt;
+  mask_out = mask;
 }
 
-// The counting pass (FILL = false) also keeps the first PAIR_CACHE pairs of every atom in
-// cache[c * n + i] (j, packed shift); the filling pass copies them for atoms whose count
-// fits and repeats the search only for the others (32 covers every atom of the 1 M-atom
-// H2/Pt(111) cell at r_list 4.7 A, whose largest count is 28). The filling pass also marks
-// every pair's reverse as not found yet (-1), and does nothing when the pairs exceed the
-// capacity (layout flag).
+// The search keeps the first PAIR_CACHE pairs of atom i at cache[PAIR_CACHE i ...] (j, packed
+// shift), so that the pass that writes the list copies them and repeats the search only for
+// atoms with more (32 covers every atom of the 1 M-atom H2/Pt(111) cell at r_list 4.7 A, whose
+// largest count is 28). Also the atom's environment bucket and the counts of the sort keys in
+// its 256-atom block, blk[key * nblk + block].
 constexpr int PAIR_CACHE = 32;
+// Up to FEW_ATOMS the search and the list run in the forms for few atoms. Search in us, 16
+// lanes against one thread an atom: 64 : 72 for a 64 k-atom slab, 97 : 81 for 120 k, 64 : 90
+// for 60 k atoms under a gas column, 108 : 95 for 200 k; list with 16 against 64 atoms a
+// work-group: 29 : 33 and 51 : 59 for the slabs, 161 : 144 for 800 k atoms under a gas column.
+constexpr int FEW_ATOMS = 81920;
+constexpr int MANY_AW = 64;
 
-template <bool FILL>
-__global__ __launch_bounds__(NT) void k_pairs(int n, const CellGrid* __restrict__ grids,
-                                              const int* __restrict__ sid,
-                                              const int* __restrict__ bin,
-                                              const double4* __restrict__ w,
-                                              const float4* __restrict__ wf,
-                                              const int* __restrict__ bstart, double rl2, float lo2,
-                                              float hi2,
-                                              int* __restrict__ cnt_out,
-                                              int* __restrict__ envmask,
-                                              int* __restrict__ bucket, int* __restrict__ blk,
-                                              int nblk, const int* __restrict__ nl_off,
-                                              int* __restrict__ nl_j, int32_t* __restrict__ nl_s,
-                                              int* __restrict__ nl_rev, int2* __restrict__ cache,
-                                              const int* __restrict__ layout) {
+// Up to FEW_ATOMS 16 lanes an atom (blk cleared at the build's start).
+template <int SL>
+__global__ __launch_bounds__(NT) void k_search(int n, PairSearch q, int* __restrict__ cnt_out,
+                                               int* __restrict__ bucket, int* __restrict__ blk, int nblk,
+                                               int2* __restrict__ cache, int* __restrict__ build_status) {
+  const int i = blockIdx.x * (NT / SL) + threadIdx.x / SL;
+  if (i >= n) return;
+  int cnt, mask;
+  int2* mine = cache + (size_t)i * PAIR_CACHE;
+  search_atom<SL>(q, i, cnt, mask, [&](int k, int j, int shift) {
+    if (k < PAIR_CACHE) mine[k] = make_int2(j, shift);
+  });
+  if ((threadIdx.x & (SL - 1)) == 0) {
+    cnt_out[i] = cnt;
+    if (cnt > PAIR_CACHE) atomicOr(build_status, BUILD_DENSE);
+    const int b = bucket_of((int)q.w[i].w, mask);
+    bucket[i] = b;
+    if (b >= 0) atomicAdd(&blk[(size_t)row_key(b, cnt) * nblk + (i >> 8)], 1);
+  }
+}
+
+// More atoms: one thread an atom, the same segments in the same order, four candidates at a
+// time. It spends a tenth of the instructions per candidate (the 16 lanes share few candidates
+// in a gas) but waits for one load after the other, so it needs the chip full of atoms.
+__global__ __launch_bounds__(NT) void k_search_many(int n, PairSearch q, int* __restrict__ cnt_out,
+                                                    int* __restrict__ bucket, int* __restrict__ blk, int nblk,
+                                                    int2* __restrict__ cache, int* __restrict__ build_status) {
 #pragma clang fp contract(off)
+  __shared__ int key_count[NKEY];
+  for (int k = threadIdx.x; k < NKEY; k += NT) key_count[k] = 0;
+  __syncthreads();
   const int i = blockIdx.x * NT + threadIdx.x;
-  int key_out = -1;
-  if (FILL) {
-    if (layout[LY_FLAGS]) return;
-    // The work-group's atoms own one contiguous range of the list. Copy the cached pairs
-    // in list order (thread t takes positions t, t + NT, ...; the atom by bisection in the
-    // offsets, in LDS), so that the writes are coalesced; an atom with more pairs than the
-    // cache holds is searched again by its own thread below.
-    __shared__ int offs[NT + 1];
-    const int a0 = blockIdx.x * NT;
-    const int na = min(NT, n - a0);
+  if (i < n) {
+    const CellGrid g = q.grids[q.sid[i]];
+    const int local = q.bin[i] - g.bin_base;
+    const int bx = local % g.nb[0];
+    const int by = (local / g.nb[0]) % g.nb[1];
+    const int bz = local / (g.nb[0] * g.nb[1]);
+    const float4 wi = q.wf[i];
+    const float lx = (float)g.L[0], ly = (float)g.L[1], lz = (float)g.L[2];
+    int2* mine = cache + (size_t)i * PAIR_CACHE;
+    int cnt = 0, mask = 0;
+    // four positions from j4 on, past the segment's end its last atom again (unused)
+    auto load = [&](int j4, int j1, float4 (&wq)[4]) {
+      const int last = max(j1 - 1, 0);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) wq[u] = q.wf[min(j4 + u, last)];
+    };
+    auto test = [&](const float4 (&wq)[4], int j4, int j1, int sx, int sy, int sz) {
+      const float tx = (float)sx * lx, ty = (float)sy * ly, tz = (float)sz * lz;
+      const int shift = pack_shift(sx, sy, sz);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int j = j4 + u;
+        const float fx = (wq[u].x - wi.x) + tx;
+        const float fy = (wq[u].y - wi.y) + ty;
+        const float fz = (wq[u].z - wi.z) + tz;
+        const float r2f = fx * fx + fy * fy + fz * fz;
+        if (j >= j1 || !(r2f < q.hi2) || (shift == 0 && j == i)) continue;
+        if (!(r2f < q.lo2)) {
+          const double4 wd = q.w[j], wi64 = q.w[i];
+          const double dx = (wd.x - wi64.x) + (double)sx * g.L[0];
+          const double dy = (wd.y - wi64.y) + (double)sy * g.L[1];
+          const double dz = (wd.z - wi64.z) + (double)sz * g.L[2];
+          if (!(dx * dx + dy * dy + dz * dz < q.rl2)) continue;
+        }
+        if (cnt < PAIR_CACHE) mine[cnt] = make_int2(j, shift);
+        mask |= 1 << (int)wq[u].w;
+        ++cnt;
+      }
+    };
+    const int sx0 = floor_div(bx - g.K[0], g.nb[0]), sx1 = floor_div(bx + g.K[0], g.nb[0]);
+    if (sx0 == sx1 && g.K[1] == 1 && g.K[2] == 1) {
+      // nine segments: their ends loaded together
+      int j0[9], j1[9], sy[3], sz[3];
+#pragma unroll
+      for (int rz = 0; rz < 3; ++rz) {
+        sz[rz] = floor_div(bz + rz - 1, g.nb[2]);
+#pragma unroll
+        for (int ry = 0; ry < 3; ++ry) {
+          sy[ry] = floor_div(by + ry - 1, g.nb[1]);
+          const int b0 = g.bin_base + ((bz + rz - 1 - sz[rz] * g.nb[2]) * g.nb[1] + (by + ry - 1 - sy[ry] * g.nb[1])) * g.nb[0] +
+                         bx - sx0 * g.nb[0];
+          j0[3 * rz + ry] = q.bstart[b0 - g.K[0]];
+          j1[3 * rz + ry] = q.bstart[b0 + g.K[0] + 1];
+        }
+      }
+      // the next four candidates, of this segment or the next one, are on their way while
+      // four are tested
+      float4 cur[4];
+      load(j0[0], j1[0], cur);
+#pragma unroll
+      for (int r = 0; r < 9; ++r) {
+        const int rn = r < 8 ? r + 1 : 8;
+        bool more;
+        int j4 = j0[r];
+        do {
+          more = j4 + 4 < j1[r];
+          float4 nxt[4];
+          load(more ? j4 + 4 : j0[rn], more ? j1[r] : j1[rn], nxt);
+          test(cur, j4, j1[r], sx0, sy[r % 3], sz[r / 3]);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) cur[u] = nxt[u];
+          j4 += 4;
+        } while (more);
+      }
+    } else {
+      for (int oz = -g.K[2]; oz <= g.K[2]; ++oz) {
+        const int sz = floor_div(bz + oz, g.nb[2]);
+        for (int oy = -g.K[1]; oy <= g.K[1]; ++oy) {
+          const int sy = floor_div(by + oy, g.nb[1]);
+          const int b0 = g.bin_base + ((bz + oz - sz * g.nb[2]) * g.nb[1] + (by + oy - sy * g.nb[1])) * g.nb[0];
+          for (int sx = sx0; sx <= sx1; ++sx) {
+            const int ja = q.bstart[b0 + max(bx - g.K[0] - sx * g.nb[0], 0)];
+            const int jb = q.bstart[b0 + min(bx + g.K[0] - sx * g.nb[0], g.nb[0] - 1) + 1];
+            for (int j4 = ja; j4 < jb; j4 += 4) {
+              float4 wq[4];
+              load(j4, jb, wq);
+              test(wq, j4, jb, sx, sy, sz);
+            }
+          }
+        }
+      }
+    }
+    cnt_out[i] = cnt;
+    if (cnt > PAIR_CACHE) atomicOr(build_status, BUILD_DENSE);
+    const int b = bucket_of((int)wi.w, mask);
+    bucket[i] = b;
+    if (b >= 0) atomicAdd(&key_count[row_key(b, cnt)], 1);
+  }
+  __syncthreads();
+  for (int k = threadIdx.x; k < NKEY; k += NT) blk[(size_t)k * nblk + blockIdx.x] = key_count[k];
+}
+
+// Atoms per bucket and the rows of every bucket padded to the 128-row tile (144-wide buckets
+// first, then the mixed ones), from the scanned key counts: every work-group that needs them
+// adds them up itself (a dozen loads).
+struct RowLayout {
+  int count[NBUCKET], row0[NBUCKET], rows1, rowsx;
+};
+__device__ inline RowLayout row_layout(const int* __restrict__ blk_scan, int nblk) {
+  RowLayout o;
+  int r1 = 0, rx = 0;
+#pragma unroll
+  for (int b = 0; b < NBUCKET; ++b) {
+    const int c = blk_scan[(size_t)(b + 1) * NCK * nblk] - blk_scan[(size_t)b * NCK * nblk];
+    const int padded = (c + TILE_ROWS - 1) / TILE_ROWS * TILE_ROWS;
+    o.count[b] = c;
+    o.row0[b] = b < 4 ? r1 : rx;
+    if (b < 4) r1 += padded;
+    else rx += padded;
+  }
+  o.rows1 = r1;
+  o.rowsx = rx;
+  return o;
+}
+
+__device__ __forceinline__ int32_t negated_shift(int32_t v) {
+  int sx, sy, sz;
+  unpack_shift(v, sx, sy, sz);
+  return pack_shift(-sx, -sy, -sz);
+}
+
+// Two passes over the atoms that both need only the search and the prefix sums, side by side
+// in one launch.
+// Work-groups [0, nlist): the list itself, AW atoms a work-group. One thread a pair p =
+// (i, j, s), in list order (its atom by bisection in the group's offsets, in LDS), copies it
+// from the cache and finds the position of the reverse q = (j, i, -s) inside j's list among
+// j's cached pairs, eight a step. The list is symmetric because the FP64 distance test gives
+// the same value for both orders (negating a rounded difference is exact). An atom with more
+// pairs than the cache is searched again by 16 lanes, and the reverse of a pair that touches
+// one is left at -1 for k_rows. Nothing is written when the pairs exceed the capacity.
+// AW: 16 atoms, about one pair a thread, when there are few (the kernel is one chain of
+// dependent loads); 64 when there are many (fewer groups, offsets shared by more pairs).
+// Work-groups from nlist: rows of each bucket in key order (see row_key), 256 atoms a group;
+// the rank among equal keys follows the internal index (the scanned key counts of the blocks
+// before, then the rank inside the block). The first of them writes the layout record.
+template <int AW>
+__global__ __launch_bounds__(NT) void k_lists(int n, int nlist, PairSearch q, const int* __restrict__ cnt,
+                                              const int* __restrict__ nl_off, const int2* __restrict__ cache,
+                                              long long max_pairs, const int* __restrict__ build_status,
+                                              int* __restrict__ nl_j, int32_t* __restrict__ nl_s,
+                                              int* __restrict__ nl_rev, const int* __restrict__ bucket,
+                                              const int* __restrict__ blk_scan, int nblk, int* __restrict__ row_of,
+                                              int* __restrict__ aor1, int* __restrict__ aorx,
+                                              int* __restrict__ layout) {
+  const int pairs = nl_off[n];
+  const bool over = (*build_status & BUILD_OVERFLOW) || (long long)pairs > max_pairs;
+  if ((int)blockIdx.x < nlist) {
+    if (over) return;
+    __shared__ int offs[AW + 1];
+    const int a0 = blockIdx.x * AW;
+    const int na = min(AW, n - a0);
     for (int k = threadIdx.x; k <= na; k += NT) offs[k] = nl_off[a0 + k];
     __syncthreads();
     for (int p = offs[0] + threadIdx.x; p < offs[na]; p += NT) {
@@ -223,212 +479,55 @@ __global__ __launch_bounds__(NT) void k_pairs(int n, const CellGrid* __restrict_
         if (offs[mid] <= p) lo = mid;
         else hi = mid;
       }
-      nl_rev[p] = -1;
       if (offs[lo + 1] - offs[lo] > PAIR_CACHE) continue;
-      const int2 e = cache[(size_t)(p - offs[lo]) * n + a0 + lo];
-      nl_j[p] = e.x;
-      nl_s[p] = e.y;
-    }
-    if (i >= n || offs[threadIdx.x + 1] - offs[threadIdx.x] <= PAIR_CACHE) return;
-  }
-  if (i < n) {
-    const CellGrid g = grids[sid[i]];
-    const int local = bin[i] - g.bin_base;
-    const int bx = local % g.nb[0];
-    const int by = (local / g.nb[0]) % g.nb[1];
-    const int bz = local / (g.nb[0] * g.nb[1]);
-    const double4 wi = w[i];
-    const double wx = wi.x, wy = wi.y, wz = wi.z;
-    const float4 wif = wf[i];
-    int cnt = 0, mask = 0;
-    long long o = FILL ? nl_off[i] : 0;
-    for (int oz = -g.K[2]; oz <= g.K[2]; ++oz) {
-      const int uz = bz + oz;
-      const int sz = floor_div(uz, g.nb[2]);
-      const int cz = uz - sz * g.nb[2];
-      const double tz = (double)sz * g.L[2];
-      const float tzf = (float)tz;
-      for (int oy = -g.K[1]; oy <= g.K[1]; ++oy) {
-        const int uy = by + oy;
-        const int sy = floor_div(uy, g.nb[1]);
-        const int cy = uy - sy * g.nb[1];
-        const double ty = (double)sy * g.L[1];
-        const float tyf = (float)ty;
-        // the atoms of bin bb (image shift sx along x) in order, four positions per step: the
-        // FP32 copies decide every candidate whose FP32 distance is outside [lo2, hi2) (the
-        // band holds the FP32 error, so the decision is the FP64 one), the FP64 test the rest
-        auto scan_bin = [&](int j0, int j1, int sx) {
-          const double tx = (double)sx * g.L[0];
-          const float txf = (float)tx;
-          const bool zero_shift = (sx == 0) && (sy == 0) && (sz == 0);
-          for (int j4 = j0; j4 < j1; j4 += 4) {
-            float4 wq[4];
+      const int2 e = cache[(size_t)(a0 + lo) * PAIR_CACHE + (p - offs[lo])];
+      const int len = cnt[e.x];
+      const int4* list = reinterpret_cast<const int4*>(cache + (size_t)e.x * PAIR_CACHE);
+      const int32_t want = negated_shift(e.y);
+      int rev = -1;
+      if (len <= PAIR_CACHE)
+        for (int k = 0; k < len && rev < 0; k += 8) {
+          int4 t[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) wq[u] = j4 + u < j1 ? wf[j4 + u] : make_float4(0.f, 0.f, 0.f, 0.f);
+          for (int u = 0; u < 4; ++u) t[u] = list[(k >> 1) + u];   // inside the atom's 32 entries
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              const int j = j4 + u;
-              if (j >= j1) break;
-              const float fx = (wq[u].x - wif.x) + txf;
-              const float fy = (wq[u].y - wif.y) + tyf;
-              const float fz = (wq[u].z - wif.z) + tzf;
-              const float r2f = fx * fx + fy * fy + fz * fz;
-              bool in = r2f < lo2;
-              if (!in && r2f < hi2) {
-                const double4 wd = w[j];
-                const double dx = (wd.x - wx) + tx;
-                const double dy = (wd.y - wy) + ty;
-                const double dz = (wd.z - wz) + tz;
-                in = dx * dx + dy * dy + dz * dz < rl2;
-              }
-              if (in && !(zero_shift && j == i)) {
-                if (FILL) {
-                  nl_j[o + cnt] = j;
-                  nl_s[o + cnt] = pack_shift(sx, sy, sz);
-                  nl_rev[o + cnt] = -1;
-                } else if (cnt < PAIR_CACHE) {
-                  cache[(size_t)cnt * n + i] = make_int2(j, pack_shift(sx, sy, sz));
-                }
-                mask |= 1 << (int)wq[u].w;
-                ++cnt;
-              }
-            }
-          }
-        };
-        const int rb = g.bin_base + (cz * g.nb[1] + cy) * g.nb[0];
-        if (g.K[0] == 1) {
-          // one-bin stencil in x: the row's three bin ranges are loaded together
-          int sxs[3], j0s[3], j1s[3];
-#pragma unroll
-          for (int u = 0; u < 3; ++u) {
-            const int ux = bx + u - 1;
-            sxs[u] = floor_div(ux, g.nb[0]);
-            const int bb = rb + (ux - sxs[u] * g.nb[0]);
-            j0s[u] = bstart[bb];
-            j1s[u] = bstart[bb + 1];
-          }
-#pragma unroll
-          for (int u = 0; u < 3; ++u) scan_bin(j0s[u], j1s[u], sxs[u]);
-        } else {
-          for (int ox = -g.K[0]; ox <= g.K[0]; ++ox) {
-            const int ux = bx + ox;
-            const int sx = floor_div(ux, g.nb[0]);
-            const int bb = rb + (ux - sx * g.nb[0]);
-            scan_bin(bstart[bb], bstart[bb + 1], sx);
+          for (int u = 3; u >= 0; --u) {
+            if (t[u].z == a0 + lo && t[u].w == want && k + 2 * u + 1 < len) rev = k + 2 * u + 1;
+            if (t[u].x == a0 + lo && t[u].y == want && k + 2 * u < len) rev = k + 2 * u;
           }
         }
+      nl_j[p] = e.x;
+      nl_s[p] = e.y;
+      nl_rev[p] = rev;
+    }
+    if (*build_status & BUILD_DENSE)
+      for (int k = threadIdx.x >> 4; k < na; k += SA) {
+        const int p0 = offs[k];
+        if (offs[k + 1] - p0 <= PAIR_CACHE) continue;
+        int c, m;
+        search_atom<16>(q, a0 + k, c, m, [&](int pos, int j, int shift) {
+          nl_j[p0 + pos] = j;
+          nl_s[p0 + pos] = shift;
+          nl_rev[p0 + pos] = -1;
+        });
       }
-    }
-    if (!FILL) {
-      cnt_out[i] = cnt;
-      envmask[i] = mask;
-      const int b = bucket_of((int)wi.w, mask);
-      bucket[i] = b;
-      if (b >= 0) key_out = row_key(b, cnt);
-    }
+    return;
   }
-  if (!FILL) block_key_counts(key_out, blk, nblk);
-}
-
-// The per-atom counts are non-negative and each is below 2^31, so their int32 prefix sum
-// has run past 2^31 - 1 exactly when one of its entries is negative.
-__global__ __launch_bounds__(NT) void k_off_check(int n, const int* __restrict__ nl_off, int* __restrict__ status) {
-  const int i = blockIdx.x * NT + threadIdx.x;
-  if (i <= n && nl_off[i] < 0) atomicOr(status, BUILD_OVERFLOW);
-}
-
-// Sizes after the counting pass: pairs, atoms per bucket, the rows of every bucket padded to
-// the 128-row tile (144-wide buckets first, then the mixed ones), 32-row slices.
-__global__ void k_layout_rows(int n, const int* __restrict__ nl_off, const int* __restrict__ blk_scan, int nblk,
-                              long long max_pairs, const int* __restrict__ build_status, int* __restrict__ layout) {
-  if (threadIdx.x != 0) return;
-  const int pairs = nl_off[n];
-  int flags = 0;
-  if ((*build_status & BUILD_OVERFLOW) || pairs < 0 || (long long)pairs > max_pairs) flags |= 1;
-  int r1 = 0, rx = 0;
-  for (int b = 0; b < NBUCKET; ++b) {
-    const int c = blk_scan[(size_t)(b + 1) * NCK * nblk] - blk_scan[(size_t)b * NCK * nblk];
-    const int padded = (c + TILE_ROWS - 1) / TILE_ROWS * TILE_ROWS;
-    layout[LY_COUNT + b] = c;
-    if (b < 4) {
-      layout[LY_ROW0 + b] = r1;
-      r1 += padded;
-    } else {
-      layout[LY_ROW0 + b] = rx;
-      rx += padded;
+  const int block = blockIdx.x - nlist;
+  const RowLayout lay = row_layout(blk_scan, nblk);
+  if (block == 0 && threadIdx.x == 0) {
+    layout[LY_PAIRS] = pairs;
+    for (int b = 0; b < NBUCKET; ++b) {
+      layout[LY_COUNT + b] = lay.count[b];
+      layout[LY_ROW0 + b] = lay.row0[b];
     }
+    layout[LY_ROWS1] = lay.rows1;
+    layout[LY_ROWSX] = lay.rowsx;
+    layout[LY_SLICES] = (lay.rows1 + lay.rowsx) / 32;
+    layout[LY_FLAGS] = over ? 1 : 0;
   }
-  layout[LY_PAIRS] = pairs;
-  layout[LY_ROWS1] = r1;
-  layout[LY_ROWSX] = rx;
-  layout[LY_SLICES] = (r1 + rx) / 32;
-  layout[LY_FLAGS] = flags;
-}
-
-// For every pair p = (i, j, s) find q = (j, i, -s) in j's list and keep the positions of
-// the two inside their lists: rev[p] = q - nl_off[j], rev[q] = p - nl_off[i]. The list is
-// symmetric because the FP64 distance test gives the same value for both orders (negating
-// a rounded difference is exact). Only pairs with i <= j search (and write both entries);
-// for a pair of an atom with its own image (i == j) both threads write the same two
-// values; rev holds -1 from the filling pass, so a pair left without a partner shows in
-// the slot pass.
-// One thread per pair: a work-group takes the pairs of NT consecutive atoms, finds each
-// pair's atom by bisection in the group's offsets (in LDS), then scans j's list.
-__global__ __launch_bounds__(NT) void k_reverse(int n, const int* __restrict__ nl_off,
-                                                const int* __restrict__ nl_j,
-                                                const int32_t* __restrict__ nl_s,
-                                                int* __restrict__ rev, const int* __restrict__ layout) {
-  if (layout[LY_FLAGS]) return;
-  __shared__ int offs[NT + 1];
-  const int a0 = blockIdx.x * NT;
-  const int na = min(NT, n - a0);
-  for (int k = threadIdx.x; k <= na; k += NT) offs[k] = nl_off[a0 + k];
-  __syncthreads();
-  const int p0 = offs[0], p1 = offs[na];
-  for (int p = p0 + threadIdx.x; p < p1; p += NT) {
-    const int j = nl_j[p];
-    int lo = 0, hi = na;            // largest k with offs[k] <= p
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (offs[mid] <= p) lo = mid;
-      else hi = mid;
-    }
-    const int i = a0 + lo;
-    if (j < i) continue;            // found by the partner's thread
-    int sx, sy, sz;
-    unpack_shift(nl_s[p], sx, sy, sz);
-    const int32_t want = pack_shift(-sx, -sy, -sz);
-    int found = -1;
-    const int q0 = nl_off[j], q1 = nl_off[j + 1];
-    // four entries per step, their loads issued together
-    for (int q = q0; q < q1 && found < 0; q += 4) {
-      int jj[4];
-      int32_t ss[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        jj[u] = q + u < q1 ? nl_j[q + u] : -1;
-        ss[u] = q + u < q1 ? nl_s[q + u] : 0;
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (found < 0 && jj[u] == i && ss[u] == want) found = q + u;
-    }
-    if (found >= 0) {
-      rev[p] = found - q0;
-      rev[found] = p - offs[lo];
-    }
-  }
-}
-
-// Rows of each bucket in key order (see row_key); the rank among equal keys follows the
-// internal index (block scan of the key counts, then the rank inside the block).
-__global__ __launch_bounds__(NT) void k_assign_rows(int n, const int* __restrict__ bucket,
-                                                    const int* __restrict__ cnt,
-                                                    const int* __restrict__ blk_scan, int nblk,
-                                                    const int* __restrict__ layout, int* __restrict__ row_of,
-                                                    int* __restrict__ aor1, int* __restrict__ aorx) {
   __shared__ int keys[NT];
-  const int i = blockIdx.x * NT + threadIdx.x;
+  const int i = block * NT + threadIdx.x;
   const int b = i < n ? bucket[i] : -1;
   const int key = b >= 0 ? row_key(b, cnt[i]) : -1;
   keys[threadIdx.x] = key;
@@ -439,9 +538,11 @@ __global__ __launch_bounds__(NT) void k_assign_rows(int n, const int* __restrict
     return;
   }
   int rank = 0;
-  for (int q = 0; q < (int)threadIdx.x; ++q) rank += keys[q] == key ? 1 : 0;
-  const int row = layout[LY_ROW0 + b] + (blk_scan[(size_t)key * nblk + blockIdx.x] -
-                                         blk_scan[(size_t)b * NCK * nblk]) + rank;
+  for (int k = 0; k < (int)threadIdx.x; ++k) rank += keys[k] == key ? 1 : 0;
+  int row0 = 0;
+#pragma unroll
+  for (int k = 0; k < NBUCKET; ++k) row0 = b == k ? lay.row0[k] : row0;
+  const int row = row0 + (blk_scan[(size_t)key * nblk + block] - blk_scan[(size_t)b * NCK * nblk]) + rank;
   row_of[i] = row;
   if (b < 4) aor1[row] = i;
   else aorx[row] = i;
@@ -450,53 +551,68 @@ __global__ __launch_bounds__(NT) void k_assign_rows(int n, const int* __restrict
 // Row R of atom i: 144-wide rows R = row_of[i], mixed rows R = rows1 + row_of[i].
 __device__ inline int global_row(int b, int r, int rows1) { return b < 4 ? r : rows1 + r; }
 
-// Per-row copies of the atom's pair count and cell (padding rows: 0, 0), over the row
-// capacity; rows past the build's rows are left alone.
-__global__ __launch_bounds__(NT) void k_row_meta(int row_cap, const int* __restrict__ layout,
-                                                 const int* __restrict__ aor1, const int* __restrict__ aorx,
-                                                 const int* __restrict__ cnt, const int* __restrict__ sid,
-                                                 int* __restrict__ cnt_row, int* __restrict__ sid_row) {
-  const int R = blockIdx.x * NT + threadIdx.x;
-  const int rows1 = layout[LY_ROWS1], rows = rows1 + layout[LY_ROWSX];
-  if (R >= rows || R >= row_cap) return;
-  const int i = R < rows1 ? aor1[R] : aorx[R - rows1];
-  cnt_row[R] = i >= 0 ? cnt[i] : 0;
-  sid_row[R] = i >= 0 ? sid[i] : 0;
+// Work-groups [0, nrows): per-row copies of the atom's pair count and cell (padding rows: 0,
+// 0) and the length of each 32-row slice, the largest pair count of its rows (zero for the
+// slices past the build's, so that the prefix over them ends at the build's total).
+// Work-groups from nrows, only when some atom has more pairs than the cache: the reverse
+// positions left open by k_lists, from the complete list.
+__global__ __launch_bounds__(NT) void k_rows(int row_max, int nrows, const int* __restrict__ layout,
+                                             const int* __restrict__ build_status, const int* __restrict__ aor1,
+                                             const int* __restrict__ aorx, const int* __restrict__ cnt,
+                                             const int* __restrict__ sid, int* __restrict__ cnt_row,
+                                             int* __restrict__ sid_row, int* __restrict__ slice_len, int n,
+                                             const int* __restrict__ nl_off, const int* __restrict__ nl_j,
+                                             const int32_t* __restrict__ nl_s, int* __restrict__ nl_rev) {
+  if ((int)blockIdx.x < nrows) {
+    const int R = blockIdx.x * NT + threadIdx.x;
+    const int rows1 = layout[LY_ROWS1], rows = rows1 + layout[LY_ROWSX];
+    int c = 0;
+    if (R < rows) {
+      const int i = R < rows1 ? aor1[R] : aorx[R - rows1];
+      c = i >= 0 ? cnt[i] : 0;
+      cnt_row[R] = c;
+      sid_row[R] = i >= 0 ? sid[i] : 0;
+    }
+#pragma unroll
+    for (int d = 16; d > 0; d >>= 1) c = max(c, __shfl_xor(c, d, 32));
+    if ((threadIdx.x & 31) == 0 && R < row_max) slice_len[R >> 5] = c;
+    return;
+  }
+  if (!(*build_status & BUILD_DENSE) || layout[LY_FLAGS]) return;
+  const int i = (blockIdx.x - nrows) * SA + (threadIdx.x >> 4);
+  if (i >= n) return;
+  const int p0 = nl_off[i], own = nl_off[i + 1] - p0;
+  for (int k = threadIdx.x & 15; k < own; k += 16) {
+    const int j = nl_j[p0 + k];
+    if (own <= PAIR_CACHE && cnt[j] <= PAIR_CACHE) continue;
+    const int32_t want = negated_shift(nl_s[p0 + k]);
+    const int q0 = nl_off[j], q1 = nl_off[j + 1];
+    for (int m = q0; m < q1; ++m)
+      if (nl_j[m] == i && nl_s[m] == want) {
+        nl_rev[p0 + k] = m - q0;
+        break;
+      }
+  }
 }
 
 // Row of every atom in caller order and the slot of its first pair in internal order (-1:
-// no listed pair, no row).
+// no listed pair, no row); the first work-item also records the slots of the build.
 __global__ __launch_bounds__(NT) void k_atom_rows(int n, const int* __restrict__ bucket,
-                                                  const int* __restrict__ row_of, const int* __restrict__ layout,
+                                                  const int* __restrict__ row_of, int* __restrict__ layout,
                                                   const int* __restrict__ perm, const int* __restrict__ slice_base,
+                                                  int slice_max, long long slot_cap,
                                                   int* __restrict__ row_caller, int* __restrict__ slot0) {
   const int i = blockIdx.x * NT + threadIdx.x;
+  if (i == 0) {
+    const int groups = slice_base[slice_max];
+    layout[LY_SLOTS32] = groups;
+    if ((long long)groups * 32 > slot_cap) layout[LY_FLAGS] |= 2;
+  }
   if (i >= n) return;
   const int b = bucket[i];
   const int R = b < 0 ? -1 : global_row(b, row_of[i], layout[LY_ROWS1]);
   row_caller[perm[i]] = R;
   slot0[i] = R < 0 ? -1 : slot_of(slice_base, R, 0);
-}
-
-// Length of each 32-row slice: the largest pair count of its rows (padding rows count 0);
-// zero for the slices past the build's, so that the prefix over the capacity ends at the
-// build's total.
-__global__ __launch_bounds__(NT) void k_slice_len(int slice_cap, const int* __restrict__ layout,
-                                                  const int* __restrict__ cnt_row, int* __restrict__ slice_len) {
-  const int S = blockIdx.x * NT + threadIdx.x;
-  if (S >= slice_cap) return;
-  int m = 0;
-  if (S < layout[LY_SLICES])
-    for (int r = 0; r < 32; ++r) m = max(m, cnt_row[S * 32 + r]);
-  slice_len[S] = m;
-}
-
-__global__ void k_layout_slots(const int* __restrict__ slice_base, int slice_cap, long long slot_cap,
-                               int* __restrict__ layout) {
-  if (threadIdx.x != 0) return;
-  const int groups = slice_base[slice_cap];
-  layout[LY_SLOTS32] = groups;
-  if ((long long)groups * 32 > slot_cap) layout[LY_FLAGS] |= 2;
 }
 
 // The sliced pair layout in one pass, a work-group per 32-row slice: thread (h, l) of 8 x 32
@@ -569,16 +685,6 @@ __global__ __launch_bounds__(NT) void k_slots(const int* __restrict__ layout, co
   }
 }
 
-// End of a build: the build's status word and the caller-visible one (which is moved to
-// the host here and cleared, so that no flag of the ended interval is lost) into the layout.
-__global__ void k_layout_status(int* __restrict__ status, int* __restrict__ layout) {
-  if (threadIdx.x == 0) {
-    layout[LY_BUILD] = status[1];
-    layout[LY_STATUS] = status[0];
-    status[0] = 0;
-  }
-}
-
 // The fills of a build in one launch: up to ten (array, count, value) segments, every
 // work-item striding over each of them.
 struct ClearSeg {
@@ -589,9 +695,19 @@ struct ClearSeg {
 struct ClearArgs {
   ClearSeg seg[10];
   int nseg;
+  int* status;    // [0] the caller-visible word, [1] the build's; the layout record follows
+  int* layout;
 };
 __global__ __launch_bounds__(NT) void k_clear(ClearArgs a) {
   const long long t = (long long)blockIdx.x * NT + threadIdx.x;
+  if (t == 0) {
+    // the caller-visible status word moves to the layout record (read by the host at the end
+    // of the build) and is cleared: no flag of the ended interval is lost
+    for (int k = 0; k < LY_N; ++k) a.layout[k] = 0;
+    a.layout[LY_STATUS] = a.status[0];
+    a.status[0] = 0;
+    a.status[1] = 0;
+  }
   const long long stride = (long long)gridDim.x * NT;
   for (int k = 0; k < a.nseg; ++k) {
     int* __restrict__ p = a.seg[k].p;
@@ -640,7 +756,8 @@ int build_list(flare_state* s, const double* x, const double* y, const double* z
     set_error("more reduction tasks than the state holds");
     return FLARE_E_CAPACITY;
   }
-  // the per-cell host data through the pinned stage: grids, offsets, tasks, task ranges
+  // the per-cell host data through the pinned stage in one copy: grids, offsets, tasks, task
+  // ranges (the device copies stand in the same order, see flare_state_create)
   char* hs = s->h_stage;
   const size_t b_grid = nc * sizeof(CellGrid), b_off = (nc + 1) * sizeof(int);
   const size_t b_task = s->tasks.size() * sizeof(RedTask), b_first = (nc + 1) * sizeof(int);
@@ -648,25 +765,31 @@ int build_list(flare_state* s, const double* x, const double* y, const double* z
   std::memcpy(hs + b_grid, s->struct_off.data(), b_off);
   std::memcpy(hs + b_grid + b_off, s->tasks.data(), b_task);
   std::memcpy(hs + b_grid + b_off + b_task, s->first_task.data(), b_first);
-  HIPCHK(hipMemcpyAsync(s->d_grids, hs, b_grid, hipMemcpyHostToDevice, st));
-  HIPCHK(hipMemcpyAsync(s->d_struct_off, hs + b_grid, b_off, hipMemcpyHostToDevice, st));
-  HIPCHK(hipMemcpyAsync(s->d_tasks, hs + b_grid + b_off, b_task, hipMemcpyHostToDevice, st));
-  HIPCHK(hipMemcpyAsync(s->d_first_task, hs + b_grid + b_off + b_task, b_first, hipMemcpyHostToDevice, st));
+  s->d_grids = reinterpret_cast<CellGrid*>(s->d_stage);
+  s->d_struct_off = reinterpret_cast<int*>(s->d_stage + b_grid);
+  s->d_tasks = reinterpret_cast<RedTask*>(s->d_stage + b_grid + b_off);
+  s->d_first_task = reinterpret_cast<int*>(s->d_stage + b_grid + b_off + b_task);
+  HIPCHK(hipMemcpyAsync(s->d_stage, hs, b_grid + b_off + b_task + b_first, hipMemcpyHostToDevice, st));
   // the build checks its inputs in a word of its own (d_status[1]); the caller-visible
-  // word d_status[0] keeps what the per-step calls raised until k_layout_status moves it
+  // word d_status[0] keeps what the per-step calls raised until k_clear moves it
   int* bst = s->d_status + 1;
+  s->d_layout = s->d_status + 16;
+  // rows of this many atoms: every bucket's padding included
+  const int row_max = std::min(s->row_cap, (n + NBUCKET * TILE_ROWS + 31) / 32 * 32);
+  const int slice_max = row_max / 32;
   {
-    // everything the build starts from: its status word and layout record, the bin
+    // everything the build starts from: its status word and layout record, the bin and key
     // counters, no atom in any row, zero energies, variances and norms (atoms without a
     // listed pair keep them)
     ClearArgs c{};
+    c.status = s->d_status;
+    c.layout = s->d_layout;
     auto seg = [&](int* p, long long cnt, int v) { c.seg[c.nseg++] = ClearSeg{p, cnt, v}; };
-    seg(bst, 1, 0);
-    seg(s->d_layout, LY_N, 0);
     seg(s->bin_count, (long long)nbins + 1, 0);
     seg(s->bin_fill, (long long)nbins + 1, 0);
-    seg(s->atom_of_row1, (long long)s->row_cap + 1, -1);
-    seg(s->atom_of_rowx, (long long)s->row_cap + 1, -1);
+    if (n <= FEW_ATOMS) seg(s->blk_bucket, (long long)NKEY * nblk, 0);
+    seg(s->atom_of_row1, row_max, -1);
+    seg(s->atom_of_rowx, row_max, -1);
     seg(reinterpret_cast<int*>(s->e_int), n, 0);
     seg(reinterpret_cast<int*>(s->v_int), n, 0);
     seg(reinterpret_cast<int*>(s->nrm), n, 0);
@@ -680,15 +803,14 @@ int build_list(flare_state* s, const double* x, const double* y, const double* z
   scan_exclusive(s->bin_count, s->bin_start, nbins, s->scan_scratch, st);
   if (n > 0) {
     k_bin_scatter<<<grid_of(n), NT, 0, st>>>(n, s->crec, s->bin_start, s->bin_fill, s->sorted);
-    k_bin_sort<<<grid_of(nbins), NT, 0, st>>>(nbins, s->bin_start, s->sorted);
-    k_to_internal<<<grid_of(n), NT, 0, st>>>(n, s->sorted, s->crec, species, s->perm, s->inv_perm, s->sp, s->sid, s->bin, s->w, s->wf,
-                                             s->off);
+    k_to_internal<<<grid_of(n), NT, 0, st>>>(n, s->sorted, s->bin_start, s->crec, species, s->perm, s->inv_perm,
+                                             s->sp, s->sid, s->bin, s->w, s->wf, s->off);
   }
   const double rl2 = s->r_list * s->r_list;
   // Band of the FP32 first test. Wrapped coordinates lie in [0, W] (W the largest box side),
-  // image shifts are at most K box sides (K the largest stencil half-width), u = 2^-24. A
-  // candidate near the list radius has every FP32 pair-vector component within
-  // e = u ((3 + K) W + 2 r_list) of the FP64 one, so the FP32 |Delta|^2 is within
+  // image shifts are at most K box sides (K the largest stencil half-width), formed in FP32
+  // from the rounded side (within 2 u K W), u = 2^-24. A candidate near the list radius has
+  // every FP32 pair-vector component within e = u ((3 + 3 K) W + 2 r_list) of the FP64 one, so the FP32 |Delta|^2 is within
   // e (2 sqrt(3) r_list + 3 e) + 4 u r_list^2 of the FP64 value; the band is twice that.
   double wmax = 0.0;
   int kmax = 1;
@@ -698,47 +820,41 @@ int build_list(flare_state* s, const double* x, const double* y, const double* z
       kmax = std::max(kmax, g.K[ax]);
     }
   const double u32 = std::ldexp(1.0, -24);
-  const double e32 = u32 * ((3.0 + kmax) * wmax + 2.0 * s->r_list);
+  const double e32 = u32 * ((3.0 + 3.0 * kmax) * wmax + 2.0 * s->r_list);
   const double band = 2.0 * (e32 * (2.0 * std::sqrt(3.0) * s->r_list + 3.0 * e32) + 4.0 * u32 * rl2);
   const float lo2 = std::nextafter((float)(rl2 - band), -INFINITY);
   const float hi2 = std::nextafter((float)(rl2 + band), INFINITY);
-  if (n > 0)
-    k_pairs<false><<<nblk, NT, 0, st>>>(n, s->d_grids, s->sid, s->bin, s->w, s->wf, s->bin_start, rl2, lo2, hi2,
-                                         s->nl_cnt,
-                                         s->envmask, s->bucket, s->blk_bucket, nblk, nullptr, nullptr, nullptr,
-                                         nullptr, s->pair_cache, nullptr);
-  scan_exclusive(s->nl_cnt, s->nl_off, n, s->scan_scratch, st);
-  scan_exclusive(s->blk_bucket, s->blk_bucket_scan, NKEY * nblk, s->scan_scratch, st);
-  k_off_check<<<grid_of(n + 1), NT, 0, st>>>(n, s->nl_off, bst);
-  k_layout_rows<<<1, 64, 0, st>>>(n, s->nl_off, s->blk_bucket_scan, nblk, s->max_pairs, bst, s->d_layout);
-  if (n > 0) {
-    k_pairs<true><<<nblk, NT, 0, st>>>(n, s->d_grids, s->sid, s->bin, s->w, s->wf, s->bin_start, rl2, lo2, hi2,
-                                        nullptr,
-                                        nullptr, nullptr, nullptr, nblk, s->nl_off, s->nl_j, s->nl_s, s->nl_rev,
-                                        s->pair_cache, s->d_layout);
-    k_reverse<<<nblk, NT, 0, st>>>(n, s->nl_off, s->nl_j, s->nl_s, s->nl_rev, s->d_layout);
-    k_assign_rows<<<nblk, NT, 0, st>>>(n, s->bucket, s->nl_cnt, s->blk_bucket_scan, nblk, s->d_layout, s->row_of,
-                                        s->atom_of_row1, s->atom_of_rowx);
-  }
-  k_row_meta<<<grid_of(s->row_cap), NT, 0, st>>>(s->row_cap, s->d_layout, s->atom_of_row1, s->atom_of_rowx,
-                                                  s->nl_cnt, s->sid, s->cnt_row, s->sid_row);
-  k_slice_len<<<grid_of(s->slice_cap), NT, 0, st>>>(s->slice_cap, s->d_layout, s->cnt_row, s->slice_len);
-  scan_exclusive(s->slice_len, s->slice_base, s->slice_cap, s->scan_scratch, st);
-  k_layout_slots<<<1, 64, 0, st>>>(s->slice_base, s->slice_cap, s->slot_cap, s->d_layout);
-  if (n > 0)
-    k_atom_rows<<<nblk, NT, 0, st>>>(n, s->bucket, s->row_of, s->d_layout, s->perm, s->slice_base, s->row_caller,
-                                      s->slot0);
-  k_slots<<<s->slice_cap, NT, 0, st>>>(s->d_layout, s->atom_of_row1, s->atom_of_rowx, s->nl_off, s->nl_j, s->nl_s,
-                                       s->nl_rev, s->slot0, s->slice_base, s->w, s->sid, s->d_grids, s->slot_atom,
-                                       s->slot_j, s->slot_rev, s->slot_d0, s->geom, bst);
-  k_layout_status<<<1, 64, 0, st>>>(s->d_status, s->d_layout);
-  HIPCHK(hipMemcpyAsync(s->h_info, s->d_layout, LY_N * sizeof(int), hipMemcpyDeviceToHost, st));
+  const PairSearch q{s->d_grids, s->sid, s->bin, s->w, s->wf, s->bin_start, rl2, lo2, hi2};
+  const bool many = n > FEW_ATOMS;
+  const int ngroup = (n + SA - 1) / SA;          // work-groups of 16 atoms
+  if (many)
+    k_search_many<<<nblk, NT, 0, st>>>(n, q, s->nl_cnt, s->bucket, s->blk_bucket, nblk, s->pair_cache, bst);
+  else if (n > 0)
+    k_search<16><<<ngroup, NT, 0, st>>>(n, q, s->nl_cnt, s->bucket, s->blk_bucket, nblk, s->pair_cache, bst);
+  scan_exclusive2(s->nl_cnt, s->nl_off, n, s->blk_bucket, s->blk_bucket_scan, NKEY * nblk, s->scan_scratch, bst,
+                  BUILD_OVERFLOW, st);
+  const int nlist = many ? (n + MANY_AW - 1) / MANY_AW : ngroup;
+  auto lists = many ? k_lists<MANY_AW> : k_lists<SA>;
+  lists<<<nlist + std::max(nblk, 1), NT, 0, st>>>(n, nlist, q, s->nl_cnt, s->nl_off, s->pair_cache, s->max_pairs, bst,
+                                                  s->nl_j, s->nl_s, s->nl_rev, s->bucket, s->blk_bucket_scan, nblk,
+                                                  s->row_of, s->atom_of_row1, s->atom_of_rowx, s->d_layout);
+  const int nrows = grid_of(row_max);
+  k_rows<<<nrows + ngroup, NT, 0, st>>>(row_max, nrows, s->d_layout, bst, s->atom_of_row1, s->atom_of_rowx, s->nl_cnt,
+                                       s->sid, s->cnt_row, s->sid_row, s->slice_len, n, s->nl_off, s->nl_j, s->nl_s,
+                                       s->nl_rev);
+  scan_exclusive(s->slice_len, s->slice_base, slice_max, s->scan_scratch, st);
+  k_atom_rows<<<std::max(nblk, 1), NT, 0, st>>>(n, s->bucket, s->row_of, s->d_layout, s->perm, s->slice_base,
+                                                slice_max, s->slot_cap, s->row_caller, s->slot0);
+  k_slots<<<slice_max, NT, 0, st>>>(s->d_layout, s->atom_of_row1, s->atom_of_rowx, s->nl_off, s->nl_j, s->nl_s,
+                                    s->nl_rev, s->slot0, s->slice_base, s->w, s->sid, s->d_grids, s->slot_atom,
+                                    s->slot_j, s->slot_rev, s->slot_d0, s->geom, bst);
+  HIPCHK(hipMemcpyAsync(s->h_info, s->d_status, (16 + LY_N) * sizeof(int), hipMemcpyDeviceToHost, st));
   HIPCHK(hipGetLastError());
   HIPCHK(hipStreamSynchronize(st));      // the build's one wait
-  const int* L = s->h_info;
+  const int* L = s->h_info + 16;
   s->flags_at_build = L[LY_STATUS];
   s->flags_pending |= L[LY_STATUS];
-  const int flags = L[LY_BUILD];
+  const int flags = s->h_info[1];
   if (flags & FLARE_FLAG_SPECIES) {
     set_error("species index outside [0, n_species)");
     return FLARE_E_SPECIES;

@@ -159,7 +159,6 @@ struct flare_state {
   int* sp = nullptr;         // species, internal order
   int* sid = nullptr;        // cell id, internal order
   int* bin = nullptr;        // global bin id, internal order
-  int* envmask = nullptr;    // species bits of listed neighbours
   int* bucket = nullptr;
   int* row_of = nullptr;     // row of each internal atom inside its width class (-1: none)
   int* nl_cnt = nullptr;
@@ -177,7 +176,7 @@ struct flare_state {
   int* sorted = nullptr;     // bin-sorted caller indices
   int* row_caller = nullptr; // [N] row of each atom, caller order (-1: none)
   int* slot0 = nullptr;      // [N] slot of each internal atom's first pair (-1: no row)
-  int2* pair_cache = nullptr;  // list build: first PAIR_CACHE pairs of each atom, [k][N]
+  int2* pair_cache = nullptr;  // list build: first PAIR_CACHE pairs of each atom, [N][k]
 
   // ---- per-pair (capacity max_pairs) ----
   int* nl_j = nullptr;       // internal index of the neighbour
@@ -185,16 +184,18 @@ struct flare_state {
   int* nl_rev = nullptr;     // position of the reverse pair (j, i, -s) inside j's list
 
   // ---- per cell, bin, block ----
-  flare::CellGrid* d_grids = nullptr;   // [cell_cap]
-  int* d_struct_off = nullptr;          // [cell_cap + 1]
+  char* d_stage = nullptr;              // the per-cell host data of a build, one copy: the four arrays
+                                        // d_grids .. d_first_task stand in it, one after the other
+  flare::CellGrid* d_grids = nullptr;   // [n_struct]
+  int* d_struct_off = nullptr;          // [n_struct + 1]
   int* bin_count = nullptr;             // [bin_cap + 1]
   int* bin_start = nullptr;
   int* bin_fill = nullptr;
   int* blk_bucket = nullptr;            // [NKEY][nblk_cap]
   int* blk_bucket_scan = nullptr;
   int* scan_scratch = nullptr;
-  flare::RedTask* d_tasks = nullptr;    // [task_cap]
-  int* d_first_task = nullptr;          // [cell_cap + 1] task range of each cell
+  flare::RedTask* d_tasks = nullptr;    // [tasks]
+  int* d_first_task = nullptr;          // [n_struct + 1] task range of each cell
   double* red_e = nullptr;              // [task_cap][2] (sum, compensation)
   float* red_s = nullptr;               // [task_cap]
 
@@ -233,11 +234,11 @@ struct flare_state {
   flare::Timers timers;
 
   // ---- status ----
-  int* d_status = nullptr;   // [0] caller-visible status word (sticky), [1] list-build checks
+  int* d_status = nullptr;   // [0] caller-visible status word (sticky), [1] list-build checks, [16 ...] d_layout
   int flags_at_build = 0;    // word [0] as the last list build found it
   int flags_pending = 0;     // flags moved to the host by list builds, not yet returned by flare_status
   int* d_layout = nullptr;   // list build: sizes formed on the device (see nlist.hip)
-  int* h_info = nullptr;     // pinned host copy of d_layout, read once per build
+  int* h_info = nullptr;     // pinned host copy of d_status and d_layout, read once per build
   char* h_stage = nullptr;   // pinned staging of the per-cell host data of a build
   size_t h_stage_bytes = 0;
 };
