@@ -46,7 +46,8 @@ constexpr int GSTRIDE = ND + 4;
 struct MixedForms {
   const float* D;
   const float* Y;
-  const float* P;        // V shares [rows][17], or null
+  const float* P;        // V shares [rows][17] in FP32, or null
+  const double* P64;     // the same in FP64, or null
   const float* nrm;
   float* e_int;
   float* v_int;
@@ -81,8 +82,9 @@ __global__ __launch_bounds__(MTHREADS) void k_adjoint_mixed(SlotView v, int rows
       q.e_int[i] = e;
       q.e_row[row] = e;
     }
-    if (q.P) {
-      const float var = mixed_row_variance(q.P + (size_t)local * (ND / 32), L);
+    if (q.P || q.P64) {
+      const float var = q.P ? mixed_row_variance(q.P + (size_t)local * (ND / 32), L)
+                            : mixed_row_variance(q.P64 + (size_t)local * (ND / 32), L);
       if (L == 0) {
         q.v_int[i] = var;
         q.v_row[row] = var;
@@ -166,7 +168,8 @@ void adjoint_rows144(flare_state* s) {
 void adjoint_mixed_chunk(flare_state* s, int r0, int nr, bool want_v) {
   const SlotView v = slot_view(s);
   StageTimer tm(s, FLARE_T_FORCEX);
-  MixedForms q{s->Dx, s->Yx, want_v ? s->Px : nullptr, s->nrm, s->e_int, s->v_int, s->e_row + s->rows1,
+  const bool v64 = s->model->var64;
+  MixedForms q{s->Dx, s->Yx, want_v && !v64 ? s->Px : nullptr, want_v && v64 ? s->Px64 : nullptr, s->nrm, s->e_int, s->v_int, s->e_row + s->rows1,
                s->v_row + s->rows1};
   if (nr > 0)
     k_adjoint_mixed<<<nr / MROWS, MTHREADS, 0, s->stream>>>(v, s->rows1, r0, s->atom_of_rowx, q, s->f_own);

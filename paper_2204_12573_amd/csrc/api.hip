@@ -240,7 +240,7 @@ static void state_arrays(flare_state* s, F&& f) {
   f((void**)&s->Yx, X * ND * 4);
   f((void**)&s->Px, X * 17 * 4);
   f((void**)&s->D6x, X * ND * 6);
-  f((void**)&s->Px64, X * 9 * 8);
+  f((void**)&s->Px64, X * 17 * 8);
   f((void**)&s->slice_len, (SL + 1) * 4);
   f((void**)&s->slice_base, (SL + 1) * 4);
   f((void**)&s->slot_atom, SC * 4);
@@ -676,7 +676,7 @@ static void mixed_rows(flare_state* s, float* d_out, bool want_e, bool want_v, b
     const int nr = std::min(s->mix_cap, s->rowsx - r0);
     desc_mixed_chunk(s, r0, nr, d_out);
     forms_mixed_chunk(s, r0, nr, want_e || want_f, want_v, !want_f);
-    if (want_f) adjoint_mixed_chunk(s, r0, nr, want_v && !s->model->var64);
+    if (want_f) adjoint_mixed_chunk(s, r0, nr, want_v);
   }
   // with one chunk the workspace keeps beta d of these positions for a later backward
   if ((want_e || want_f) && s->rowsx <= s->mix_cap) s->gx_gen = s->pos_gen;

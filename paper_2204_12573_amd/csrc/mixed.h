@@ -54,9 +54,13 @@ __device__ __forceinline__ float mixed_row_energy(const float4* __restrict__ d4,
   for (int k = 0; k < NQ4; ++k) e += (d[k].x * y[k].x + d[k].y * y[k].y) + (d[k].z * y[k].z + d[k].w * y[k].w);
   return sum16(e);
 }
-// Variance of the row from the shares of its 17 column pairs.
+// Variance of the row from the shares of its 17 column pairs (FP64 ones summed in FP64 and
+// rounded once).
 __device__ __forceinline__ float mixed_row_variance(const float* __restrict__ p, int L) {
   return sum16(p[L] + (L == 0 ? p[16] : 0.f));
+}
+__device__ __forceinline__ float mixed_row_variance(const double* __restrict__ p, int L) {
+  return (float)sum16d(p[L] + (L == 0 ? p[16] : 0.0));
 }
 
 // Channels (a, b) of packed B2 pair P of a 544-wide row: (H,H) pairs 0..35 (na <= nb,

@@ -304,126 +304,121 @@ __global__ __launch_bounds__(256) void k_forms544_finish(int rows, int mode, con
 // Variance of the mixed rows in the split forms, in FP64: V_i = |L_s^T d_i|^2 with the FP64
 // Cholesky factor of Sigma_s on v_mfma_f64_16x16x4_f64 (exact products of the FP32 row and
 // the FP64 factor, FP64 sums), so the near-cancelling d^T Sigma d keeps FP64 accuracy in the
-// form. A wave owns 32 rows (two 16-row blocks, which share every B fragment) and a group of
-// four column blocks of Z = D L: for every K chunk from the group's first block (L[k][n] = 0
-// for k < n) lane (m, q) supplies D[row m][16 kc + 4 q + t] and the fragments
-// L[16 kc + 4 q + t][16 cb + m] (fragment order [cb][kc][t][lane]); eight independent
-// accumulators per k-step, and the next chunk's fragments load while this one runs.
-// Accumulator r of lane (n, q) holds row q + 4 r of the block (the FP64 instruction's
-// layout). The group's sum of squares per row goes to P64[row][group]; k_var544_finish adds
-// the groups in a fixed order.
+// form. A wave owns 32 rows (two 16-row blocks, which share every B fragment) and one pair m
+// of 16-column blocks of Z = D L: for every K chunk from 2 m on (L[k][n] = 0 for k < n) lane
+// (l, q) supplies D[row l][16 kc + 4 q + t] and the fragments L[16 kc + 4 q + t][16 cb + l]
+// (fragment order [cb][kc][t][lane]); four independent accumulators per k-step, and the next
+// chunk's fragments load while this one runs. Accumulator r of lane (n, q) holds row q + 4 r
+// of the block (the FP64 instruction's layout). The pair's sum of squares per row goes to
+// P64[row][m]; the pairs are added in a fixed order.
+// Bound by the FP64 matrix rate (595 blocks x 8 products of 64 cycles a 32-row block: 62 us
+// for 16 k rows). A pair's work falls from 34 chunks to 2, so the pairs go out longest first
+// as work units of their own, 95 us (35 us for 4 k rows, 23 us for 128); four-block groups in
+// balanced pairs of equal length left three waves on some SIMDs and two on others: 111 us
+// (57 us for 4 k rows).
 constexpr int XCB = ND / 16;                 // 34 column blocks
-constexpr int XG = 4;                        // column blocks per wave
-constexpr int NXG = (XCB + XG - 1) / XG;     // 9 groups
 typedef double d4 __attribute__((ext_vector_type(4)));
 
 struct VarArgs {
   const float* D;          // [rows][544]
   int rows;                // padded rows (a multiple of 64)
   int split_row;           // rows >= split_row belong to the second bucket (Pt centre)
+  const int* aor;          // as XArgs
+  int n_given;
   const double* L[2];      // per bucket: fragments of the factor
-  double* P64;             // [rows][NXG]
+  double* P64;             // [rows][XNP]
 };
 
-// One column group g of one 32-row block.
-__device__ __forceinline__ void var544_group(const VarArgs& q, int row0, int g, int lane) {
-  const int l16 = lane & 15, grp = lane >> 4;
-  // the split between the two buckets falls on a 128-row boundary: one factor per block
-  const double* __restrict__ L = (row0 >= q.split_row ? q.L[1] : q.L[0]) + lane;
-  const float* __restrict__ d0 = q.D + (size_t)(row0 + l16) * ND + 4 * grp;
-  const float* __restrict__ d1 = d0 + (size_t)16 * ND;
-  d4 acc[2][XG];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int u = 0; u < XG; ++u) acc[i][u] = d4{0.0, 0.0, 0.0, 0.0};
-  const int cb0 = g * XG;
-  auto load_b = [&](int kc, double (&b)[XG][4]) {
-#pragma unroll
-    for (int u = 0; u < XG; ++u)
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-        b[u][t] = (cb0 + u < XCB && cb0 + u <= kc) ? L[(((size_t)(cb0 + u) * XCB + kc) * 4 + t) * 64] : 0.0;
-  };
-  double bA[XG][4], bB[XG][4];
-  load_b(cb0, bA);
-  for (int kc = cb0; kc < XCB; kc += 2) {
-    // two chunks per trip, one B buffer each; the next one's loads ahead of the MFMAs
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      const int k = kc + half;
-      if (k >= XCB) break;
-      double (&cur)[XG][4] = half ? bB : bA;
-      double (&nxt)[XG][4] = half ? bA : bB;
-      if (k + 1 < XCB) load_b(k + 1, nxt);
-      const float4 a0 = *reinterpret_cast<const float4*>(d0 + k * 16);
-      const float4 a1 = *reinterpret_cast<const float4*>(d1 + k * 16);
-      const double av[2][4] = {{a0.x, a0.y, a0.z, a0.w}, {a1.x, a1.y, a1.z, a1.w}};
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int u = 0; u < XG; ++u)
-#pragma unroll
-          for (int i = 0; i < 2; ++i)
-            acc[i][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[i][t], cur[u][t], acc[i][u], 0, 0, 0);
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      double ss = 0.0;
-#pragma unroll
-      for (int u = 0; u < XG; ++u) ss = fma(acc[i][u][r], acc[i][u][r], ss);
-      ss = sum16d(ss);
-      if (l16 == 0) q.P64[(size_t)(row0 + 16 * i + grp + 4 * r) * NXG + g] = ss;
-    }
-}
-
-// Group g of a row block runs 34 - 4 g chunks, so groups g and 8 - g together run 36: the
-// first four tasks of every 32-row block are such pairs, the fifth the middle group alone
-// (18 chunks). Tasks go out longest first (all pairs, then the middle groups), so the
-// short ones fill in at the end.
+constexpr int VRB = 2;                       // 16-row blocks a wave (4: no faster at 16 k rows, 41 : 23 us at 128)
 __global__ __launch_bounds__(256) void k_var544_f64(VarArgs q) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int nrb = q.rows / (16 * VRB);
   const int task = blockIdx.x * 4 + wave;
-  const int nrb = q.rows / 32;
-  if (task < 4 * nrb) {
-    const int pr = task / nrb, rb = task % nrb;
-    var544_group(q, rb * 32, pr, lane);
-    var544_group(q, rb * 32, NXG - 1 - pr, lane);
-  } else if (task < 5 * nrb) {
-    var544_group(q, (task - 4 * nrb) * 32, NXG / 2, lane);
+  if (task >= nrb * XNP) return;
+  const int m = task / nrb;
+  const int row0 = (task - m * nrb) * 16 * VRB;
+  if (q.aor ? q.aor[row0] < 0 : row0 >= q.n_given) return;     // padding rows only
+  const int l16 = lane & 15, grp = lane >> 4;
+  // the split between the two buckets falls on a 128-row boundary: one factor per block
+  const double* __restrict__ L = (row0 >= q.split_row ? q.L[1] : q.L[0]) + (size_t)2 * m * XCB * 4 * 64 + lane;
+  const float* __restrict__ d0 = q.D + (size_t)(row0 + l16) * ND + 4 * grp;
+  d4 acc[VRB][2];
+#pragma unroll
+  for (int i = 0; i < VRB; ++i)
+#pragma unroll
+    for (int u = 0; u < 2; ++u) acc[i][u] = d4{0.0, 0.0, 0.0, 0.0};
+  // chunk 2 m of the pair's second block lies above the diagonal and is stored as zeros
+  auto load = [&](int kc, double (&b)[2][4], float4 (&x)[VRB]) {
+    const int k = min(kc, XCB - 1);
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) b[u][t] = L[((size_t)(u * XCB + k) * 4 + t) * 64];
+#pragma unroll
+    for (int i = 0; i < VRB; ++i) x[i] = *reinterpret_cast<const float4*>(d0 + (size_t)i * 16 * ND + k * 16);
+  };
+  auto products = [&](const double (&b)[2][4], const float4 (&x)[VRB]) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int i = 0; i < VRB; ++i) {
+          const float v = t == 0 ? x[i].x : t == 1 ? x[i].y : t == 2 ? x[i].z : x[i].w;
+          acc[i][u] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)v, b[u][t], acc[i][u], 0, 0, 0);
+        }
+  };
+  double bA[2][4], bB[2][4];
+  float4 xA[VRB], xB[VRB];
+  load(2 * m, bA, xA);
+  // the chunks of a pair are even in number (34 - 2 m): two per trip, one buffer each
+  for (int kc = 2 * m; kc < XCB; kc += 2) {
+    load(kc + 1, bB, xB);
+    __builtin_amdgcn_sched_barrier(0);
+    products(bA, xA);
+    load(kc + 2, bA, xA);
+    __builtin_amdgcn_sched_barrier(0);
+    products(bB, xB);
   }
+#pragma unroll
+  for (int i = 0; i < VRB; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const double ss = sum16d(fma(acc[i][1][r], acc[i][1][r], acc[i][0][r] * acc[i][0][r]));
+      if (l16 == 0) q.P64[(size_t)(row0 + 16 * i + grp + 4 * r) * XNP + m] = ss;
+    }
 }
 
-// V of each mixed row from its group sums (fixed order), rounded to FP32 once.
+// V of each mixed row from its pair sums, rounded to FP32 once, for the calls without forces.
 __global__ __launch_bounds__(256) void k_var544_finish(int rows, const double* __restrict__ P64,
                                                        const int* __restrict__ aor, int n_given,
                                                        float* __restrict__ v_int, float* __restrict__ v_row) {
-  const int row = blockIdx.x * 256 + threadIdx.x;
+  const int row = blockIdx.x * 16 + (threadIdx.x >> 4);
+  const int L = threadIdx.x & 15;
   if (row >= rows) return;
   const int atom = aor ? aor[row] : (row < n_given ? row : -1);
   if (atom < 0) return;
-  double v = 0.0;
-#pragma unroll
-  for (int g = 0; g < NXG; ++g) v += P64[(size_t)row * NXG + g];
-  v_int[atom] = (float)v;
-  v_row[row] = (float)v;
+  const float v = mixed_row_variance(P64 + (size_t)row * XNP, L);
+  if (L == 0) {
+    v_int[atom] = v;
+    v_row[row] = v;
+  }
 }
 
 void var544_f64(flare_state* s, const float* D, int rows, int split_row, const int* aor, int n_given,
-                float* v_int, float* v_row) {
+                float* v_int, float* v_row, bool finish) {
   VarArgs q{};
   q.D = D;
   q.rows = rows;
   q.split_row = split_row;
+  q.aor = aor;
+  q.n_given = n_given;
   q.L[0] = s->model->Lx64[0];
   q.L[1] = s->model->Lx64[1];
   q.P64 = s->Px64;
-  const int tasks = rows / 32 * 5;      // per 32-row block: four pairs of groups and the middle group
-  k_var544_f64<<<(tasks + 3) / 4, 256, 0, s->stream>>>(q);
-  k_var544_finish<<<(rows + 255) / 256, 256, 0, s->stream>>>(rows, s->Px64, aor, n_given, v_int, v_row);
+  k_var544_f64<<<(rows / (16 * VRB) * XNP + 3) / 4, 256, 0, s->stream>>>(q);
+  if (finish)
+    k_var544_finish<<<(rows + 15) / 16, 256, 0, s->stream>>>(rows, s->Px64, aor, n_given, v_int, v_row);
 }
 
 }  // namespace
@@ -441,7 +436,7 @@ void forms_mixed_chunk(flare_state* s, int r0, int nr, bool want_e, bool want_v,
   float* v_row = s->v_row + s->rows1 + r0;
   const int split = s->bucket_row0[5] - r0;
   if (want_v && m->var64) {
-    var544_f64(s, s->Dx, nr, split, aor, 0, s->v_int, v_row);
+    var544_f64(s, s->Dx, nr, split, aor, 0, s->v_int, v_row, finish);
     want_v = false;
     if (!want_e) return;
   }
@@ -498,7 +493,7 @@ int forms_given_544(flare_state* s, int bucket, int n, const float* d, float* e,
     q.Y = s->Yx;
     q.P = s->Px;
     if (m->var64) {
-      var544_f64(s, s->Dx, rows, split, nullptr, nc, v + c0, s->v_row);
+      var544_f64(s, s->Dx, rows, split, nullptr, nc, v + c0, s->v_row, true);
       q.mode = 1;
     }
     launch_forms544(q, s->stream);

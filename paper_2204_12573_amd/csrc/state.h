@@ -214,7 +214,7 @@ struct flare_state {
   float* Yx = nullptr;                  // D beta
   float* Px = nullptr;                  // [mix_cap][17] variance partials of the column pairs
   uint4* D6x = nullptr;                 // the descriptors in three BF16 parts, fragment order (bf16x3.h)
-  double* Px64 = nullptr;               // [mix_cap][9] FP64 variance partials (split forms)
+  double* Px64 = nullptr;               // [mix_cap][17] the same in FP64 (split forms)
 
   // ---- sliced pair layout (capacity slot_cap) ----
   int n_slices = 0;
