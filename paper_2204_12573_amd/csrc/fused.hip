@@ -521,14 +521,16 @@ __device__ __forceinline__ TileModel tile_model(const FusedArgs& a, int row0) {
 }
 
 // Per-row scalars of the tile (LDS): |d~| (FP32), |d~|^2 in FP64 (split forms), the FP8 row
-// scale, the row's atom (-1: padding) and 1/|d~|^2, set by the descriptor phase so that the
-// later phases read them from LDS instead of global memory.
+// scale, the row's atom (-1: padding), 1/|d~|^2 and the scale of the tile's d~ (1, or 2^80
+// for rows just inside the cutoff), set by the descriptor phase so that the later phases read
+// them from LDS instead of global memory.
 struct RowScalars {
   float* nrm;
   double* nrm2;
   float* rsc;
   int* atom;
   float* inv2;
+  float* scale2;
 };
 
 // 1. descriptors of the tile's rows into the LDS tile (thread t of 256: row t/2, half t&1);
@@ -551,6 +553,7 @@ __device__ __forceinline__ void desc_phase(const FusedArgs& a, float* As, const 
   typedef typename std::conditional<PREC == FLARE_FP32, float, double>::type NormT;
   NormT nrm2 = 0;
   float amax = 0.f;     // max |d~_k| (FP8 row scale)
+  float scale = 1.f;    // of the densities behind the tile's d~
   if (GIVEN) {
     // lane h copies components 72 h .. 72 h + 71 of its row (zeros for padding rows)
     const float4* src = reinterpret_cast<const float4*>(a.D_in + (size_t)(row0 + rl) * ND1 + 72 * h);
@@ -563,22 +566,44 @@ __device__ __forceinline__ void desc_phase(const FusedArgs& a, float* As, const 
       *reinterpret_cast<float4*>(dst + 4 * q) = v;
     }
   } else {
+    // Densities of a row whose only neighbours are just inside the cutoff go down to 1e-14
+    // (f_c = (r_c - r)^2), and |d~|^2 is of their fourth power: such rows are formed again
+    // from densities scaled by 2^40 (exact), so that no product of d~ under- or overflows;
+    // everything but g = de/dd~ and |d~| is independent of the scale.
+    const float c00 = xor1(c[0][0]);
+    const bool any = (h ? c00 : c[0][0]) > 0.f;      // some neighbour inside the cutoff
     float* rowp = As + rl * AS + 2 * h;
-    int k = 0;
+    for (;;) {
+      nrm2 = 0;
+      amax = 0.f;
+      int k = 0;
 #pragma unroll
-    for (int na = 0; na < NR; ++na) {
+      for (int na = 0; na < NR; ++na) {
 #pragma unroll
-      for (int nb = na; nb < NR; ++nb) {
-        const float2 mine = b2_half(c[na], c[nb], h);    // this lane's two components
-        nrm2 += (NormT)(mine.x * mine.x + mine.y * mine.y);
-        if (PREC == FLARE_FP8_SPLIT) amax = fmaxf(amax, fmaxf(fabsf(mine.x), fabsf(mine.y)));
-        *reinterpret_cast<float2*>(rowp + 4 * k) = mine;
-        ++k;
+        for (int nb = na; nb < NR; ++nb) {
+          const float2 mine = b2_half(c[na], c[nb], h);    // this lane's two components
+          nrm2 += (NormT)(mine.x * mine.x + mine.y * mine.y);
+          if (PREC == FLARE_FP8_SPLIT) amax = fmaxf(amax, fmaxf(fabsf(mine.x), fabsf(mine.y)));
+          *reinterpret_cast<float2*>(rowp + 4 * k) = mine;
+          ++k;
+        }
       }
+      if (PREC == FLARE_FP32) nrm2 += xor1((float)nrm2);    // the row's other half
+      else nrm2 += xor1d((double)nrm2);
+      if (scale != 1.f || !any || !(nrm2 < (NormT)0x1p-60)) break;
+      scale = 0x1p40f;
+#pragma unroll
+      for (int n = 0; n < NR; ++n)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) c[n][q] *= 0x1p40f;
+    }
+    if (scale != 1.f) {
+#pragma unroll
+      for (int n = 0; n < NR; ++n)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) c[n][q] *= 0x1p-40f;
     }
   }
-  if (PREC == FLARE_FP32) nrm2 += xor1((float)nrm2);    // the row's other half
-  else nrm2 += xor1d((double)nrm2);
   if (GIVEN) nrm2 = i >= 0 ? 1 : 0;     // given vectors: no normalisation
   const float nrm = (float)sqrt(nrm2);   // sqrtf in the FP32 form
   if (PREC == FLARE_FP8_SPLIT) {
@@ -591,8 +616,9 @@ __device__ __forceinline__ void desc_phase(const FusedArgs& a, float* As, const 
     rs.nrm[rl] = nrm;
     rs.atom[rl] = i;
     rs.inv2[rl] = nrm > 0.f ? 1.f / (nrm * nrm) : 0.f;
+    rs.scale2[rl] = scale * scale;
     if (PREC != FLARE_FP32) rs.nrm2[rl] = (double)nrm2;
-    if (i >= 0) a.nrm[i] = nrm;
+    if (i >= 0) a.nrm[i] = nrm / (scale * scale);
   }
 }
 
@@ -678,7 +704,7 @@ __device__ __forceinline__ void forms_phase(const FusedArgs& a, float* As, const
         const int rl = wave * 32 + i * 16 + 4 * grp + r;
         const float inv2 = rs.inv2[rl];
         const float e = dots[i][r] * inv2;
-        const float s2 = 2.f * inv2;
+        const float s2 = 2.f * inv2 * rs.scale2[rl];
         dots[i][r] = e;
         float* p = As + rl * AS + l16;
 #pragma unroll
@@ -718,7 +744,8 @@ __global__ __launch_bounds__(FT, 2) void k_fused144(FusedArgs a) {
   __shared__ float rsc_s[FR];     // FP8 split form: power-of-two row scale s_r
   __shared__ int atom_s[FR];
   __shared__ float inv2_s[FR];
-  const RowScalars rs{nrm_s, nrm2_s, rsc_s, atom_s, inv2_s};
+  __shared__ float scale2_s[FR];
+  const RowScalars rs{nrm_s, nrm2_s, rsc_s, atom_s, inv2_s, scale2_s};
   const int tile = xcd_remap(blockIdx.x, gridDim.x);
   const int row0 = tile * FR;
   const int t = threadIdx.x;
@@ -776,11 +803,12 @@ __global__ __launch_bounds__(WW * 64, 1) void k_fused144_w(FusedArgs a, int nsub
   __shared__ float rsc_s[WW][WR];
   __shared__ int atom_s[WW][WR];
   __shared__ float inv2_s[WW][WR];
+  __shared__ float scale2_s[WW][WR];
   // the wave index is uniform over the wave: scalar, and with it the sub-tile loop and rows
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int nw = gridDim.x * WW;
   float* A = As[wv];
-  const RowScalars rs{nrm_s[wv], nrm2_s[wv], rsc_s[wv], atom_s[wv], inv2_s[wv]};
+  const RowScalars rs{nrm_s[wv], nrm2_s[wv], rsc_s[wv], atom_s[wv], inv2_s[wv], scale2_s[wv]};
   for (int st = blockIdx.x * WW + wv; st < nsub; st += nw) {
     const int row0 = st * WR;
     float c[NR][NQ];
