@@ -33,8 +33,8 @@ __global__ __launch_bounds__(TA) void k_adjoint144(SlotView v, const int* __rest
   adjoint_pairs_half(v, R, h, c, f_own);
 }
 
-// Mixed rows, 16 lanes per row (mixed.h): lane a = s*8 + n forms its density channel,
-// then its adjoint channel u_{a,lm} = sum_b G^_{ab,l} c_{b,lm} over the 16 channels of
+// Mixed rows, 16 lanes per row (mixed.h): with the densities that the descriptor kernel left in
+// Cx, lane a = s*8 + n forms its adjoint channel u_{a,lm} = sum_b G^_{ab,l} c_{b,lm} over the 16 channels of
 // the row (G^ from the row's 544 gradient components: (H,H) and (Pt,Pt) blocks doubled on
 // the diagonal, the (H,Pt) block shared by both orders), and the row's slots are split
 // over the lanes (k = L, L + 16, ...), each pair reading u of its neighbour species from LDS.
@@ -44,6 +44,7 @@ __global__ __launch_bounds__(TA) void k_adjoint144(SlotView v, const int* __rest
 // 16 us of 39 for 13 k rows); with it the row's e and, given the column pairs' shares P, V.
 constexpr int GSTRIDE = ND + 4;
 struct MixedForms {
+  const float* C;        // densities [rows][MSTRIDE]
   const float* D;
   const float* Y;
   const float* P;        // V shares [rows][17] in FP32, or null
@@ -91,13 +92,11 @@ __global__ __launch_bounds__(MTHREADS) void k_adjoint_mixed(SlotView v, int rows
       }
     }
   }
-  float c[NLM];
-#pragma unroll
-  for (int lm = 0; lm < NLM; ++lm) c[lm] = 0.f;
-  if (i >= 0) mixed_channel_density(v, R, L, c);
   float* crow = cs + rl * MSTRIDE;
-#pragma unroll
-  for (int lm = 0; lm < NLM; ++lm) crow[cidx(L, lm)] = c[lm];
+  {
+    const float4* from = reinterpret_cast<const float4*>(q.C + (size_t)blockIdx.x * MROWS * MSTRIDE);
+    for (int k = threadIdx.x; k < MROWS * MSTRIDE / 4; k += MTHREADS) reinterpret_cast<float4*>(cs)[k] = from[k];
+  }
   __syncthreads();
   float u[NLM];
 #pragma unroll
@@ -169,7 +168,7 @@ void adjoint_mixed_chunk(flare_state* s, int r0, int nr, bool want_v) {
   const SlotView v = slot_view(s);
   StageTimer tm(s, FLARE_T_FORCEX);
   const bool v64 = s->model->var64;
-  MixedForms q{s->Dx, s->Yx, want_v && !v64 ? s->Px : nullptr, want_v && v64 ? s->Px64 : nullptr, s->nrm, s->e_int, s->v_int, s->e_row + s->rows1,
+  MixedForms q{s->Cx, s->Dx, s->Yx, want_v && !v64 ? s->Px : nullptr, want_v && v64 ? s->Px64 : nullptr, s->nrm, s->e_int, s->v_int, s->e_row + s->rows1,
                s->v_row + s->rows1};
   if (nr > 0)
     k_adjoint_mixed<<<nr / MROWS, MTHREADS, 0, s->stream>>>(v, s->rows1, r0, s->atom_of_rowx, q, s->f_own);

@@ -239,7 +239,8 @@ static void state_arrays(flare_state* s, F&& f) {
   f((void**)&s->Dx, X * ND * 4);
   f((void**)&s->Yx, X * ND * 4);
   f((void**)&s->Px, X * 17 * 4);
-  f((void**)&s->D6x, X * ND * 6);
+  f((void**)&s->Cx, X * 272 * 4);
+  f((void**)&s->D6x, std::min(X, (size_t)FEW_ROWS) * ND * 6);
   f((void**)&s->Px64, X * 17 * 8);
   f((void**)&s->slice_len, (SL + 1) * 4);
   f((void**)&s->slice_base, (SL + 1) * 4);

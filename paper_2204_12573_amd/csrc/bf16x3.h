@@ -48,11 +48,10 @@ __device__ __forceinline__ void split8x3(const float4 (&u)[2], bf8& x0, bf8& x1,
   x2 = __builtin_bit_cast(bf8, p2);
 }
 
-// ---- the 544-wide rows in fragment order ----
+// ---- few 544-wide rows in fragment order ----
 // D6: [16-row block][K step 17][part 3][lane 64] x 8 bf16, lane l holding row l % 16 and
 // k = 32 step + 8 (l / 16) .. + 7: the A operand of one MFMA is one contiguous 1 KB load.
 constexpr int XKS = ND / 32;                 // 17 K steps
-constexpr int D6_ROW = ND * 3 / 8;           // uint4 per row (averaged over a block): 204
 
 // components 4 P .. 4 P + 3 of row `row`, split, to their places in D6
 __device__ __forceinline__ void store_d6(uint4* __restrict__ D6, int row, int P, const float4& o) {

@@ -3,16 +3,19 @@
 //   Y = D beta_s (FP32-accurate products in three BF16 parts, see bf16x3.h), e_i = Y_i . D_i,
 //   V_i = D_i . Sigma_s D_i, or |L_s^T D_i|^2 with the Cholesky factor of Sigma_s,
 //   g_i = (2/|d~_i|) (Y_i - e_i d_i)  (de_i/dd~_i, formed from Y and D by the adjoint kernel).
-// The rows come in fragment order (D6), already split by the kernel that forms them, and
-// so do the model matrices: [K step 17][column block 34][part 3][lane 64] x 8 bf16. Columns
+// The model matrices come split and in fragment order: [K step 17][column block 34][part 3]
+// [lane 64] x 8 bf16; the rows are FP32 and split in registers, beside the products (rows
+// written split cost 53 MB of writes and half as much again to read for 16 k rows). Columns
 // go in pairs of 16-wide blocks: pair m is columns 32 m .. 32 m + 31, and of a lower-
 // triangular factor only the K steps >= m of it are non-zero. Two kernels share the work:
 //   k_forms544      many rows: a work-group of four waves takes 128 rows x 4 or 5 column
 //                   pairs, 32 rows a wave; the matrix fragments of a K step are shared
 //                   through LDS (copied there by the loads themselves, two buffers), the
-//                   row fragments go to registers one K step ahead
+//                   rows' values go to registers one K step ahead
 //   k_forms544_few  few rows: a wave takes one 16-row block x one column pair on its own,
-//                   three K steps of fragments in flight, no LDS and no barrier
+//                   three K steps of fragments in flight, no LDS and no barrier; the rows come
+//                   already split and in fragment order from the kernel that forms them
+//                   (split here they took 14 us in place of 10 for 1 k rows)
 // Both form every product, partial sum and row in the same order, so a row's results do
 // not depend on which of them ran.
 #include <algorithm>
@@ -29,14 +32,10 @@ constexpr int XNB = ND / 16;                 // 34 column blocks
 constexpr int XNP = ND / 32;                 // 17 column pairs
 constexpr int XTILES = 4;                    // column tiles of the many-row kernel
 constexpr int XTP = 5;                       // pairs of its widest tile
-// Up to FEW_ROWS one wave per 16 rows and column pair: each reads 9 KB a K step through L2 for
-// 12 products, so its time grows with the rows once the 1,024 SIMDs are filled. Energies and
-// variances in us, few-row against many-row kernel: 27 : 32 for 2,176 rows, 36 : 32 for 3,072.
-constexpr int FEW_ROWS = 2560;
 
 struct XArgs {
-  const uint4* D6;       // rows in fragment order
-  const float* D;        // the same rows in FP32, [rows][544] (V from the full Sigma)
+  const float* D;        // rows, [rows][544]
+  const uint4* D6;       // few rows: the same split, in fragment order
   const int* aor;        // atom of row (-1: padding), or null: rows 0 .. n_given - 1 are given
   int n_given;
   int rows;              // padded rows (a multiple of 128)
@@ -138,7 +137,7 @@ typedef __attribute__((address_space(1))) const void gvoid;
 typedef __attribute__((address_space(3))) void lvoid;
 
 // 128 rows x up to five column pairs. Per K step a wave forms 2 x 10 blocks x 6 products
-// (1,920 cycles of its SIMD's matrix core) from 6 KB of row fragments of its own and 30 KB
+// (1,920 cycles of its SIMD's matrix core) from 4 KB of rows of its own and 30 KB
 // of matrix fragments in LDS; two work-groups a CU. Energies and variances of 13,440 rows:
 // 70 us, 47 % of the SIMD cycles matrix work (the work-groups' unequal lengths leave 1.5 of 2
 // waves on a SIMD on average), against 140 us on FP32 matrix instructions.
@@ -171,7 +170,7 @@ __global__ __launch_bounds__(NTQ, 2) void k_forms544(XArgs q) {
   const int ks0 = tri ? m0 : 0;
   const int wrow = row0 + wave * 32;
   const bool idle = block_empty(q, wrow);           // padding rows only: copies, no products
-  const uint4* __restrict__ A = q.D6 + (size_t)(wrow >> 4) * XKS * 3 * 64 + lane;
+  const float* __restrict__ A = q.D + (size_t)(wrow + (lane & 15)) * ND + 8 * (lane >> 4);
   f4 acc[2][XTP][2];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -185,12 +184,13 @@ __global__ __launch_bounds__(NTQ, 2) void k_forms544(XArgs q) {
     for (int f = wave; f < np * 6; f += 4)
       __builtin_amdgcn_global_load_lds((gvoid*)(src + f * 64), (lvoid*)(&Bs[buf][f * 64]), 16, 0, 0);
   };
-  bf8 a[2][3], an[2][3];
-  auto load_a = [&](int ks, bf8 (&x)[2][3]) {
+  float4 av[2][2];
+  bf8 a[2][3];
+  auto load_a = [&](int ks) {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int t = 0; t < 3; ++t) x[i][t] = __builtin_bit_cast(bf8, A[((size_t)(i * XKS + ks) * 3 + t) * 64]);
+      for (int t = 0; t < 2; ++t) av[i][t] = *reinterpret_cast<const float4*>(A + (size_t)i * 16 * ND + ks * 32 + 4 * t);
   };
   // all waves' copies of the next K step have landed before any wave reads them (the copies
   // count as vector memory operations, which a barrier alone does not wait for)
@@ -199,13 +199,15 @@ __global__ __launch_bounds__(NTQ, 2) void k_forms544(XArgs q) {
     __syncthreads();
   };
   copy_b(ks0, ks0 & 1);
-  load_a(ks0, a);
+  load_a(ks0);
   copies_done();
   for (int ks = ks0; ks < XKS; ++ks) {
     const int buf = ks & 1;
     const int kn = min(ks + 1, XKS - 1);
     if (ks + 1 < XKS) copy_b(kn, buf ^ 1);
-    load_a(kn, an);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) split8x3(av[i], a[i][0], a[i][1], a[i][2]);
+    load_a(kn);
     if (!idle) {
       // the next pair's fragments are read from LDS while this pair's products run
       bf8 bA[2][3], bB[2][3];
@@ -237,10 +239,6 @@ __global__ __launch_bounds__(NTQ, 2) void k_forms544(XArgs q) {
       }
     }
     copies_done();
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int t = 0; t < 3; ++t) a[i][t] = an[i][t];
   }
   if (idle) return;
 #pragma unroll
@@ -441,8 +439,8 @@ void forms_mixed_chunk(flare_state* s, int r0, int nr, bool want_e, bool want_v,
     if (!want_e) return;
   }
   XArgs q{};
-  q.D6 = s->D6x;
   q.D = s->Dx;
+  q.D6 = s->D6x;
   q.aor = aor;
   q.rows = nr;
   q.split_row = split;
@@ -474,13 +472,14 @@ int forms_given_544(flare_state* s, int bucket, int n, const float* d, float* e,
     if (err == hipSuccess && rows > nc)
       err = hipMemsetAsync(s->Dx + (size_t)nc * ND, 0, (size_t)(rows - nc) * ND * sizeof(float), s->stream);
     if (err != hipSuccess) return (int)err;
-    k_split544<<<(rows * (ND / 4) + NTQ - 1) / NTQ, NTQ, 0, s->stream>>>(rows, s->Dx, s->D6x);
+    if (rows <= FEW_ROWS)
+      k_split544<<<(rows * (ND / 4) + NTQ - 1) / NTQ, NTQ, 0, s->stream>>>(rows, s->Dx, s->D6x);
     // every row of the chunk has the model of `bucket`: the Pt-centre factor from row 0 for
     // bucket 5, the H-centre one throughout for bucket 4
     const int split = bucket == 5 ? 0 : rows;
     XArgs q{};
+      q.D = s->Dx;
     q.D6 = s->D6x;
-    q.D = s->Dx;
     q.n_given = nc;
     q.rows = rows;
     q.split_row = split;

@@ -6,6 +6,12 @@
 
 namespace flare {
 
+// Mixed rows of one call up to which their forms take the kernel for few rows (one wave per 16
+// rows and column pair): each wave reads 9 KB a K step through L2 for 12 products, so its time
+// grows with the rows once the 1,024 SIMDs are filled. Energies and variances in us, few-row
+// against many-row kernel: 27 : 32 for 2,176 rows, 36 : 32 for 3,072.
+constexpr int FEW_ROWS = 2560;
+
 // Small device array that grows at list builds (never on the per-step path).
 template <class T>
 struct DevBuf {
@@ -213,7 +219,8 @@ struct flare_state {
   float* Dx = nullptr;                  // [mix_cap][544] descriptors
   float* Yx = nullptr;                  // D beta
   float* Px = nullptr;                  // [mix_cap][17] variance partials of the column pairs
-  uint4* D6x = nullptr;                 // the descriptors in three BF16 parts, fragment order (bf16x3.h)
+  uint4* D6x = nullptr;                 // up to FEW_ROWS rows: the descriptors in three BF16 parts (bf16x3.h)
+  float* Cx = nullptr;                  // [mix_cap][272] densities (mixed.h)
   double* Px64 = nullptr;               // [mix_cap][17] the same in FP64 (split forms)
 
   // ---- sliced pair layout (capacity slot_cap) ----
@@ -285,7 +292,7 @@ void pair_geometry(flare_state* s);
 constexpr int FORMS_DESCRIPTORS = 8;
 void fused_quadratic_forms(flare_state* s, int mode, float* d_out);
 // mixed rows [r0, r0 + nr) of the 544-wide class (nr <= mix_cap, r0 a multiple of mix_cap),
-// in the chunk workspace Dx/D6x/Yx/Px: descriptors (and their export to caller order),
+// in the chunk workspace Dx/Cx/Yx/Px: descriptors (and their export to caller order),
 // quadratic forms, adjoint terms
 void desc_mixed_chunk(flare_state* s, int r0, int nr, float* d_out);
 void forms_mixed_chunk(flare_state* s, int r0, int nr, bool want_e, bool want_v, bool finish);
