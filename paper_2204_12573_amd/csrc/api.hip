@@ -762,8 +762,7 @@ int flare_energy_forces(flare_state* s, float* e_atom, float* fx, float* fy, flo
   }
   {
     StageTimer tm(s, FLARE_T_OUT);
-    finalize_outputs(s, e_atom, fx, fy, fz, var_atom, sigma_atom);
-    reduce_cells(s, e_struct, nullptr);
+    finalize_outputs(s, {e_atom, fx, fy, fz, var_atom, sigma_atom}, {e_struct});
   }
   if (want_v) s->v_gen = s->pos_gen;
   CHK(hipGetLastError());
@@ -787,7 +786,7 @@ int flare_forces(flare_state* s, const double* cell_scale, float* fx, float* fy,
   }
   {
     StageTimer tm(s, FLARE_T_OUT);
-    finalize_outputs(s, nullptr, fx, fy, fz, nullptr, nullptr, cell_scale);
+    finalize_outputs(s, {nullptr, fx, fy, fz}, {}, cell_scale);
   }
   CHK(hipGetLastError());
   return FLARE_OK;
@@ -824,8 +823,7 @@ int flare_variance(flare_state* s, float* var_atom, float* sigma_atom, float* si
   }
   {
     StageTimer tm(s, FLARE_T_OUT);
-    finalize_outputs(s, nullptr, nullptr, nullptr, nullptr, var_atom, sigma_atom);
-    reduce_cells(s, nullptr, sigma_max);
+    finalize_outputs(s, {nullptr, nullptr, nullptr, nullptr, var_atom, sigma_atom}, {nullptr, sigma_max});
   }
   CHK(hipGetLastError());
   return FLARE_OK;
@@ -868,7 +866,7 @@ int flare_uncertainty_monitor(flare_state* s, double threshold, float* sigma_max
   }
   {
     StageTimer tm(s, FLARE_T_OUT);
-    reduce_cells(s, nullptr, nullptr, (float)threshold, sigma_max_run, over_count);
+    reduce_cells(s, {nullptr, nullptr, (float)threshold, sigma_max_run, over_count});
   }
   CHK(hipGetLastError());
   return FLARE_OK;
@@ -950,8 +948,7 @@ int flare_md_step(flare_state* s, double* x, double* y, double* z, double* vx, d
   }
   {
     StageTimer tm(s, FLARE_T_OUT);
-    outputs_second_half(s, e_atom, fx, fy, fz, var_atom, sigma_atom, vx, vy, vz, species, im0, im1, dt);
-    reduce_cells(s, e_struct, nullptr);
+    outputs_second_half(s, {e_atom, fx, fy, fz, var_atom, sigma_atom}, {e_struct}, vx, vy, vz, species, im0, im1, dt);
   }
   if (want_v) s->v_gen = s->pos_gen;
   CHK(hipGetLastError());

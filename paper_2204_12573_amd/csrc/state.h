@@ -304,11 +304,23 @@ void forms_given_144(flare_state* s, int bucket, int n, const float* d, float* e
 int forms_given_544(flare_state* s, int bucket, int n, const float* d, float* e, float* v);
 // adjoint terms of the 144-wide rows from G1 (separate from the energies)
 void adjoint_rows144(flare_state* s);
-void finalize_outputs(flare_state* s, float* e_atom, float* fx, float* fy, float* fz,
-                      float* var_atom, float* sigma_atom, const double* cell_scale = nullptr);
-// per-cell E and max sigma; with run_max, the uncertainty monitor (threshold thr, counts in over)
-void reduce_cells(flare_state* s, double* e_struct, float* sigma_max, float thr = 0.f, float* run_max = nullptr,
-                  int* over = nullptr);
+// caller-order outputs (null: not written) and per-cell results: E and max sigma; with
+// run_max, the uncertainty monitor (threshold thr, counts in over)
+struct Outputs {
+  float* e_atom = nullptr;
+  float *fx = nullptr, *fy = nullptr, *fz = nullptr;
+  float* var_atom = nullptr;
+  float* sigma_atom = nullptr;
+};
+struct Reduction {
+  double* e_struct = nullptr;
+  float* sigma_max = nullptr;
+  float thr = 0.f;
+  float* run_max = nullptr;
+  int* over = nullptr;
+};
+void finalize_outputs(flare_state* s, const Outputs& out, const Reduction& red, const double* cell_scale = nullptr);
+void reduce_cells(flare_state* s, const Reduction& red);
 // per-cell virial; red_w: [tasks][9] FP64 task sums (scratch)
 void virial_cells(flare_state* s, double* virial_struct, double* red_w);
 void md_first(flare_state* s, double* x, double* y, double* z, double* vx, double* vy,
@@ -319,9 +331,8 @@ void md_first(flare_state* s, double* x, double* y, double* z, double* vx, doubl
 void md_first_drift(flare_state* s, double* x, double* y, double* z, double* vx, double* vy, double* vz,
                     const float* fx, const float* fy, const float* fz, const int32_t* species, double inv_m0,
                     double inv_m1, double dt, bool displacements);
-void outputs_second_half(flare_state* s, float* e_atom, float* fx, float* fy, float* fz, float* var_atom,
-                         float* sigma_atom, double* vx, double* vy, double* vz, const int32_t* species,
-                         double inv_m0, double inv_m1, double dt);
+void outputs_second_half(flare_state* s, const Outputs& out, const Reduction& red, double* vx, double* vy, double* vz,
+                         const int32_t* species, double inv_m0, double inv_m1, double dt);
 void md_second(flare_state* s, double* vx, double* vy, double* vz, const float* fx,
                const float* fy, const float* fz, const int32_t* species, double inv_m0,
                double inv_m1, double dt);
