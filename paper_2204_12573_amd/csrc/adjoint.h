@@ -20,18 +20,42 @@ namespace flare {
 // sum_lm A_lm grad P_lm(x, y, z)
 __device__ __forceinline__ void poly_grad_dot(const float* A, float x, float y, float z,
                                               float& gx, float& gy, float& gz) {
+#pragma clang fp contract(off)
   const float xx = x * x, yy = y * y, zz = z * z;
-  gx = kY1 * A[3] + kY2a * (y * A[4] + z * A[7]) + kY20 * (-2.f * x) * A[6] + 2.f * kY22 * x * A[8] +
-       6.f * kY33 * x * y * A[9] + kY32a * y * z * A[10] - 2.f * kY31 * x * y * A[11] -
-       6.f * kY30 * x * z * A[12] + kY31 * (4.f * zz - 3.f * xx - yy) * A[13] +
-       2.f * kY32b * x * z * A[14] + 3.f * kY33 * (xx - yy) * A[15];
-  gy = kY1 * A[1] + kY2a * (x * A[4] + z * A[5]) + kY20 * (-2.f * y) * A[6] - 2.f * kY22 * y * A[8] +
-       3.f * kY33 * (xx - yy) * A[9] + kY32a * x * z * A[10] + kY31 * (4.f * zz - xx - 3.f * yy) * A[11] -
-       6.f * kY30 * y * z * A[12] - 2.f * kY31 * x * y * A[13] - 2.f * kY32b * y * z * A[14] -
-       6.f * kY33 * x * y * A[15];
-  gz = kY1 * A[2] + kY2a * (y * A[5] + x * A[7]) + 4.f * kY20 * z * A[6] + kY32a * x * y * A[10] +
-       8.f * kY31 * y * z * A[11] + kY30 * (6.f * zz - 3.f * xx - 3.f * yy) * A[12] +
-       8.f * kY31 * x * z * A[13] + kY32b * (xx - yy) * A[14];
+  const float xy = x * y, xz = x * z, yz = y * z, dxy = xx - yy, z4 = 4.f * zz;
+  gx = kY1 * A[3];
+  gx = fmaf(kY2a * y, A[4], gx);
+  gx = fmaf(kY2a * z, A[7], gx);
+  gx = fmaf(-2.f * kY20 * x, A[6], gx);
+  gx = fmaf(2.f * kY22 * x, A[8], gx);
+  gx = fmaf(6.f * kY33 * xy, A[9], gx);
+  gx = fmaf(kY32a * yz, A[10], gx);
+  gx = fmaf(-2.f * kY31 * xy, A[11], gx);
+  gx = fmaf(-6.f * kY30 * xz, A[12], gx);
+  gx = fmaf(kY31 * (fmaf(-3.f, xx, z4) - yy), A[13], gx);
+  gx = fmaf(2.f * kY32b * xz, A[14], gx);
+  gx = fmaf(3.f * kY33 * dxy, A[15], gx);
+  gy = kY1 * A[1];
+  gy = fmaf(kY2a * x, A[4], gy);
+  gy = fmaf(kY2a * z, A[5], gy);
+  gy = fmaf(-2.f * kY20 * y, A[6], gy);
+  gy = fmaf(-2.f * kY22 * y, A[8], gy);
+  gy = fmaf(3.f * kY33 * dxy, A[9], gy);
+  gy = fmaf(kY32a * xz, A[10], gy);
+  gy = fmaf(kY31 * (fmaf(-3.f, yy, z4) - xx), A[11], gy);
+  gy = fmaf(-6.f * kY30 * yz, A[12], gy);
+  gy = fmaf(-2.f * kY31 * xy, A[13], gy);
+  gy = fmaf(-2.f * kY32b * yz, A[14], gy);
+  gy = fmaf(-6.f * kY33 * xy, A[15], gy);
+  gz = kY1 * A[2];
+  gz = fmaf(kY2a * y, A[5], gz);
+  gz = fmaf(kY2a * x, A[7], gz);
+  gz = fmaf(4.f * kY20 * z, A[6], gz);
+  gz = fmaf(kY32a * xy, A[10], gz);
+  gz = fmaf(8.f * kY31 * yz, A[11], gz);
+  gz = fmaf(kY30 * fmaf(-3.f, xx + yy, 6.f * zz), A[12], gz);
+  gz = fmaf(8.f * kY31 * xz, A[13], gz);
+  gz = fmaf(kY32b * dxy, A[14], gz);
 }
 
 // w = de_i/dDelta for one pair from the adjoint densities u[n][lm] of the neighbour's
@@ -41,6 +65,7 @@ __device__ __forceinline__ void poly_grad_dot(const float* A, float x, float y, 
 template <class U>
 __device__ __forceinline__ void pair_force(const PairGeom& pg, float rc, U u, float& wx, float& wy,
                                            float& wz) {
+#pragma clang fp contract(off)
   float R[NR], dR[NR], Y[NLM];
   radial_d(pg.r, rc, R, dR);
   sph_harm(pg.ux, pg.uy, pg.uz, Y);
@@ -55,8 +80,8 @@ __device__ __forceinline__ void pair_force(const PairGeom& pg, float rc, U u, fl
 #pragma unroll
     for (int lm = 0; lm < NLM; ++lm) {
       const float un = u(n, lm);
-      A[lm] += un * R[n];
-      B[lm] += un * dR[n];
+      A[lm] = fmaf(un, R[n], A[lm]);
+      B[lm] = fmaf(un, dR[n], B[lm]);
     }
   const float inv_r = __builtin_amdgcn_rcpf(pg.r);   // 1 ulp; r >= the shortest pair distance
   const float il[LMAX + 1] = {0.f, inv_r, 2.f * inv_r, 3.f * inv_r};
@@ -65,9 +90,9 @@ __device__ __forceinline__ void pair_force(const PairGeom& pg, float rc, U u, fl
   for (int lm = 0; lm < NLM; ++lm) s1 = fmaf(Y[lm], fmaf(-il[lm_l(lm)], A[lm], B[lm]), s1);
   float gx, gy, gz;
   poly_grad_dot(A, pg.ux, pg.uy, pg.uz, gx, gy, gz);
-  wx = pg.ux * s1 + gx * inv_r;
-  wy = pg.uy * s1 + gy * inv_r;
-  wz = pg.uz * s1 + gz * inv_r;
+  wx = fmaf(pg.ux, s1, gx * inv_r);
+  wy = fmaf(pg.uy, s1, gy * inv_r);
+  wz = fmaf(pg.uz, s1, gz * inv_r);
 }
 
 __device__ __forceinline__ int pair_index_same(int na, int nb) {
@@ -105,7 +130,7 @@ __device__ __forceinline__ void u_transform_half(const float* g, int gstride, in
       for (int n = 0; n < NR; ++n) {
         float acc = 0.f;
 #pragma unroll
-        for (int m = 0; m < NR; ++m) acc += gh[n][m] * col[m];
+        for (int m = 0; m < NR; ++m) acc = fmaf(gh[n][m], col[m], acc);
         c[n][q] = acc;
       }
     }
@@ -167,6 +192,67 @@ __device__ __forceinline__ void adjoint_pairs_half(const SlotView& v, int R, int
       term(k0 + 4, gb[0], rb[0]);
       term(k0 + 6, gb[1], rb[1]);
     }
+  }
+  sx += xor1(sx);
+  sy += xor1(sy);
+  sz += xor1(sz);
+  if (h == 0) f_own[R] = make_float4(sx, sy, sz, 0.f);
+}
+
+// The same with the row's slots split over eight lanes of four waves, for few rows: u of the 32
+// rows in LDS (row stride US), each wave w of the work-group takes the slots k = h + 2 w, + 8,
+// ... of its lane's row; the terms also go to LDS, where the first wave then adds the row's own
+// in the order above. len <= ADJ_FEW_SLOTS.
+constexpr int US = NR * NLM + 4;
+constexpr int ADJ_FEW_SLOTS = 48;
+__device__ __forceinline__ void adjoint_pairs_few(const SlotView& v, int R, int rl, int h, int wave,
+                                                  const float* __restrict__ us, float* __restrict__ ws) {
+  const int S = wave_slice(R);
+  const int base = v.slice_base[S];
+  const int len = v.slice_base[S + 1] - base;
+  const size_t s0 = (size_t)base * 32 + (R & 31);
+  const int k0 = h + 2 * wave;
+  float4 g = k0 < len ? v.geom[s0 + (size_t)k0 * 32] : make_float4(0.f, 0.f, 0.f, 0.f);
+  int r = k0 < len ? v.rev[s0 + (size_t)k0 * 32] : 0;
+  float u[NR][NLM];
+  const float4* u4 = reinterpret_cast<const float4*>(us + rl * US);
+#pragma unroll
+  for (int n = 0; n < NR; ++n)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float4 t = u4[n * 4 + q];
+      u[n][4 * q] = t.x;
+      u[n][4 * q + 1] = t.y;
+      u[n][4 * q + 2] = t.z;
+      u[n][4 * q + 3] = t.w;
+    }
+  for (int k = k0; k < len; k += 8) {
+    const float4 gk = g;
+    const int rk = r;
+    const size_t next = s0 + (size_t)min(k + 8, len - 1) * 32;
+    g = v.geom[next];
+    r = v.rev[next];
+    PairGeom pg;
+    int sp;
+    float wx = 0.f, wy = 0.f, wz = 0.f;
+    if (unpack_geom(gk, pg, sp)) pair_force(pg, v.rc, [&](int n, int lm) { return u[n][lm]; }, wx, wy, wz);
+    v.w_in[rk] = make_float4(wx, wy, wz, 0.f);
+    float* w3 = ws + (k * 32 + rl) * 3;
+    w3[0] = wx;
+    w3[1] = wy;
+    w3[2] = wz;
+  }
+}
+__device__ __forceinline__ void adjoint_own_few(const SlotView& v, int R, int rl, int h, const float* __restrict__ ws,
+                                                float4* __restrict__ f_own) {
+  const int S = wave_slice(R);
+  const int len = v.slice_base[S + 1] - v.slice_base[S];
+  float sx = 0.f, sy = 0.f, sz = 0.f;
+  for (int k = h; k < len; k += 2) {
+    const float* w3 = ws + (k * 32 + rl) * 3;
+    sx += w3[0];
+    sy += w3[1];
+    sz += w3[2];
   }
   sx += xor1(sx);
   sy += xor1(sy);

@@ -672,10 +672,11 @@ int flare_neighbors_export(flare_state* s, long long* offsets, int32_t* j_out, i
 // The mixed (544-wide) rows in chunks of mix_cap rows: descriptors (exported to d_out in
 // caller order when given), quadratic forms (energies and gradients when want_e or want_f,
 // variances when want_v), adjoint terms when want_f.
-static void mixed_rows(flare_state* s, float* d_out, bool want_e, bool want_v, bool want_f) {
+// have_desc: the descriptors are in the workspace already (one chunk).
+static void mixed_rows(flare_state* s, bool have_desc, float* d_out, bool want_e, bool want_v, bool want_f) {
   for (int r0 = 0; r0 < s->rowsx; r0 += s->mix_cap) {
     const int nr = std::min(s->mix_cap, s->rowsx - r0);
-    desc_mixed_chunk(s, r0, nr, d_out);
+    if (!have_desc) desc_mixed_chunk(s, r0, nr, d_out);
     forms_mixed_chunk(s, r0, nr, want_e || want_f, want_v, !want_f);
     if (want_f) adjoint_mixed_chunk(s, r0, nr, want_v);
   }
@@ -699,8 +700,8 @@ int flare_descriptors(flare_state* s, const double* x, const double* y, const do
   if (d_out || norm_out) {
     // the single-species rows come from the fused kernel run without quadratic forms
     if (d_out) CHK(hipMemsetAsync(d_out, 0, (size_t)s->n_atoms * ND * sizeof(float), s->stream));
-    fused_quadratic_forms(s, FORMS_DESCRIPTORS, d_out);
-    mixed_rows(s, d_out, false, false, false);
+    const bool both = fused_quadratic_forms(s, FORMS_DESCRIPTORS, d_out);
+    mixed_rows(s, both, d_out, false, false, false);
     export_norms(s, norm_out);
   }
   CHK(hipGetLastError());
@@ -716,26 +717,28 @@ static int evaluate_forms(flare_state* s, bool want_f, bool want_v) {
   // the step's pair geometry and write disjoint rows and disjoint slots of w_in, so the
   // mixed rows' kernels fill the fused kernel's tail. The main stream waits for them
   // before anything that reads their results. With the stage timers on, everything runs
-  // in order on the one stream.
-  const bool beside = want_f && s->rowsx > 0 && !s->timers.on;
+  // in order on the one stream, and few rows in any case: their descriptors are formed beside
+  // the fused kernel's work-groups in one launch, and an event costs more than the rest.
+  const bool beside = want_f && s->rowsx > 0 && !s->timers.on && !few_single_rows(s);
   if (beside) {
     CHK(hipEventRecord(s->ev_fork, s->stream));
     CHK(hipStreamWaitEvent(s->side, s->ev_fork, 0));
   }
+  bool both;
   {
     // with forces, the fused kernel also runs the adjoint of the 144-wide rows in place
     StageTimer tm(s, FLARE_T_QFORM1);
-    fused_quadratic_forms(s, 1 | (want_v ? 2 : 0) | (want_f ? 4 : 0), nullptr);
+    both = fused_quadratic_forms(s, 1 | (want_v ? 2 : 0) | (want_f ? 4 : 0), nullptr);
   }
   if (beside) {
     hipStream_t main = s->stream;
     s->stream = s->side;
-    mixed_rows(s, nullptr, true, want_v, want_f);
+    mixed_rows(s, false, nullptr, true, want_v, want_f);
     s->stream = main;
     CHK(hipEventRecord(s->ev_join, s->side));
     CHK(hipStreamWaitEvent(s->stream, s->ev_join, 0));
   } else {
-    mixed_rows(s, nullptr, true, want_v, want_f);
+    mixed_rows(s, both, nullptr, true, want_v, want_f);
   }
   if (want_f) {
     s->w_gen = s->pos_gen;
@@ -781,7 +784,7 @@ int flare_forces(flare_state* s, const double* cell_scale, float* fx, float* fy,
     // recomputed chunk by chunk
     adjoint_rows144(s);
     if (s->gx_gen == s->pos_gen) adjoint_mixed_chunk(s, 0, s->rowsx, false);
-    else mixed_rows(s, nullptr, true, false, true);
+    else mixed_rows(s, false, nullptr, true, false, true);
     s->w_gen = s->pos_gen;
   }
   {
@@ -814,11 +817,12 @@ int flare_variance(flare_state* s, float* var_atom, float* sigma_atom, float* si
     return FLARE_E_STALE;
   }
   if (s->v_gen != s->pos_gen) {
+    bool both;
     {
       StageTimer tm(s, FLARE_T_QFORM1);
-      fused_quadratic_forms(s, 2, nullptr);
+      both = fused_quadratic_forms(s, 2, nullptr);
     }
-    mixed_rows(s, nullptr, false, true, false);
+    mixed_rows(s, both, nullptr, false, true, false);
     s->v_gen = s->pos_gen;
   }
   {
@@ -857,11 +861,12 @@ int flare_uncertainty_monitor(flare_state* s, double threshold, float* sigma_max
     return FLARE_E_STALE;
   }
   if (s->v_gen != s->pos_gen) {
+    bool both;
     {
       StageTimer tm(s, FLARE_T_QFORM1);
-      fused_quadratic_forms(s, 2, nullptr);
+      both = fused_quadratic_forms(s, 2, nullptr);
     }
-    mixed_rows(s, nullptr, false, true, false);
+    mixed_rows(s, both, nullptr, false, true, false);
     s->v_gen = s->pos_gen;
   }
   {

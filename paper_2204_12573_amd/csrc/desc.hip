@@ -9,82 +9,15 @@
 // (fused.hip).
 // Pair geometry: positions are FP64; Delta = (x_j - x_i) + s*L is formed in FP64 and
 // rounded to FP32 before the basis is evaluated.
-#include "bf16x3.h"
-#include "mixed.h"
-#include "state.h"
+#include "mixed_desc.h"
 
 namespace flare {
 namespace {
 
 
-// One mixed row per 16 lanes (mixed.h): channel densities into LDS, then the 136 B2
-// channel pairs spread over the row's lanes, the norm summed in FP64 across the lanes, and the normalised row written as float4 per pair: into the chunk's
-// workspace D (row - r0, the densities beside it in Cx; few rows also split, in D6) and, when exporting, into d_out at the atom's caller index.
-__global__ __launch_bounds__(MTHREADS) void k_desc_mixed(SlotView v, int rows1, int r0,
-                                                         const int* __restrict__ atom_of_row,
-                                                         const int* __restrict__ perm, float* __restrict__ D,
-                                                         uint4* __restrict__ D6, float* __restrict__ Cx,
-                                                         float* __restrict__ nrm_out, float* __restrict__ d_out) {
-  // the slots' basis values, then the channels
-  __shared__ __attribute__((aligned(16))) float lds[MROWS * 16 * PBS];
-  static_assert(MROWS * MSTRIDE <= MROWS * 16 * PBS, "the channels reuse the basis block");
-  const int rl = threadIdx.x >> 4, L = threadIdx.x & 15;
-  const int local = blockIdx.x * MROWS + rl;
-  const int row = r0 + local;
-  const int i = atom_of_row[row];
-  float c[NLM];
-  mixed_densities(v, rows1 + row, rl, L, lds, c);     // padding rows: empty slots, zeros
-  float* crow = lds + rl * MSTRIDE;
-#pragma unroll
-  for (int lm = 0; lm < NLM; ++lm) crow[cidx(L, lm)] = c[lm];
-  __syncthreads();
-  if (Cx) {
-    float4* to = reinterpret_cast<float4*>(Cx + (size_t)blockIdx.x * MROWS * MSTRIDE);
-    for (int k = threadIdx.x; k < MROWS * MSTRIDE / 4; k += MTHREADS) to[k] = reinterpret_cast<const float4*>(lds)[k];
-  }
-  // lane L takes the channel pairs {L, (L + k) mod 16}, k = 0 .. 7, and of k = 8 the lanes
-  // below 8 (each unordered pair once): its own channel stays in registers
-  constexpr int NQP = 9;
-  float4 d[NQP];
-  double nrm2 = 0.0;
-#pragma unroll
-  for (int k = 0; k < NQP; ++k) {
-    d[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (k < 8 || L < 8) {
-      const float4* y4 = reinterpret_cast<const float4*>(crow + cidx((L + k) & 15, 0));
-      float y[NLM];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const float4 t = y4[u];
-        y[4 * u] = t.x; y[4 * u + 1] = t.y; y[4 * u + 2] = t.z; y[4 * u + 3] = t.w;
-      }
-      float d0 = c[0] * y[0];
-      float d1 = c[1] * y[1] + c[2] * y[2] + c[3] * y[3];
-      float d2 = 0.f, d3 = 0.f;
-#pragma unroll
-      for (int lm = 4; lm < 9; ++lm) d2 += c[lm] * y[lm];
-#pragma unroll
-      for (int lm = 9; lm < 16; ++lm) d3 += c[lm] * y[lm];
-      d[k] = make_float4(d0, d1, d2, d3);
-      nrm2 += (double)(d0 * d0 + d1 * d1) + (double)(d2 * d2 + d3 * d3);
-    }
-  }
-  nrm2 = sum16d(nrm2);                    // the row's 16 lanes form one DPP row
-  const float nrm = (float)sqrt(nrm2);
-  const float scale = nrm > 0.f ? 1.f / nrm : 0.f;
-  float4* out = reinterpret_cast<float4*>(D + (size_t)local * ND);
-  float4* ext = d_out && i >= 0 ? reinterpret_cast<float4*>(d_out + (size_t)perm[i] * ND) : nullptr;
-#pragma unroll
-  for (int k = 0; k < NQP; ++k) {
-    if (k < 8 || L < 8) {
-      const int P = mixed_pair_index(L, (L + k) & 15);
-      const float4 o = make_float4(d[k].x * scale, d[k].y * scale, d[k].z * scale, d[k].w * scale);
-      out[P] = o;
-      if (D6) store_d6(D6, local, P, o);
-      if (ext) ext[P] = o;
-    }
-  }
-  if (L == 0 && i >= 0) nrm_out[i] = nrm;
+__global__ __launch_bounds__(MTHREADS) void k_desc_mixed(MixedDescArgs q) {
+  __shared__ __attribute__((aligned(16))) float lds[MIXED_LDS];
+  desc_mixed_block(q, blockIdx.x, lds);
 }
 
 constexpr int NTG = 256;
@@ -148,13 +81,14 @@ void pair_geometry(flare_state* s) {
                                                              (float)(rc * rc), s->geom);
 }
 
+MixedDescArgs mixed_desc_args(flare_state* s, int r0, int nr, float* d_out) {
+  return MixedDescArgs{slot_view(s), s->rows1, r0, s->atom_of_rowx, s->perm, s->Dx, nr <= FEW_ROWS ? s->D6x : nullptr,
+                       s->Cx, s->nrm, d_out};
+}
+
 void desc_mixed_chunk(flare_state* s, int r0, int nr, float* d_out) {
-  const SlotView v = slot_view(s);
   StageTimer tm(s, FLARE_T_DESCX);
-  if (nr > 0)
-    k_desc_mixed<<<nr / MROWS, MTHREADS, 0, s->stream>>>(v, s->rows1, r0, s->atom_of_rowx, s->perm, s->Dx,
-                                                         nr <= FEW_ROWS ? s->D6x : nullptr, s->Cx, s->nrm,
-                                                         d_out);
+  if (nr > 0) k_desc_mixed<<<nr / MROWS, MTHREADS, 0, s->stream>>>(mixed_desc_args(s, r0, nr, d_out));
 }
 
 void export_norms(flare_state* s, float* norm_out) {

@@ -29,6 +29,7 @@
 
 #include "adjoint.h"
 #include "bf16x3.h"
+#include "mixed_desc.h"
 #include "state.h"
 
 namespace flare {
@@ -175,16 +176,17 @@ __device__ __forceinline__ void load_a8(const float* As, int wave, int l16, int 
 // TRI: W is lower-triangular, so of K step ks (rows 32 ks .. 32 ks + 31) only the column
 // blocks j <= 2 ks + 1 are non-zero: 29 of the 45 blocks, in 11 of the 15 groups. The K
 // steps then run from the last (9 blocks) to the first (2 blocks).
-template <bool TRI>
+// One group of three column blocks alone (G >= 0) takes its five steps in the same order.
+template <bool TRI, int G = -1>
 struct X6Steps {
-  static constexpr int N = TRI ? 11 : 15;
+  static constexpr int N = G >= 0 ? NKS : (TRI ? 11 : 15);
   int ks[N] = {}, jg[N] = {};
   constexpr X6Steps() {
     int n = 0;
     for (int k = 0; k < NKS; ++k)
       for (int g = 0; g < NCB / 3; ++g) {
         const int q = TRI ? NKS - 1 - k : k;
-        if (TRI && 3 * g > 2 * q + 1) continue;
+        if ((TRI && 3 * g > 2 * q + 1) || (G >= 0 && g != G)) continue;
         ks[n] = q;
         jg[n] = g;
         ++n;
@@ -194,10 +196,12 @@ struct X6Steps {
 template <bool TRI>
 constexpr bool x6_live(int ks, int j) { return !TRI || j <= 2 * ks + 1; }
 
-template <bool TRI>
+template <bool TRI, int G = -1>
 __device__ __forceinline__ void mfma_pass_bf16x6(const float* As, const uint4* __restrict__ W, int wave,
                                                  int lane, f4 (&acc)[2][NCB]) {
-  constexpr X6Steps<TRI> st;
+  static_assert(!TRI || G < 0, "groups of full matrices only");
+  typedef X6Steps<TRI, G> Steps;
+  constexpr Steps st;
   const int l16 = lane & 15, grp = lane >> 4;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -211,17 +215,17 @@ __device__ __forceinline__ void mfma_pass_bf16x6(const float* As, const uint4* _
   for (int jj = 0; jj < 3; ++jj)
 #pragma unroll
     for (int pt = 0; pt < 3; ++pt)
-      b[jj][pt] = __builtin_bit_cast(bf8, Wp[((st.ks[0] * NCB + jj) * 3 + pt) * 64]);
+      b[jj][pt] = __builtin_bit_cast(bf8, Wp[((st.ks[0] * NCB + 3 * st.jg[0] + jj) * 3 + pt) * 64]);
 #pragma unroll
   for (int i = 0; i < 2; ++i) load_a8(As, wave, l16, grp, i, st.ks[0], araw[i]);
 #pragma unroll
-  for (int n = 0; n < X6Steps<TRI>::N; ++n) {
+  for (int n = 0; n < Steps::N; ++n) {
     const int ks = st.ks[n], jg = st.jg[n];
     if (n == 0 || st.ks[n] != st.ks[n - 1]) {
 #pragma unroll
       for (int i = 0; i < 2; ++i) split8x3(araw[i], a[0][i], a[1][i], a[2][i]);
     }
-    const bool more = n + 1 < X6Steps<TRI>::N;
+    const bool more = n + 1 < Steps::N;
     const int nks = more ? st.ks[n + 1] : ks, njg = more ? st.jg[n + 1] : jg;
     if (more && nks != ks) {
 #pragma unroll
@@ -378,7 +382,7 @@ __device__ __forceinline__ void row_sumsq(const f4 (&acc)[2][NCB], float (&out)[
 #pragma unroll
         for (int j = 0; j < NCB; ++j) {
           const double z = (double)acc[i][j][r];
-          s += z * z;
+          s = fma(z, z, s);
         }
         out[i][r] = (float)sum16d(s);
       } else {
@@ -402,62 +406,71 @@ __device__ __forceinline__ void row_sumsq(const f4 (&acc)[2][NCB], float (&out)[
 // load while the current one runs.
 typedef double d4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ void var_pass_f64(const float* As, const double* __restrict__ L, int wave, int lane,
-                                             double (&out)[2][4]) {
+// Z of one group jg of three column blocks.
+template <int JG>
+__device__ __forceinline__ void var_group_f64(const float* As, const double* __restrict__ L, int wave, int lane,
+                                              d4 (&acc)[2][3]) {
+  constexpr int jg = JG;
   const int l16 = lane & 15, grp = lane >> 4;
-  double ss[2][4];
+  const double* Lp = L + lane;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) ss[i][r] = 0.0;
-  const double* Lp = L + lane;
+    for (int jj = 0; jj < 3; ++jj) acc[i][jj] = d4{0.0, 0.0, 0.0, 0.0};
+  double bA[3][4], bB[3][4];
 #pragma unroll
-  for (int jg = 0; jg < 3; ++jg) {
-    d4 acc[2][3];
+  for (int jj = 0; jj < 3; ++jj)
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      if (jj == 0) bA[jj][t] = Lp[(((3 * jg + jj) * NKC + 3 * jg) * 4 + t) * 64];
+#pragma unroll
+  for (int kc = 3 * jg; kc < NKC; ++kc) {
+    const bool odd = (kc - 3 * jg) & 1;
+    double (&cur)[3][4] = odd ? bB : bA;
+    double (&nxt)[3][4] = odd ? bA : bB;
+    if (kc + 1 < NKC) {
+#pragma unroll
+      for (int jj = 0; jj < 3; ++jj)
+        if (3 * jg + jj <= kc + 1)
+#pragma unroll
+          for (int t = 0; t < 4; ++t) nxt[jj][t] = Lp[(((3 * jg + jj) * NKC + kc + 1) * 4 + t) * 64];
+    }
+    float4 a[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
+      a[i] = *reinterpret_cast<const float4*>(&As[(wave * 32 + i * 16 + l16) * AS + kc * 16 + 4 * grp]);
+    const float av[2][4] = {{a[0].x, a[0].y, a[0].z, a[0].w}, {a[1].x, a[1].y, a[1].z, a[1].w}};
 #pragma unroll
-      for (int jj = 0; jj < 3; ++jj) acc[i][jj] = d4{0.0, 0.0, 0.0, 0.0};
-    double bA[3][4], bB[3][4];
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int jj = 0; jj < 3; ++jj) {
+        if (3 * jg + jj > kc) continue;     // block above the diagonal of L
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+          acc[i][jj] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)av[i][t], cur[jj][t], acc[i][jj], 0, 0, 0);
+      }
+  }
+}
+// ... and its squares, added to the row sums in the order of the groups.
+__device__ __forceinline__ void var_squares_f64(const d4 (&acc)[2][3], double (&ss)[2][4]) {
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int jj = 0; jj < 3; ++jj)
 #pragma unroll
-      for (int t = 0; t < 4; ++t)
-        if (jj == 0) bA[jj][t] = Lp[(((3 * jg + jj) * NKC + 3 * jg) * 4 + t) * 64];
-#pragma unroll
-    for (int kc = 3 * jg; kc < NKC; ++kc) {
-      const bool odd = (kc - 3 * jg) & 1;
-      double (&cur)[3][4] = odd ? bB : bA;
-      double (&nxt)[3][4] = odd ? bA : bB;
-      if (kc + 1 < NKC) {
-#pragma unroll
-        for (int jj = 0; jj < 3; ++jj)
-          if (3 * jg + jj <= kc + 1)
-#pragma unroll
-            for (int t = 0; t < 4; ++t) nxt[jj][t] = Lp[(((3 * jg + jj) * NKC + kc + 1) * 4 + t) * 64];
-      }
-      float4 a[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-        a[i] = *reinterpret_cast<const float4*>(&As[(wave * 32 + i * 16 + l16) * AS + kc * 16 + 4 * grp]);
-      const float av[2][4] = {{a[0].x, a[0].y, a[0].z, a[0].w}, {a[1].x, a[1].y, a[1].z, a[1].w}};
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int jj = 0; jj < 3; ++jj) {
-          if (3 * jg + jj > kc) continue;     // block above the diagonal of L
-#pragma unroll
-          for (int i = 0; i < 2; ++i)
-            acc[i][jj] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)av[i][t], cur[jj][t], acc[i][jj], 0, 0, 0);
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int jj = 0; jj < 3; ++jj)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) ss[i][r] = fma(acc[i][jj][r], acc[i][jj][r], ss[i][r]);
-  }
+      for (int r = 0; r < 4; ++r) ss[i][r] = fma(acc[i][jj][r], acc[i][jj][r], ss[i][r]);
+}
+
+__device__ __forceinline__ void var_pass_f64(const float* As, const double* __restrict__ L, int wave, int lane,
+                                             double (&out)[2][4]) {
+  double ss[2][4] = {};
+  d4 acc[2][3];
+  var_group_f64<0>(As, L, wave, lane, acc);
+  var_squares_f64(acc, ss);
+  var_group_f64<1>(As, L, wave, lane, acc);
+  var_squares_f64(acc, ss);
+  var_group_f64<2>(As, L, wave, lane, acc);
+  var_squares_f64(acc, ss);
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -479,7 +492,7 @@ __device__ __forceinline__ void block_dots(const float* As, const f4 (&acc)[2][N
   for (int r = 0; r < 4; ++r) {
     float s = 0.f;
 #pragma unroll
-    for (int j = 0; j < NCB; ++j) s += acc[i][j][r] * d[r][j];
+    for (int j = 0; j < NCB; ++j) s = fmaf(acc[i][j][r], d[r][j], s);
     out[r] = sum16(s);
   }
 }
@@ -539,6 +552,7 @@ struct RowScalars {
 template <int PREC, bool GIVEN>
 __device__ __forceinline__ void desc_phase(const FusedArgs& a, float* As, const RowScalars& rs, int row0,
                                            int t, float (&c)[NR][NQ]) {
+#pragma clang fp contract(off)
   const int rl = t >> 1, h = t & 1;
   const int i = atom_of<GIVEN>(a, row0 + rl);
 #pragma unroll
@@ -582,7 +596,7 @@ __device__ __forceinline__ void desc_phase(const FusedArgs& a, float* As, const 
 #pragma unroll
         for (int nb = na; nb < NR; ++nb) {
           const float2 mine = b2_half(c[na], c[nb], h);    // this lane's two components
-          nrm2 += (NormT)(mine.x * mine.x + mine.y * mine.y);
+          nrm2 += (NormT)fmaf(mine.x, mine.x, mine.y * mine.y);
           if (PREC == FLARE_FP8_SPLIT) amax = fmaxf(amax, fmaxf(fabsf(mine.x), fabsf(mine.y)));
           *reinterpret_cast<float2*>(rowp + 4 * k) = mine;
           ++k;
@@ -622,6 +636,70 @@ __device__ __forceinline__ void desc_phase(const FusedArgs& a, float* As, const 
   }
 }
 
+// FP8 form: the pass and its power-of-two scales undone, Y~ = acc / (16 s_r s_b), exact.
+__device__ __forceinline__ void energy_pass_fp8(const float* As, const float* rsc_s, const TileModel& tm, int wave,
+                                                int lane, f4 (&acc)[2][NCB]) {
+  const int grp = lane >> 4;
+  mfma_pass_fp8(As, rsc_s, tm.W8, wave, lane, acc);
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float inv = 1.f / (16.f * rsc_s[wave * 32 + i * 16 + 4 * grp + r] * tm.bsc);
+#pragma unroll
+      for (int j = 0; j < NCB; ++j) acc[i][j][r] *= inv;
+    }
+}
+
+// V of the wave's rows from the FP64 row sums: V = |L^T d~|^2 / |d~|^2 with an FP64 division.
+__device__ __forceinline__ void store_variance_f64(const FusedArgs& a, const RowScalars& rs, int row0, int wave, int lane,
+                                                   const double (&vv)[2][4]) {
+  const int l16 = lane & 15, grp = lane >> 4;
+  const double x = row_value(vv, l16);
+  if (l16 < 8) {
+    const int rl = wave * 32 + (l16 >> 2) * 16 + grp + 4 * (l16 & 3);     // FP64 accumulator layout
+    const int atom = rs.atom[rl];
+    const double n2 = rs.nrm2[rl];
+    if (atom >= 0) {
+      const float v = n2 > 0.0 ? (float)(x / n2) : 0.f;
+      a.v_int[atom] = v;
+      a.v_row[row0 + rl] = v;
+    }
+  }
+}
+
+// V of the wave's rows through the FP32 factor (or the full Sigma).
+template <int PREC>
+__device__ __forceinline__ void variance_fp32(const FusedArgs& a, const float* As, const RowScalars& rs, int row0, int wave,
+                                              int lane, const TileModel& tm) {
+  const int l16 = lane & 15, grp = lane >> 4;
+  f4 acc[2][NCB];
+  float dots[2][4];
+  if (a.vchol) {
+    // Z = D L, L lower-triangular
+    mfma_pass_bf16x6<true>(As, tm.V6, wave, lane, acc);
+    row_sumsq<PREC != FLARE_FP32>(acc, dots);
+  } else {
+    mfma_pass_bf16x6<false>(As, tm.V6, wave, lane, acc);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      float d[4][NCB];
+      block_dots(As, acc, wave, lane, i, d, dots[i]);
+    }
+  }
+  const float x = row_value(dots, l16);
+  if (l16 < 8) {
+    const int rl = wave * 32 + (l16 >> 2) * 16 + 4 * grp + (l16 & 3);
+    const int atom = rs.atom[rl];
+    const float nv = rs.nrm[rl];
+    if (atom >= 0) {
+      const float v = nv > 0.f ? x / (nv * nv) : 0.f;
+      a.v_int[atom] = v;
+      a.v_row[row0 + rl] = v;
+    }
+  }
+}
+
 // 2/3. quadratic forms and epilogue on a complete descriptor tile; leaves g in the tile
 // when the energy pass runs. Wave w of the 4 owns rows 32w .. 32w + 31.
 // V64: the variance in FP64 (split forms); otherwise through the FP32 factor (or the full
@@ -631,64 +709,20 @@ __device__ __forceinline__ void forms_phase(const FusedArgs& a, float* As, const
                                             const TileModel& tm) {
   const int lane = t & 63, wave = t >> 6;
   const int l16 = lane & 15, grp = lane >> 4;
-  const float* nrm_s = rs.nrm;
-  const float* rsc_s = rs.rsc;
-  f4 acc[2][NCB];
-  float dots[2][4];
   if ((a.mode & 2) && V64) {
-    // split forms: V = |L^T d~|^2 / |d~|^2 with FP64 products, sums and division
     double vv[2][4];
     var_pass_f64(As, tm.L64, wave, lane, vv);
-    const double x = row_value(vv, l16);
-    if (l16 < 8) {
-      const int rl = wave * 32 + (l16 >> 2) * 16 + grp + 4 * (l16 & 3);     // FP64 accumulator layout
-      const int atom = rs.atom[rl];
-      const double n2 = rs.nrm2[rl];
-      if (atom >= 0) {
-        const float v = n2 > 0.0 ? (float)(x / n2) : 0.f;
-        a.v_int[atom] = v;
-        a.v_row[row0 + rl] = v;
-      }
-    }
+    store_variance_f64(a, rs, row0, wave, lane, vv);
   } else if (a.mode & 2) {
-    if (a.vchol) {
-      // Z = D L, L lower-triangular
-      mfma_pass_bf16x6<true>(As, tm.V6, wave, lane, acc);
-      row_sumsq<PREC != FLARE_FP32>(acc, dots);
-    } else {
-      mfma_pass_bf16x6<false>(As, tm.V6, wave, lane, acc);
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        float d[4][NCB];
-        block_dots(As, acc, wave, lane, i, d, dots[i]);
-      }
-    }
-    const float x = row_value(dots, l16);
-    if (l16 < 8) {
-      const int rl = wave * 32 + (l16 >> 2) * 16 + 4 * grp + (l16 & 3);
-      const int atom = rs.atom[rl];
-      const float nv = nrm_s[rl];
-      if (atom >= 0) {
-        const float v = nv > 0.f ? x / (nv * nv) : 0.f;
-        a.v_int[atom] = v;
-        a.v_row[row0 + rl] = v;
-      }
-    }
+    variance_fp32<PREC>(a, As, rs, row0, wave, lane, tm);
   }
   if (a.mode & 1) {
+    f4 acc[2][NCB];
+    float dots[2][4];
     if (PREC == FLARE_BF16_SPLIT) {
       mfma_pass_bf16<0>(As, tm.Wb, wave, lane, acc);
     } else if (PREC == FLARE_FP8_SPLIT) {
-      mfma_pass_fp8(As, rsc_s, tm.W8, wave, lane, acc);
-      // undo the power-of-two scales: Y~ = acc / (16 s_r s_b), exact
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const float inv = 1.f / (16.f * rsc_s[wave * 32 + i * 16 + 4 * grp + r] * tm.bsc);
-#pragma unroll
-          for (int j = 0; j < NCB; ++j) acc[i][j][r] *= inv;
-        }
+      energy_pass_fp8(As, rs.rsc, tm, wave, lane, acc);
     } else {
       mfma_pass_bf16x6<false>(As, tm.W6, wave, lane, acc);
     }
@@ -708,7 +742,7 @@ __device__ __forceinline__ void forms_phase(const FusedArgs& a, float* As, const
         dots[i][r] = e;
         float* p = As + rl * AS + l16;
 #pragma unroll
-        for (int j = 0; j < NCB; ++j) p[j * 16] = s2 * (acc[i][j][r] - e * d[r][j]);
+        for (int j = 0; j < NCB; ++j) p[j * 16] = s2 * fmaf(-e, d[r][j], acc[i][j][r]);
       }
     }
     const float e = row_value(dots, l16);
@@ -830,6 +864,166 @@ __global__ __launch_bounds__(WW * 64, 1) void k_fused144_w(FusedArgs a, int nsub
   }
 }
 
+// Few rows: a work-group of four waves per 32-row sub-tile, and in the same launch the
+// descriptors of the mixed rows (work-groups from nsub on). One wave working through a
+// sub-tile's phases is one chain of waits (37-46 us whatever the number of rows); here the
+// phases after the densities are shared out: the energy pass by groups of column blocks
+// (waves 0-2) beside the variance (wave 3; in FP64 waves 1-3 beside the energy), the epilogue
+// by rows, the pair terms by slots. Every product and sum is formed in the order of the kernels
+// for many rows, so a row's results do not depend on the route. The energy pass's three groups
+// and the pair terms' eight lanes set the registers (one wave a SIMD): nothing else is there to
+// hide behind, so latency alone counts. With the mixed rows' descriptors in the same launch no
+// second stream is needed, whose two events cost 20-40 us a call. A cell of 80 atoms with its
+// list 200 -> 144 us, ten steps of 1,200 atoms 940 -> 655.
+constexpr int FW = 256;
+
+template <int PREC, bool V64>
+__global__ __launch_bounds__(FW, 1) void k_fused144_few(FusedArgs a, int nsub, int forces, MixedDescArgs md) {
+  __shared__ __attribute__((aligned(16))) float lds[2 * WR * AS > MIXED_LDS ? 2 * WR * AS : MIXED_LDS];
+  __shared__ float nrm_s[WR];
+  __shared__ double nrm2_s[WR];
+  __shared__ float rsc_s[WR];
+  __shared__ int atom_s[WR];
+  __shared__ float inv2_s[WR];
+  __shared__ float scale2_s[WR];
+  __shared__ double ss_s[64][8];           // FP64 variance: row sums handed from group to group
+  if ((int)blockIdx.x >= nsub) {
+    desc_mixed_block(md, blockIdx.x - nsub, lds);
+    return;
+  }
+  static_assert(FW == MTHREADS, "a work-group takes a block of mixed rows");
+  static_assert(US <= AS, "u of a row fits the Y tile's stride");
+  static_assert(ADJ_FEW_SLOTS * 32 * 3 <= WR * AS, "the pair terms fit the descriptor tile");
+  float* As = lds;
+  float* Ys = lds + WR * AS;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int l16 = lane & 15, grp = lane >> 4;
+  const RowScalars rs{nrm_s, nrm2_s, rsc_s, atom_s, inv2_s, scale2_s};
+  const int row0 = blockIdx.x * WR;
+  const TileModel tm = tile_model(a, row0);
+  float c[NR][NQ];
+  if (wave == 0) desc_phase<PREC, false>(a, As, rs, row0, lane, c);
+  __syncthreads();
+  if (a.D_out) {
+    for (int idx = threadIdx.x; idx < WR * ND1; idx += FW) {
+      const int r = idx / ND1, k = idx % ND1;
+      const int i = atom_s[r];
+      const float nv = nrm_s[r];
+      if (i >= 0) a.D_out[(size_t)a.perm[i] * ND + tm.dstart + k] = nv > 0.f ? As[r * AS + k] / nv : 0.f;
+    }
+  }
+  if (!(a.mode & 3)) return;
+  constexpr bool X6 = PREC == FLARE_FP32 || PREC == FLARE_BF16X6_SPLIT;
+  constexpr bool BY_GROUP = X6 && !V64;    // the energy pass over waves 0-2
+  const bool want_v = a.mode & 2;
+  if (a.mode & 1) {
+    f4 acc[2][NCB];
+    int j0 = 0, j1 = 0;                    // column blocks of this wave
+    if (BY_GROUP) {
+      if (wave == 0) mfma_pass_bf16x6<false, 0>(As, tm.W6, 0, lane, acc);
+      else if (wave == 1) mfma_pass_bf16x6<false, 1>(As, tm.W6, 0, lane, acc);
+      else if (wave == 2) mfma_pass_bf16x6<false, 2>(As, tm.W6, 0, lane, acc);
+      j0 = wave < 3 ? 3 * wave : NCB;
+      j1 = wave < 3 ? j0 + 3 : NCB;
+    } else if (wave == 0) {
+      if (X6) mfma_pass_bf16x6<false>(As, tm.W6, 0, lane, acc);
+      else if (PREC == FLARE_BF16_SPLIT) mfma_pass_bf16<0>(As, tm.Wb, 0, lane, acc);
+      else energy_pass_fp8(As, rsc_s, tm, 0, lane, acc);
+      j1 = NCB;
+    }
+#pragma unroll
+    for (int j = 0; j < NCB; ++j)
+      if (j >= j0 && j < j1)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) Ys[(i * 16 + 4 * grp + r) * AS + j * 16 + l16] = acc[i][j][r];
+  }
+  if (V64 && want_v) {
+    // groups 0, 1, 2 on waves 1, 2, 3; the squares in the order of the groups
+    d4 acc[2][3];
+    if (wave == 1) var_group_f64<0>(As, tm.L64, 0, lane, acc);
+    else if (wave == 2) var_group_f64<1>(As, tm.L64, 0, lane, acc);
+    else if (wave == 3) var_group_f64<2>(As, tm.L64, 0, lane, acc);
+#pragma unroll
+    for (int g = 1; g <= 3; ++g) {
+      if (wave == g) {
+        double ss[2][4];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) ss[k >> 2][k & 3] = g == 1 ? 0.0 : ss_s[lane][k];
+        var_squares_f64(acc, ss);
+        if (g < 3) {
+#pragma unroll
+          for (int k = 0; k < 8; ++k) ss_s[lane][k] = ss[k >> 2][k & 3];
+        } else {
+          double vv[2][4];
+#pragma unroll
+          for (int k = 0; k < 8; ++k) vv[k >> 2][k & 3] = sum16d(ss[k >> 2][k & 3]);
+          store_variance_f64(a, rs, row0, 0, lane, vv);
+        }
+      }
+      __syncthreads();
+    }
+  } else {
+    if (want_v && wave == 3) variance_fp32<PREC>(a, As, rs, row0, 0, lane, tm);
+    __syncthreads();
+  }
+  if (!(a.mode & 1)) return;
+  // e and g: wave w takes the rows 4 grp + 2 (w & 1), + 1 of row block w >> 1
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {
+    const int rl = (wave >> 1) * 16 + 4 * grp + 2 * (wave & 1) + r;
+    float* p = As + rl * AS + l16;
+    const float* q = Ys + rl * AS + l16;
+    float d[NCB], y[NCB];
+#pragma unroll
+    for (int j = 0; j < NCB; ++j) {
+      d[j] = p[j * 16];
+      y[j] = q[j * 16];
+    }
+    float s = 0.f;
+#pragma unroll
+    for (int j = 0; j < NCB; ++j) s = fmaf(y[j], d[j], s);
+    const float inv2 = inv2_s[rl];
+    const float e = sum16(s) * inv2;
+    const float s2 = 2.f * inv2 * scale2_s[rl];
+#pragma unroll
+    for (int j = 0; j < NCB; ++j) p[j * 16] = s2 * fmaf(-e, d[j], y[j]);
+    const int atom = atom_s[rl];
+    if (l16 == 0 && atom >= 0) {
+      a.e_int[atom] = e;
+      a.e_row[row0 + rl] = e;
+    }
+  }
+  __syncthreads();
+  if (!forces) {
+    float* G = a.G + (size_t)(row0 / FR) * ND1 * FR + row0 % FR;
+    for (int idx = threadIdx.x; idx < ND1 * WR; idx += FW) G[(idx >> 5) * FR + (idx & 31)] = As[(idx & 31) * AS + (idx >> 5)];
+    return;
+  }
+  const int S = wave_slice(row0);
+  const int len = a.v.slice_base[S + 1] - a.v.slice_base[S];
+  const int rl = lane >> 1, h = lane & 1;
+  const int atom = atom_s[rl];
+  if (len > ADJ_FEW_SLOTS) {
+    if (wave == 0) adjoint_phase(a, As, rs, row0, lane, c);
+    return;
+  }
+  if (wave == 0 && atom >= 0) {
+    u_transform_half(As + rl * AS, 1, h, c);
+#pragma unroll
+    for (int n = 0; n < NR; ++n)
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        *reinterpret_cast<float4*>(Ys + rl * US + n * NLM + NQ * h + 4 * q) =
+            make_float4(c[n][4 * q], c[n][4 * q + 1], c[n][4 * q + 2], c[n][4 * q + 3]);
+  }
+  __syncthreads();
+  if (atom >= 0) adjoint_pairs_few(a.v, row0 + rl, rl, h, wave, Ys, As);
+  __syncthreads();
+  if (wave == 0 && atom >= 0) adjoint_own_few(a.v, row0 + rl, rl, h, As, a.f_own);
+}
+
 }  // namespace
 
 void make_fp8_fragments(const float* vals, int groups, uint64_t* out) {
@@ -851,6 +1045,39 @@ void launch_tiles(const flare_model* m, const FusedArgs& a, int ntiles, hipStrea
     else k_fused144<FLARE_FP8_SPLIT, false, GIVEN><<<ntiles, FT, 0, st>>>(a);
   } else {
     k_fused144<FLARE_FP32, false, GIVEN><<<ntiles, FT, 0, st>>>(a);
+  }
+}
+
+// The rows take k_fused144_few while its work-groups, sub-tiles and blocks of mixed rows, are
+// at most two for each of the 256 CUs (one at a time is resident); the mixed rows must fit one
+// chunk. Many -> few, us for energies + forces + variances / descriptors / variances alone:
+// 1,000 atoms of a gas column 94 -> 55 / 28 -> 24 / 49 -> 42, slabs of 3,000 atoms 83 -> 71 /
+// 28 -> 24 / 55 -> 44, of 8,000 (348 and 398 work-groups) 97 -> 89 / 28 -> 24 / 77 -> 71 and
+// 105 -> 98 / 32 -> 28 / 83 -> 75, of 12,000 (510) 105 -> 103 / 32 -> 31 / 82 -> 78, of 16,000
+// (675) no gain, of 24,000 (1,022) 135 -> 145 / 41 -> 49 / 89 -> 100.
+constexpr int FEW_GROUPS = 512;
+bool few_single_rows(const flare_state* s) {
+  return s->rows1 > 0 && s->rows1 / WR + s->rowsx / MROWS <= FEW_GROUPS && s->rowsx <= s->mix_cap;
+}
+
+void launch_few(flare_state* s, const FusedArgs& a, bool forces, float* d_out) {
+  const flare_model* m = s->model;
+  const bool v64 = m->var64;
+  const int nsub = s->rows1 / WR, f = forces ? 1 : 0;
+  const int grid = nsub + s->rowsx / MROWS;
+  const MixedDescArgs md = mixed_desc_args(s, 0, s->rowsx, d_out);
+  hipStream_t st = s->stream;
+  if (m->precision == FLARE_BF16_SPLIT) {
+    if (v64) k_fused144_few<FLARE_BF16_SPLIT, true><<<grid, FW, 0, st>>>(a, nsub, f, md);
+    else k_fused144_few<FLARE_BF16_SPLIT, false><<<grid, FW, 0, st>>>(a, nsub, f, md);
+  } else if (m->precision == FLARE_BF16X6_SPLIT) {
+    if (v64) k_fused144_few<FLARE_BF16X6_SPLIT, true><<<grid, FW, 0, st>>>(a, nsub, f, md);
+    else k_fused144_few<FLARE_BF16X6_SPLIT, false><<<grid, FW, 0, st>>>(a, nsub, f, md);
+  } else if (m->precision == FLARE_FP8_SPLIT) {
+    if (v64) k_fused144_few<FLARE_FP8_SPLIT, true><<<grid, FW, 0, st>>>(a, nsub, f, md);
+    else k_fused144_few<FLARE_FP8_SPLIT, false><<<grid, FW, 0, st>>>(a, nsub, f, md);
+  } else {
+    k_fused144_few<FLARE_FP32, false><<<grid, FW, 0, st>>>(a, nsub, f, md);
   }
 }
 
@@ -885,8 +1112,8 @@ void forms_given_144(flare_state* s, int bucket, int n, const float* d, float* e
   launch_tiles<true>(m, a, rows / FR, s->stream);
 }
 
-void fused_quadratic_forms(flare_state* s, int mode, float* d_out) {
-  if (s->rows1 == 0 || (!(mode & (3 | FORMS_DESCRIPTORS)) && !d_out)) return;
+bool fused_quadratic_forms(flare_state* s, int mode, float* d_out) {
+  if (s->rows1 == 0 || (!(mode & (3 | FORMS_DESCRIPTORS)) && !d_out)) return false;
   FusedArgs a{};
   a.v = slot_view(s);
   a.aor = s->atom_of_row1;
@@ -915,6 +1142,10 @@ void fused_quadratic_forms(flare_state* s, int mode, float* d_out) {
   for (int k = 0; k < 4; ++k) a.dstart[k] = bucket_env(k) == 0 ? 0 : ND - ND1;
   const int ntiles = s->rows1 / FR;
   a.mode = mode & 3;
+  if (few_single_rows(s)) {
+    launch_few(s, a, (mode & 4) != 0, d_out);
+    return true;
+  }
   if ((mode & 5) == 5) {
     // energies + forces: persistent work-groups, one per CU, waves independent
     const int nsub = s->rows1 / WR;
@@ -934,9 +1165,10 @@ void fused_quadratic_forms(flare_state* s, int mode, float* d_out) {
     } else {
       k_fused144_w<FLARE_FP32, false><<<grid, WW * 64, 0, st>>>(a, nsub);
     }
-    return;
+    return false;
   }
   launch_tiles<false>(s->model, a, ntiles, s->stream);
+  return false;
 }
 
 }  // namespace flare

@@ -25,7 +25,7 @@ __device__ __forceinline__ void accumulate_half(const SlotView& v, int Rw, int h
     for (int q = 0; q < NQ; ++q) {
       const float y = h ? Y[NQ + q] : Y[q];
 #pragma unroll
-      for (int nn = 0; nn < NR; ++nn) c[nn][q] += R[nn] * y;
+      for (int nn = 0; nn < NR; ++nn) c[nn][q] = fmaf(R[nn], y, c[nn][q]);
     }
   });
 }
@@ -36,9 +36,10 @@ __device__ __forceinline__ void accumulate_half(const SlotView& v, int Rw, int h
 // l = 1 (q1..3) and part of l = 2 (q4..7); lane 1 the rest of l = 2 (q0) and l = 3
 // (q1..7). One cross-lane move per pair brings lane 0's part of l = 2 to lane 1.
 __device__ __forceinline__ float2 b2_half(const float* ca, const float* cb, int h) {
+#pragma clang fp contract(off)
   const float v0 = ca[0] * cb[0];
-  const float v1 = ca[1] * cb[1] + ca[2] * cb[2] + ca[3] * cb[3];
-  const float v2 = ca[4] * cb[4] + ca[5] * cb[5] + ca[6] * cb[6] + ca[7] * cb[7];
+  const float v1 = fmaf(ca[3], cb[3], fmaf(ca[2], cb[2], ca[1] * cb[1]));
+  const float v2 = fmaf(ca[7], cb[7], fmaf(ca[6], cb[6], fmaf(ca[5], cb[5], ca[4] * cb[4])));
   const float x = xor1(v2);            // lane 1 receives lane 0's part of l = 2
   return h ? make_float2(v0 + x, v1 + v2) : make_float2(v0, v1);
 }

@@ -92,7 +92,8 @@ __device__ __forceinline__ float mixed_row_energy(const float4* __restrict__ d4,
   }
   float e = 0.f;
 #pragma unroll
-  for (int k = 0; k < NQ4; ++k) e += (d[k].x * y[k].x + d[k].y * y[k].y) + (d[k].z * y[k].z + d[k].w * y[k].w);
+  for (int k = 0; k < NQ4; ++k)
+    e = fmaf(d[k].w, y[k].w, fmaf(d[k].z, y[k].z, fmaf(d[k].y, y[k].y, fmaf(d[k].x, y[k].x, e))));
   return sum16(e);
 }
 // Variance of the row from the shares of its 17 column pairs (FP64 ones summed in FP64 and

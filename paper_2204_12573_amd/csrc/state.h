@@ -290,7 +290,9 @@ void pair_geometry(flare_state* s);
 // kernel, FORMS_DESCRIPTORS the descriptors (and norms) alone; d_out (caller order, [n][544],
 // zeroed by the caller) receives their descriptors
 constexpr int FORMS_DESCRIPTORS = 8;
-void fused_quadratic_forms(flare_state* s, int mode, float* d_out);
+// Few rows: the mixed rows' descriptors are formed in the same launch (returns true).
+bool fused_quadratic_forms(flare_state* s, int mode, float* d_out);
+bool few_single_rows(const flare_state* s);   // whether it will take the route for few rows
 // mixed rows [r0, r0 + nr) of the 544-wide class (nr <= mix_cap, r0 a multiple of mix_cap),
 // in the chunk workspace Dx/Cx/Yx/Px: descriptors (and their export to caller order),
 // quadratic forms, adjoint terms
