@@ -160,7 +160,7 @@ __device__ __forceinline__ void adjoint_pairs_half(const SlotView& v, int R, int
   float sx = 0.f, sy = 0.f, sz = 0.f;
   // lane h takes slots k = h, h + 2, ...: the geometry and reverse index of its next two
   // slots are in flight while two are evaluated, in two register groups that take turns
-  // (as in for_each_slot: unconditional loads, past the slice re-reading its last slot)
+  // (unconditional loads, past the slice re-reading its last slot)
   auto load = [&](int k, float4& g, int& r) {
     const size_t sl = s0 + (size_t)min(k, len - 1) * 32;
     g = v.geom[sl];

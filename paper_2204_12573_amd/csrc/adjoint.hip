@@ -28,7 +28,7 @@ __global__ __launch_bounds__(TA) void k_adjoint144(SlotView v, const int* __rest
 #pragma unroll
     for (int q = 0; q < NQ; ++q) c[n][q] = 0.f;
   const int R = tile * 128 + rl;
-  accumulate_half(v, R, h, c);
+  accumulate_half(v, R, i, h, false, c);
   u_transform_half(G + (size_t)tile * ND1 * 128 + rl, 128, h, c);
   adjoint_pairs_half(v, R, h, c, f_own);
 }

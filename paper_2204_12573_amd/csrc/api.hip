@@ -16,11 +16,14 @@ void set_error(const std::string& msg) { g_last_error = msg; }
 
 SlotView slot_view(const flare_state* s) {
   SlotView v;
+  v.d0 = s->slot_d0;
+  v.dlt = s->dlt;
   v.geom = s->geom;
   v.slice_base = s->slice_base;
   v.rev = s->slot_rev;
   v.w_in = s->w_in;
   v.rc = (float)s->model->r_cut;
+  v.rc2 = (float)(s->model->r_cut * s->model->r_cut);
   return v;
 }
 
@@ -244,8 +247,6 @@ static void state_arrays(flare_state* s, F&& f) {
   f((void**)&s->Px64, X * 17 * 8);
   f((void**)&s->slice_len, (SL + 1) * 4);
   f((void**)&s->slice_base, (SL + 1) * 4);
-  f((void**)&s->slot_atom, SC * 4);
-  f((void**)&s->slot_j, SC * 4);
   f((void**)&s->slot_rev, SC * 4);
   f((void**)&s->slot_d0, SC * 16);
   f((void**)&s->geom, SC * 16);
@@ -676,7 +677,7 @@ int flare_neighbors_export(flare_state* s, long long* offsets, int32_t* j_out, i
 static void mixed_rows(flare_state* s, bool have_desc, float* d_out, bool want_e, bool want_v, bool want_f) {
   for (int r0 = 0; r0 < s->rowsx; r0 += s->mix_cap) {
     const int nr = std::min(s->mix_cap, s->rowsx - r0);
-    if (!have_desc) desc_mixed_chunk(s, r0, nr, d_out);
+    if (!have_desc) desc_mixed_chunk(s, r0, nr, d_out, want_e || want_f);
     forms_mixed_chunk(s, r0, nr, want_e || want_f, want_v, !want_f);
     if (want_f) adjoint_mixed_chunk(s, r0, nr, want_v);
   }
@@ -695,7 +696,6 @@ int flare_descriptors(flare_state* s, const double* x, const double* y, const do
   {
     StageTimer tm(s, FLARE_T_DESC1);
     gather_positions(s, x, y, z);
-    pair_geometry(s);
   }
   if (d_out || norm_out) {
     // the single-species rows come from the fused kernel run without quadratic forms
@@ -939,10 +939,9 @@ int flare_md_step(flare_state* s, double* x, double* y, double* z, double* vx, d
     if (rc != FLARE_OK) return rc;
     s->have_list = true;
   }
-  {
+  if (rebuild) {
     StageTimer tm(s, FLARE_T_DESC1);
-    if (rebuild) gather_positions(s, x, y, z);   // the displacements from the new build (zero)
-    pair_geometry(s);
+    gather_positions(s, x, y, z);   // the displacements from the new build (zero)
   }
   s->have_desc = true;
   s->pos_gen += 1;

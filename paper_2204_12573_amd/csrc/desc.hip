@@ -14,7 +14,6 @@
 namespace flare {
 namespace {
 
-
 __global__ __launch_bounds__(MTHREADS) void k_desc_mixed(MixedDescArgs q) {
   __shared__ __attribute__((aligned(16))) float lds[MIXED_LDS];
   desc_mixed_block(q, blockIdx.x, lds);
@@ -33,24 +32,6 @@ __global__ __launch_bounds__(NTG) void k_disp(int n, const int* __restrict__ inv
   const int a = blockIdx.x * NTG + threadIdx.x;
   if (a >= n) return;
   store_displacement(a, n, x[a], y[a], z[a], xb, inv_perm, dlt, lim2, status);
-}
-
-// Per-step geometry of every listed pair (slot_geom). The pair vector is split as
-//   Delta = [(w_j - w_i) + s*L] + (delta_j - delta_i),
-// the bracket fixed at the list build (FP64, stored rounded to FP32 with the neighbour's
-// species in .w) and the displacements since the build added in FP32. One thread per slot
-// (its loads independent of each other's); padding slots keep the zero geometry the list
-// build gave them.
-__global__ __launch_bounds__(NTG) void k_geom(long long nslots, const int* __restrict__ slot_atom,
-                                              const int* __restrict__ slot_j,
-                                              const float4* __restrict__ slot_d0,
-                                              const float4* __restrict__ dlt, float rc2,
-                                              float4* __restrict__ geom) {
-  const long long slot = (long long)blockIdx.x * NTG + threadIdx.x;
-  if (slot >= nslots) return;
-  const int i = slot_atom[slot];
-  if (i < 0) return;
-  geom[slot] = slot_geom(slot_d0[slot], dlt[slot_j[slot]], dlt[i], rc2);
 }
 
 // |d~| of every atom in caller order (0 for an atom without neighbours).
@@ -73,22 +54,14 @@ void gather_positions(flare_state* s, const double* x, const double* y, const do
                                                      s->d_status);
 }
 
-void pair_geometry(flare_state* s) {
-  const long long ns = s->n_slots;
-  if (ns == 0) return;
-  const double rc = s->model->r_cut;
-  k_geom<<<(int)((ns + NTG - 1) / NTG), NTG, 0, s->stream>>>(ns, s->slot_atom, s->slot_j, s->slot_d0, s->dlt,
-                                                             (float)(rc * rc), s->geom);
-}
-
-MixedDescArgs mixed_desc_args(flare_state* s, int r0, int nr, float* d_out) {
+MixedDescArgs mixed_desc_args(flare_state* s, int r0, int nr, float* d_out, bool keep_geom) {
   return MixedDescArgs{slot_view(s), s->rows1, r0, s->atom_of_rowx, s->perm, s->Dx, nr <= FEW_ROWS ? s->D6x : nullptr,
-                       s->Cx, s->nrm, d_out};
+                       s->Cx, s->nrm, d_out, keep_geom};
 }
 
-void desc_mixed_chunk(flare_state* s, int r0, int nr, float* d_out) {
+void desc_mixed_chunk(flare_state* s, int r0, int nr, float* d_out, bool keep_geom) {
   StageTimer tm(s, FLARE_T_DESCX);
-  if (nr > 0) k_desc_mixed<<<nr / MROWS, MTHREADS, 0, s->stream>>>(mixed_desc_args(s, r0, nr, d_out));
+  if (nr > 0) k_desc_mixed<<<nr / MROWS, MTHREADS, 0, s->stream>>>(mixed_desc_args(s, r0, nr, d_out, keep_geom));
 }
 
 void export_norms(flare_state* s, float* norm_out) {

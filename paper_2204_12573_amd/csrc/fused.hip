@@ -559,7 +559,7 @@ __device__ __forceinline__ void desc_phase(const FusedArgs& a, float* As, const 
   for (int n = 0; n < NR; ++n)
 #pragma unroll
     for (int q = 0; q < NQ; ++q) c[n][q] = 0.f;
-  if (i >= 0 && !GIVEN) accumulate_half(a.v, row0 + rl, h, c);
+  if (i >= 0 && !GIVEN) accumulate_half(a.v, row0 + rl, i, h, a.mode & 1, c);
   // one B2 pass: the unnormalised d~ goes into the tile; 1/|d~| is applied in the
   // epilogue (Y is linear in the row, so Y(d) = Y(d~)/|d~|)
   // |d~|^2: FP64 in the split forms (their norms stay FP64), FP32 in the FP32 form (144
@@ -1065,7 +1065,7 @@ void launch_few(flare_state* s, const FusedArgs& a, bool forces, float* d_out) {
   const bool v64 = m->var64;
   const int nsub = s->rows1 / WR, f = forces ? 1 : 0;
   const int grid = nsub + s->rowsx / MROWS;
-  const MixedDescArgs md = mixed_desc_args(s, 0, s->rowsx, d_out);
+  const MixedDescArgs md = mixed_desc_args(s, 0, s->rowsx, d_out, a.mode & 1);
   hipStream_t st = s->stream;
   if (m->precision == FLARE_BF16_SPLIT) {
     if (v64) k_fused144_few<FLARE_BF16_SPLIT, true><<<grid, FW, 0, st>>>(a, nsub, f, md);

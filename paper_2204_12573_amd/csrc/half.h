@@ -11,23 +11,72 @@ namespace flare {
 
 constexpr int NQ = 8;   // (l, m) indices per lane
 
-// c[n][q] += R_n Y_{8h+q} over the neighbours of row R inside the cutoff. All rows of a
-// wave share one slice, so the trip count is uniform across the wave.
-__device__ __forceinline__ void accumulate_half(const SlotView& v, int Rw, int h, float (*c)[NQ]) {
-  for_each_slot<4>(v, Rw, [&](const float4& g, int) {
-    PairGeom pg;
-    int sp;
-    if (!unpack_geom(g, pg, sp)) return;
-    float R[NR], Y[NLM];
-    radial(pg.r, v.rc, R);
-    sph_harm(pg.ux, pg.uy, pg.uz, Y);
+// c[n][q] += R_n Y_{8h+q} over the neighbours of row R (atom i) inside the cutoff. The lanes
+// take the slots in turns (k = 2 m + h): each forms its slot's geometry from the fixed part and
+// the displacements (kept in v.geom for the later passes when keep), evaluates the basis once
+// and hands the partner R and the partner's half of Y; both then add the two slots, their own
+// first. All rows of a wave share one slice, so the trip count is uniform across the wave.
+// What a slot needs arrives over two dependent loads: the fixed parts are loaded two groups of
+// two slots a lane ahead and the neighbours' displacements one, in two register groups that take
+// turns (every value is used from the register it was loaded into, so that each wait covers
+// only the older group). Loads are unconditional: past the slice they re-read its last slot.
+__device__ __forceinline__ void accumulate_half(const SlotView& v, int R, int i, int h, bool keep, float (*c)[NQ]) {
+#pragma clang fp contract(off)
+  const int S = wave_slice(R);
+  const int base = v.slice_base[S];
+  const int len = v.slice_base[S + 1] - base;
+  if (len <= 0) return;
+  const float4 di = v.dlt[i];
+  const size_t s0 = (size_t)base * 32 + (R & 31);
+  const float4* p = v.d0 + s0;
+  float4* to = v.geom + s0;
+  auto fixed = [&](int k) { return p[(size_t)min(k + h, len - 1) * 32]; };
+  auto moved = [&](const float4& d) { return v.dlt[slot_neighbour(d)]; };
+  auto add = [&](int k, float4 g) {
+    if (k >= len) return;
+    if (k + h >= len) g.w = 0.f;
+    else if (keep) to[(size_t)(k + h) * 32] = g;
+    const float r = g.w != 0.f ? fabsf(g.w) : v.rc;       // R = 0 at the cutoff, exactly
+    float R0[NR], Y[NLM], R1[NR];
+    radial(r, v.rc, R0);
+    sph_harm(g.x, g.y, g.z, Y);
+#pragma unroll
+    for (int n = 0; n < NR; ++n) R1[n] = xor1(R0[n]);
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
-      const float y = h ? Y[NQ + q] : Y[q];
+      const float own = h ? Y[NQ + q] : Y[q];
+      const float other = xor1(h ? Y[q] : Y[NQ + q]);
 #pragma unroll
-      for (int nn = 0; nn < NR; ++nn) c[nn][q] = fmaf(R[nn], y, c[nn][q]);
+      for (int n = 0; n < NR; ++n) c[n][q] = fmaf(R1[n], other, fmaf(R0[n], own, c[n][q]));
     }
-  });
+  };
+  float4 da[2], ea[2], db[2], eb[2], g[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) da[u] = fixed(2 * u);
+#pragma unroll
+  for (int u = 0; u < 2; ++u) db[u] = fixed(4 + 2 * u);
+#pragma unroll
+  for (int u = 0; u < 2; ++u) ea[u] = moved(da[u]);
+  for (int k0 = 0;; k0 += 8) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) eb[u] = moved(db[u]);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) g[u] = slot_geom(da[u], ea[u], di, v.rc2);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) da[u] = fixed(k0 + 8 + 2 * u);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) add(k0 + 2 * u, g[u]);
+    if (k0 + 4 >= len) break;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) ea[u] = moved(da[u]);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) g[u] = slot_geom(db[u], eb[u], di, v.rc2);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) db[u] = fixed(k0 + 12 + 2 * u);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) add(k0 + 4 + 2 * u, g[u]);
+    if (k0 + 8 >= len) break;
+  }
 }
 
 // One B2 radial pair (a, b) of a single-species block, split between the two lanes of

@@ -20,24 +20,33 @@ __device__ __forceinline__ int cidx(int a, int lm) { return a * NLM + (a >> 3) *
 
 // Densities c[lm] of channel L of every row of the work-group, c = sum over the row's slots of
 // R_{L & 7}(r) Y_lm(r^) for neighbours of species L >> 3. Slots go in groups of 16: each lane
-// evaluates the basis of one of them into LDS (16 radial values, the other species' eight
+// forms the geometry of one of them (kept in v.geom for the later
+// passes when keep) and evaluates its basis into LDS (16 radial values, the other species' eight
 // zero, and 16 harmonics), then every lane adds the 16 slots in order to its channel. (Each
 // lane evaluating the whole basis of every slot for its one channel did 1.7 k vector
 // instructions a row group where this does 0.6 k: 42.5 -> 37.6 us for 16 k rows of slabs, with the
 // rows written once in FP32 where they are many.)
 constexpr int PBS = 32;                    // LDS floats per slot
-__device__ __forceinline__ void mixed_densities(const SlotView& v, int R, int rl, int L, float* __restrict__ bs,
-                                                float (&c)[NLM]) {
+__device__ __forceinline__ void mixed_densities(const SlotView& v, int R, int i, int rl, int L, bool keep,
+                                                float* __restrict__ bs, float (&c)[NLM]) {
   const int S = wave_slice(R);
   const int base = v.slice_base[S];
   const int len = v.slice_base[S + 1] - base;
-  const float4* p = v.geom + (size_t)base * 32 + (R & 31);
+  const size_t s0 = (size_t)base * 32 + (R & 31);
+  auto fixed = [&](int k) { return k < len ? v.d0[s0 + (size_t)k * 32] : pad_slot(); };
+  const float4 di = i >= 0 ? v.dlt[i] : make_float4(0.f, 0.f, 0.f, 0.f);
+  float4 d0 = fixed(L), d1 = fixed(16 + L);
+  float4 dj = v.dlt[slot_neighbour(d0)];
   float* mine = bs + (rl * 16 + L) * PBS;
   const float* row = bs + rl * 16 * PBS;
 #pragma unroll
   for (int lm = 0; lm < NLM; ++lm) c[lm] = 0.f;
   for (int k0 = 0; k0 < len; k0 += 16) {
-    const float4 g = k0 + L < len ? p[(size_t)(k0 + L) * 32] : make_float4(0.f, 0.f, 0.f, 0.f);
+    const float4 g = slot_geom(d0, dj, di, v.rc2);
+    if (keep && k0 + L < len) v.geom[s0 + (size_t)(k0 + L) * 32] = g;
+    d0 = d1;
+    dj = v.dlt[slot_neighbour(d0)];
+    d1 = fixed(k0 + 32 + L);
     PairGeom pg;
     int sp;
     float Rn[NR], Y[NLM];

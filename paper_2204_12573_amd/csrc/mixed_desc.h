@@ -19,6 +19,7 @@ struct MixedDescArgs {
   float* Cx;                 // densities
   float* nrm_out;
   float* d_out;              // caller order, or null
+  bool keep_geom;
 };
 
 // LDS of a work-group: the slots' basis values, then the channels
@@ -37,7 +38,7 @@ __device__ __forceinline__ void desc_mixed_block(const MixedDescArgs& q, int blo
   const int row = q.r0 + local;
   const int i = q.atom_of_row[row];
   float c[NLM];
-  mixed_densities(q.v, q.rows1 + row, rl, L, lds, c);     // padding rows: empty slots, zeros
+  mixed_densities(q.v, q.rows1 + row, i, rl, L, q.keep_geom, lds, c);     // padding rows: empty slots, zeros
   float* crow = lds + rl * MSTRIDE;
 #pragma unroll
   for (int lm = 0; lm < NLM; ++lm) crow[cidx(L, lm)] = c[lm];
@@ -93,6 +94,6 @@ __device__ __forceinline__ void desc_mixed_block(const MixedDescArgs& q, int blo
 }
 
 // the arguments for rows [r0, r0 + nr) of the mixed class (desc.hip)
-MixedDescArgs mixed_desc_args(flare_state* s, int r0, int nr, float* d_out);
+MixedDescArgs mixed_desc_args(flare_state* s, int r0, int nr, float* d_out, bool keep_geom);
 
 }  // namespace flare

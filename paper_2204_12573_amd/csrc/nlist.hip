@@ -20,6 +20,7 @@
 #include <cmath>
 #include <cstring>
 
+#include "pair.h"
 #include "state.h"
 
 namespace flare {
@@ -618,11 +619,11 @@ __global__ __launch_bounds__(NT) void k_atom_rows(int n, const int* __restrict__
 // The sliced pair layout in one pass, a work-group per 32-row slice: thread (h, l) of 8 x 32
 // takes the slots (slice_base[S] + k) * 32 + l for k = h, h + 8, ... of row R = 32 S + l, so
 // every store is coalesced and the gathers of eight positions of a row are in flight at
-// once. A slot of a listed pair p = (i, j, s) gets i, j, the fixed part of the pair vector
-// (w_j - w_i) + s*L (FP64, stored FP32, neighbour species as the sign of .w) and the slot of
+// once. A slot of a listed pair p = (i, j, s) gets the fixed part of the pair vector
+// (w_j - w_i) + s*L (FP64, stored FP32) with j and its species in .w, and the slot of
 // its reverse pair: slot0[j] + 32 rev[p], rev[p] being the reverse pair's position in j's
 // list. Per pair this gathers two things of the neighbour, w[j] and slot0[j]. Every other
-// slot of the slice is padding: pointing at itself, its geometry zero (for every step of
+// slot of the slice is padding: pointing at itself, with no neighbour (for every step of
 // the list's life).
 __global__ __launch_bounds__(NT) void k_slots(const int* __restrict__ layout, const int* __restrict__ aor1,
                                               const int* __restrict__ aorx, const int* __restrict__ nl_off,
@@ -630,9 +631,7 @@ __global__ __launch_bounds__(NT) void k_slots(const int* __restrict__ layout, co
                                               const int* __restrict__ nl_rev, const int* __restrict__ slot0,
                                               const int* __restrict__ slice_base, const double4* __restrict__ w,
                                               const int* __restrict__ sid, const CellGrid* __restrict__ grids,
-                                              int* __restrict__ slot_atom, int* __restrict__ slot_j,
                                               int* __restrict__ slot_rev, float4* __restrict__ slot_d0,
-                                              float4* __restrict__ geom,
                                               int* __restrict__ status) {
 #pragma clang fp contract(off)
   if (layout[LY_FLAGS]) return;
@@ -671,16 +670,11 @@ __global__ __launch_bounds__(NT) void k_slots(const int* __restrict__ layout, co
       const double dx = (wj.x - wi.x) + (double)sx * L[0];
       const double dy = (wj.y - wi.y) + (double)sy * L[1];
       const double dz = (wj.z - wi.z) + (double)sz * L[2];
-      slot_atom[slot] = i;
-      slot_j[slot] = j;
       slot_rev[slot] = rs;
-      slot_d0[slot] = make_float4((float)dx, (float)dy, (float)dz, wj.w != 0.0 ? 1.f : -1.f);
+      slot_d0[slot] = make_float4((float)dx, (float)dy, (float)dz, __int_as_float(slot_code(j, wj.w != 0.0 ? 1 : 0)));
     } else {
-      slot_atom[slot] = -1;
-      slot_j[slot] = 0;
       slot_rev[slot] = slot;            // padding slots point at themselves
-      slot_d0[slot] = make_float4(0.f, 0.f, 0.f, 0.f);
-      geom[slot] = make_float4(0.f, 0.f, 0.f, 0.f);   // the per-step geometry skips padding
+      slot_d0[slot] = pad_slot();
     }
   }
 }
@@ -846,8 +840,8 @@ int build_list(flare_state* s, const double* x, const double* y, const double* z
   k_atom_rows<<<std::max(nblk, 1), NT, 0, st>>>(n, s->bucket, s->row_of, s->d_layout, s->perm, s->slice_base,
                                                 slice_max, s->slot_cap, s->row_caller, s->slot0);
   k_slots<<<slice_max, NT, 0, st>>>(s->d_layout, s->atom_of_row1, s->atom_of_rowx, s->nl_off, s->nl_j, s->nl_s,
-                                    s->nl_rev, s->slot0, s->slice_base, s->w, s->sid, s->d_grids, s->slot_atom,
-                                    s->slot_j, s->slot_rev, s->slot_d0, s->geom, bst);
+                                    s->nl_rev, s->slot0, s->slice_base, s->w, s->sid, s->d_grids, s->slot_rev,
+                                    s->slot_d0, bst);
   HIPCHK(hipMemcpyAsync(s->h_info, s->d_status, (16 + LY_N) * sizeof(int), hipMemcpyDeviceToHost, st));
   HIPCHK(hipGetLastError());
   HIPCHK(hipStreamSynchronize(st));      // the build's one wait

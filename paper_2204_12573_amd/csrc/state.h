@@ -50,12 +50,15 @@ struct Timers {
 //   row R: 144-wide rows are R = 0..rows1-1, mixed rows R = rows1 + r
 //   slot(R, k) = (slice_base[R / 32] + k) * 32 + R % 32
 struct SlotView {
-  const float4* geom;       // per slot: (u_x, u_y, u_z, r) of the pair, r = 0 outside the
-                            // cutoff or padding; r < 0 marks an H neighbour, r > 0 Pt
+  const float4* d0;         // per slot: fixed part of the pair vector, .w the slot's code (pair.h)
+  const float4* dlt;        // per atom (internal index): displacement since the list build
+  float4* geom;             // per slot: (u_x, u_y, u_z, r) of the pair, r = 0 outside the
+                            // cutoff or padding; r < 0 marks an H neighbour, r > 0 Pt. Written
+                            // with the densities of an evaluation of energies
   const int* slice_base;    // [slices + 1] in groups of 32 slots
   const int* rev;           // per slot: slot of the reverse pair (padding: itself)
   float4* w_in;             // per slot: the adjoint term de_j/dDelta of the reverse pair
-  float rc;
+  float rc, rc2;
 };
 
 __host__ __device__ inline int slot_of(const int* slice_base, int R, int k) {
@@ -228,10 +231,8 @@ struct flare_state {
   long long n_slots = 0;
   int* slice_len = nullptr;             // [slice_cap + 1]
   int* slice_base = nullptr;
-  int* slot_atom = nullptr;              // row's atom (padding: -1)
-  int* slot_j = nullptr;
   int* slot_rev = nullptr;
-  float4* slot_d0 = nullptr;            // per slot: (w_j - w_i) + s*L in FP32, neighbour species sign
+  float4* slot_d0 = nullptr;            // per slot: (w_j - w_i) + s*L in FP32, neighbour and species
   float4* geom = nullptr;               // per slot, per step
   float4* w_in = nullptr;               // per slot: w of the reverse pair
 
@@ -285,7 +286,6 @@ int list_layout_words();   // ints of the device layout record
 int build_list(flare_state* s, const double* x, const double* y, const double* z,
                const int32_t* species);
 void gather_positions(flare_state* s, const double* x, const double* y, const double* z);
-void pair_geometry(flare_state* s);
 // 144-wide rows: mode bit 0 energies and gradients, bit 1 variances, bit 2 forces in the same
 // kernel, FORMS_DESCRIPTORS the descriptors (and norms) alone; d_out (caller order, [n][544],
 // zeroed by the caller) receives their descriptors
@@ -296,7 +296,7 @@ bool few_single_rows(const flare_state* s);   // whether it will take the route 
 // mixed rows [r0, r0 + nr) of the 544-wide class (nr <= mix_cap, r0 a multiple of mix_cap),
 // in the chunk workspace Dx/Cx/Yx/Px: descriptors (and their export to caller order),
 // quadratic forms, adjoint terms
-void desc_mixed_chunk(flare_state* s, int r0, int nr, float* d_out);
+void desc_mixed_chunk(flare_state* s, int r0, int nr, float* d_out, bool keep_geom);
 void forms_mixed_chunk(flare_state* s, int r0, int nr, bool want_e, bool want_v, bool finish);
 void adjoint_mixed_chunk(flare_state* s, int r0, int nr, bool want_v);
 // |d~| of every atom in caller order
