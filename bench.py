@@ -44,7 +44,7 @@ PROFILE = os.path.join(ROOT, "profiles", "k_fused144_w_h2_pt111_1M_fp32.txt")
 def kernel_sources_sha():
     import hashlib
     h = hashlib.sha256()
-    for f in ["fused.hip", "adjoint.h", "half.h", "pair.h", "basis.h", "common.h", "state.h"]:
+    for f in ["fused.hip", "bf16x3.h", "adjoint.h", "half.h", "pair.h", "basis.h", "common.h", "state.h"]:
         with open(os.path.join(ROOT, "paper_2204_12573_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()
@@ -160,9 +160,9 @@ def md_throughput(engine, torch, st, beta, sigma, steps, warmup, precision, sett
     v = torch.zeros_like(p)
     md = engine.MD(ev, p, v, s, [0, n], st.box, dt=0.5, skin=0.2, rebuild=10, want_var=True)
     # a fresh GPU speeds up during its first few tens of ms under load (the fused kernel's
-    # launches fall from about 880 to 780 us over the first 40 steps, the list build's by
-    # 4 %, then stay flat), so untimed settle steps come before the warm-up: the timed
-    # steps are then those of a long run whatever the warm-up count
+    # launches fall from about 800 to 665 us over the first 40 steps, then stay flat), so
+    # untimed settle steps come before the warm-up: the timed steps are then those of a long
+    # run whatever the warm-up count
     for _ in range(settle):
         md.step()
     for _ in range(warmup):
@@ -227,8 +227,8 @@ def form_roofline(prec, fused_work, t_launch):
     peak of each instruction type plus its vector work at the FP32 vector peak (the matrix
     and vector instructions share the SIMD datapath). Per row: the energy pass takes
     `products` part products of 2*144^2 flop (BF16 x3: 3, FP8 x3: 3, BF16 x6: 6) on the
-    form's matrix type; the variance |L^T d|^2 takes 144*145 flop on FP64 matrix cores, or on
-    FP32 ones with FLARE_VAR_FP32."""
+    form's matrix type; the variance |L^T d|^2 takes 144*145 flop on FP64 matrix cores, or with
+    FLARE_VAR_FP32 to FP32 accuracy, counted at the FP32 matrix peak."""
     from paper_2204_12573_amd import binding as B
     base = prec & ~B.VAR_FP32
     products, peak, kind = {B.BF16_SPLIT: (3, PEAK_BF16_MFMA, "bf16"), B.FP8_SPLIT: (3, PEAK_FP8_MFMA, "fp8"),
@@ -524,35 +524,37 @@ def main():
     flops_per_row = 2 * 144 * 144 + (144 * 145 if vchol else 2 * 144 * 144)
     flops_per_launch = n144 * flops_per_row
     t_launch = q_ms / q_cnt * 1e-3
-    # FP32 matrix instructions and FP32 vector instructions share one datapath on gfx950
-    # (measured: a wave issuing MFMAs and a wave issuing FMAs on the same SIMD take the sum
-    # of their separate times), so the kernel is bound by that datapath: its time is at
-    # least the MFMA work at the matrix peak plus the vector work at the non-packed vector
-    # peak. The bound's peak is the blend of the two for this kernel's mix of work.
+    # the FP32 form's products run as six part products on the BF16 matrix cores (three
+    # parts an operand, exact): the kernel's time is at least that matrix work at the BF16 peak
+    # plus the vector work at the non-packed vector peak (both issue from the same SIMD). The
+    # bound's peak is the blend of the two for this kernel's mix of work; flops are the
+    # method's, each FP32 product counted once.
     valu_flops = work["pairs144"] * (VALU_FLOP_DENS + VALU_FLOP_ADJ) + n144 * (
         VALU_FLOP_B2 + VALU_FLOP_NORM + VALU_FLOP_EPI + VALU_FLOP_U)
-    t_min = flops_per_launch / PEAK_FP32_MFMA + valu_flops / PEAK_FP32_VALU
+    peak_x6 = PEAK_BF16_MFMA / 6
+    t_min = flops_per_launch / peak_x6 + valu_flops / PEAK_FP32_VALU
     fused_work = {"n144": n144, "valu_flops": valu_flops, "vchol": vchol}
     total = flops_per_launch + valu_flops
     roofline = {"bound": "alu", "achieved": total / t_launch / 1e12, "peak": total / t_min / 1e12,
                 "unit": "TFLOP/s", "frac": t_min / t_launch, "traffic": profiled_traffic(),
-                "kernel": "k_fused144_w (144-wide rows: descriptors, D[L] and D[beta] on FP32 MFMA, adjoint "
-                          "terms; FP32 matrix and vector instructions share the SIMD datapath)",
-                "peak_derivation": "blend of the FP32 MFMA peak (157.3 TFLOP/s) and the non-packed FP32 vector "
-                                   "peak (78.6 TFLOP/s = 256 CU x 4 SIMD x 16 lanes x 2 flop x 2.4 GHz) "
-                                   "weighted by this kernel's matrix and vector flops",
+                "kernel": "k_fused144_w (144-wide rows: pair geometry, descriptors, D[L] and D[beta] in three "
+                          "BF16 parts on the matrix cores, adjoint terms)",
+                "peak_derivation": "blend of a sixth of the BF16 matrix peak (2500 / 6 TFLOP/s: six part products "
+                                   "an FP32 product) and the non-packed FP32 vector peak (78.6 TFLOP/s = 256 CU x "
+                                   "4 SIMD x 16 lanes x 2 flop x 2.4 GHz) weighted by this kernel's matrix and "
+                                   "vector flops",
                 "mfma_flop_per_launch": flops_per_launch, "mfma_flop_per_row": flops_per_row,
                 "valu_flop_per_launch": int(valu_flops), "pairs_in_cutoff_144": int(work["pairs144"]),
                 "t_min_us": t_min * 1e6, "avg_launch_us": t_launch * 1e6,
                 "variance_form": "cholesky" if vchol else "full",
-                "mfma_only": {"achieved": flops_per_launch / t_launch / 1e12, "peak": PEAK_FP32_MFMA / 1e12,
-                              "frac": flops_per_launch / t_launch / PEAK_FP32_MFMA}}
+                "mfma_only": {"achieved": flops_per_launch / t_launch / 1e12, "peak": peak_x6 / 1e12,
+                              "frac": flops_per_launch / t_launch / peak_x6}}
     # whole step against its ideal time: every stage at the bound of its algorithmic work
     # (the per-unit figures of the method; stage-internal layouts such as the per-slot pair
     # geometry are implementation, not algorithmic work):
     #   144-wide rows  the fused kernel's t_min above (matrix + vector flops);
-    #   544-wide rows  Y = D beta (2 544^2) and Z = D L (544 * 545) per row on the FP32 matrix
-    #                  cores, vector work per pair (densities 320, adjoint 830) and per row
+    #   544-wide rows  Y = D beta (2 544^2) and Z = D L (544 * 545) per row, six part products
+    #                  on the BF16 matrix cores, vector work per pair (densities 320, adjoint 830) and per row
     #                  (B2 4352, |d~|^2 1088, epilogue e, g, V 3808, u 8192) at the vector peak;
     #   list build     100 B per Pt atom, 50 B per H atom of HBM traffic, every `rebuild` steps;
     #   integrator, reductions and outputs  100 B per atom of HBM traffic.
@@ -560,7 +562,7 @@ def main():
     mx_mfma = n544 * (2 * 544 * 544 + (544 * 545 if vchol else 2 * 544 * 544))
     mx_valu = work["pairs544"] * (VALU_FLOP_DENS + VALU_FLOP_ADJ) + n544 * (4352 + 1088 + 3808 + 8192)
     t_parts = {"rows144_fused": t_min,
-               "rows544": mx_mfma / PEAK_FP32_MFMA + mx_valu / PEAK_FP32_VALU,
+               "rows544": mx_mfma / peak_x6 + mx_valu / PEAK_FP32_VALU,
                "list_build": (n_pt * 100 + (n - n_pt) * 50) / PEAK_HBM / 10,
                "integrator_outputs": n * 100 / PEAK_HBM}
     t_ideal = sum(t_parts.values())
@@ -568,8 +570,8 @@ def main():
     step_roofline = {"t_ideal_us": t_ideal * 1e6, "t_measured_us": t_step * 1e6, "frac": t_ideal / t_step,
                      "parts_us": {k: round(v * 1e6, 2) for k, v in t_parts.items()},
                      "note": "T_ideal / T_measured of one whole MD step (list rebuilds amortised), each stage "
-                             "at the bound of its algorithmic work (FP32 matrix 157.3, FP32 vector 78.6 "
-                             "TFLOP/s, HBM 8 TB/s)"}
+                             "at the bound of its algorithmic work (FP32 products at 2500 / 6, FP32 vector "
+                             "78.6 TFLOP/s, HBM 8 TB/s)"}
     stage_us = {k: round(ms / max(c, 1) * 1e3, 1) for k, (ms, c) in tm.items() if c}
     out = {
         "metric": METRIC,

@@ -63,7 +63,7 @@ extern "C" {
  * The variance d.Sigma.d is computed as |L^T d|^2 with the FP64 Cholesky factor L of each
  * Sigma block, a sum of squares, whenever all Sigma blocks are positive definite (the split
  * forms require it; the FP32 form falls back to the full matrix otherwise): in the FP32
- * form with L rounded to FP32 on FP32 matrix cores, in the split forms (all rows) with L in
+ * form with L rounded to FP32 and FP32-accurate products, in the split forms (all rows) with L in
  * FP64 on the FP64 matrix cores, FP64 sums and an FP64 division by |d~|^2, so that a
  * near-cancelling variance (an environment close to the sparse set of Eq. 2) keeps FP64
  * accuracy in the form and only the FP32 rounding of the descriptors remains. Norms and
@@ -161,8 +161,8 @@ int flare_descriptor_dim(const flare_model* model, int* n_d);
  * first flare_virial (its task sums; flare_virial_noalloc allocates nothing).
  * flare_memory_bytes reports the total. One state serves one stream; calls on one state
  * must not overlap. The state also creates one internal stream (default priority, on the
- * current device) and two events: with forces, the 544-wide rows run on it beside the
- * single-species kernel, forked from and joined back into the caller's stream inside the
+ * current device) and two events: with forces, unless the rows are few, the 544-wide rows run
+ * on it beside the single-species kernel, forked from and joined back into the caller's stream inside the
  * call, so the caller's stream alone orders every result, as with one stream.
  */
 int flare_state_create(flare_state** out, const flare_model* model, int max_atoms,
