@@ -27,7 +27,7 @@ class _EnergyFn(torch.autograd.Function):
         ctx.module = module
         ctx.gen = module._gen
         ctx.save_for_backward(pos)
-        return out["E"].clone()
+        return out["E"]                # of this call alone
 
     @staticmethod
     @once_differentiable

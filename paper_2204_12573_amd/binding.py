@@ -104,6 +104,14 @@ def ptr(t):
     return t.ctypes.data
 
 
+def row_ptrs(t):
+    """Addresses of the three rows of a [3, N] array (those of t[0], t[1], t[2])."""
+    if type(t) is torch.Tensor and t.dim() == 2 and t.shape[0] >= 3 and t.shape[1]:
+        base, step = t.data_ptr(), t.stride(0) * t.element_size()
+        return base, base + step, base + 2 * step
+    return ptr(t[0]), ptr(t[1]), ptr(t[2])
+
+
 def stream_handle(stream=None):
     s = stream if stream is not None else torch.cuda.current_stream()
     return s.cuda_stream

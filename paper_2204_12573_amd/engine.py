@@ -5,6 +5,7 @@ owns torch tensors (device memory), orders the calls and converts arguments.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 
 import numpy as np
@@ -13,6 +14,7 @@ import torch
 from . import binding as B
 
 MASSES = np.array([1.008, 195.084])   # amu, H and Pt
+_HERE = contextlib.nullcontext()
 
 
 class Model:
@@ -79,6 +81,7 @@ class Evaluator:
         self.model = model
         self.device = torch.device(device)
         self.stream = stream if stream is not None else torch.cuda.current_stream(self.device)
+        self._index = self.stream.device.index
         h = ctypes.c_void_p()
         B.check(self.lib.flare_state_create(ctypes.byref(h), model.handle, int(max_atoms),
                                             int(max_pairs), ctypes.c_void_p(self.stream.cuda_stream)))
@@ -87,6 +90,12 @@ class Evaluator:
         self.max_pairs = max_pairs
         self.n = 0
         self.n_struct = 0
+
+    def _on_device(self):
+        """The context of a call into the library: the state's device as the current one. The
+        calls enqueue on the state's own stream whatever torch's current stream is, so only the
+        device matters, and mostly it is current already (torch.cuda.stream took 6.7 us a call)."""
+        return _HERE if torch.cuda.current_device() == self._index else torch.cuda.device(self._index)
 
     def __del__(self):
         if getattr(self, "handle", None):
@@ -99,10 +108,9 @@ class Evaluator:
         offsets = np.ascontiguousarray(offsets, dtype=np.int32)
         boxes = np.ascontiguousarray(boxes, dtype=np.float64).reshape(-1, 3)
         n = pos.shape[1]
-        with torch.cuda.stream(self.stream):
-            B.check(self.lib.flare_neighbors(self.handle, n, B.ptr(pos[0]), B.ptr(pos[1]), B.ptr(pos[2]),
-                                             B.ptr(species), len(boxes), B.ptr(offsets), B.ptr(boxes),
-                                             float(skin)))
+        with self._on_device():
+            B.check(self.lib.flare_neighbors(self.handle, n, *B.row_ptrs(pos), B.ptr(species), len(boxes),
+                                             B.ptr(offsets), B.ptr(boxes), float(skin)))
         self.n = n
         self.n_struct = len(boxes)
         self.species = species
@@ -125,16 +133,14 @@ class Evaluator:
     def descriptors(self, pos, want_d=False, want_norm=False):
         d = torch.empty((self.n, self.model.n_desc), dtype=torch.float32, device=self.device) if want_d else None
         nrm = torch.empty(self.n, dtype=torch.float32, device=self.device) if want_norm else None
-        with torch.cuda.stream(self.stream):
-            B.check(self.lib.flare_descriptors(self.handle, B.ptr(pos[0]), B.ptr(pos[1]), B.ptr(pos[2]),
-                                               B.ptr(d), B.ptr(nrm)))
+        with self._on_device():
+            B.check(self.lib.flare_descriptors(self.handle, *B.row_ptrs(pos), B.ptr(d), B.ptr(nrm)))
         return d, nrm
 
     def energy_forces(self, out=None, want_var=False):
         out = self._outputs(out, want_var)
-        with torch.cuda.stream(self.stream):
-            B.check(self.lib.flare_energy_forces(self.handle, B.ptr(out["e"]), B.ptr(out["f"][0]),
-                                                 B.ptr(out["f"][1]), B.ptr(out["f"][2]), B.ptr(out["E"]),
+        with self._on_device():
+            B.check(self.lib.flare_energy_forces(self.handle, B.ptr(out["e"]), *B.row_ptrs(out["f"]), B.ptr(out["E"]),
                                                  B.ptr(out.get("var")), B.ptr(out.get("sigma"))))
         return out
 
@@ -142,12 +148,16 @@ class Evaluator:
         """Energies (and variances) without forces; the gradients stay resident."""
         out = {} if out is None else out
         dev = self.device
-        out.setdefault("e", torch.empty(self.n, dtype=torch.float32, device=dev))
-        out.setdefault("E", torch.empty(self.n_struct, dtype=torch.float64, device=dev))
+        if "e" not in out:
+            out["e"] = torch.empty(self.n, dtype=torch.float32, device=dev)
+        if "E" not in out:
+            out["E"] = torch.empty(self.n_struct, dtype=torch.float64, device=dev)
         if want_var:
-            out.setdefault("var", torch.empty(self.n, dtype=torch.float32, device=dev))
-            out.setdefault("sigma", torch.empty(self.n, dtype=torch.float32, device=dev))
-        with torch.cuda.stream(self.stream):
+            if "var" not in out:
+                out["var"] = torch.empty(self.n, dtype=torch.float32, device=dev)
+            if "sigma" not in out:
+                out["sigma"] = torch.empty(self.n, dtype=torch.float32, device=dev)
+        with self._on_device():
             B.check(self.lib.flare_energy_forces(self.handle, B.ptr(out["e"]), None, None, None, B.ptr(out["E"]),
                                                  B.ptr(out.get("var")), B.ptr(out.get("sigma"))))
         return out
@@ -155,21 +165,21 @@ class Evaluator:
     def forces(self, cell_scale=None, f=None):
         """Forces of the last energies() / energy_forces() positions, optionally scaled per cell."""
         f = torch.empty((3, self.n), dtype=torch.float32, device=self.device) if f is None else f
-        with torch.cuda.stream(self.stream):
-            B.check(self.lib.flare_forces(self.handle, B.ptr(cell_scale), B.ptr(f[0]), B.ptr(f[1]), B.ptr(f[2])))
+        with self._on_device():
+            B.check(self.lib.flare_forces(self.handle, B.ptr(cell_scale), *B.row_ptrs(f)))
         return f
 
     def virial(self, out=None):
         """Per-cell virial W = -dE/d(strain), [n_struct, 3, 3] FP64, from the last forces."""
         out = torch.empty((self.n_struct, 3, 3), dtype=torch.float64, device=self.device) if out is None else out
-        with torch.cuda.stream(self.stream):
+        with self._on_device():
             B.check(self.lib.flare_virial(self.handle, B.ptr(out)))
         return out
 
     def virial_noalloc(self, out):
         """As virial(), through the allocation-free entry point; `out` is a device FP64
         [n_struct, 3, 3] tensor (the call allocates nothing)."""
-        with torch.cuda.stream(self.stream):
+        with self._on_device():
             B.check(self.lib.flare_virial_noalloc(self.handle, B.ptr(out)))
         return out
 
@@ -182,10 +192,13 @@ class Evaluator:
     def variance(self, out=None):
         out = out or {}
         dev = self.device
-        out.setdefault("var", torch.empty(self.n, dtype=torch.float32, device=dev))
-        out.setdefault("sigma", torch.empty(self.n, dtype=torch.float32, device=dev))
-        out.setdefault("sigma_max", torch.empty(self.n_struct, dtype=torch.float32, device=dev))
-        with torch.cuda.stream(self.stream):
+        if "var" not in out:
+            out["var"] = torch.empty(self.n, dtype=torch.float32, device=dev)
+        if "sigma" not in out:
+            out["sigma"] = torch.empty(self.n, dtype=torch.float32, device=dev)
+        if "sigma_max" not in out:
+            out["sigma_max"] = torch.empty(self.n_struct, dtype=torch.float32, device=dev)
+        with self._on_device():
             B.check(self.lib.flare_variance(self.handle, B.ptr(out["var"]), B.ptr(out["sigma"]),
                                             B.ptr(out["sigma_max"])))
         return out
@@ -218,43 +231,44 @@ class Evaluator:
     def uncertainty_monitor(self, threshold, sigma_max_run, over_count):
         """Per-cell running max of sigma and count of evaluations above `threshold`
         (device FP32 / int32 [n_struct], updated in place) for the staged positions."""
-        with torch.cuda.stream(self.stream):
+        with self._on_device():
             B.check(self.lib.flare_uncertainty_monitor(self.handle, float(threshold), B.ptr(sigma_max_run),
                                                        B.ptr(over_count)))
 
     def _outputs(self, out, want_var):
         out = {} if out is None else out
         dev = self.device
-        out.setdefault("e", torch.empty(self.n, dtype=torch.float32, device=dev))
-        out.setdefault("f", torch.empty((3, self.n), dtype=torch.float32, device=dev))
-        out.setdefault("E", torch.empty(self.n_struct, dtype=torch.float64, device=dev))
+        if "e" not in out:
+            out["e"] = torch.empty(self.n, dtype=torch.float32, device=dev)
+        if "f" not in out:
+            out["f"] = torch.empty((3, self.n), dtype=torch.float32, device=dev)
+        if "E" not in out:
+            out["E"] = torch.empty(self.n_struct, dtype=torch.float64, device=dev)
         if want_var:
-            out.setdefault("var", torch.empty(self.n, dtype=torch.float32, device=dev))
-            out.setdefault("sigma", torch.empty(self.n, dtype=torch.float32, device=dev))
+            if "var" not in out:
+                out["var"] = torch.empty(self.n, dtype=torch.float32, device=dev)
+            if "sigma" not in out:
+                out["sigma"] = torch.empty(self.n, dtype=torch.float32, device=dev)
         return out
 
     # ---- integrator ----
     def md_first_half(self, pos, vel, f, dt):
-        with torch.cuda.stream(self.stream):
-            B.check(self.lib.flare_md_first_half(self.handle, B.ptr(pos[0]), B.ptr(pos[1]), B.ptr(pos[2]),
-                                                 B.ptr(vel[0]), B.ptr(vel[1]), B.ptr(vel[2]), B.ptr(f[0]),
-                                                 B.ptr(f[1]), B.ptr(f[2]), B.ptr(self.species),
-                                                 B.ptr(MASSES), float(dt)))
+        with self._on_device():
+            B.check(self.lib.flare_md_first_half(self.handle, *B.row_ptrs(pos), *B.row_ptrs(vel), *B.row_ptrs(f),
+                                                 B.ptr(self.species), B.ptr(MASSES), float(dt)))
 
     def md_second_half(self, vel, f, dt):
-        with torch.cuda.stream(self.stream):
-            B.check(self.lib.flare_md_second_half(self.handle, B.ptr(vel[0]), B.ptr(vel[1]), B.ptr(vel[2]),
-                                                  B.ptr(f[0]), B.ptr(f[1]), B.ptr(f[2]), B.ptr(self.species),
-                                                  B.ptr(MASSES), float(dt)))
+        with self._on_device():
+            B.check(self.lib.flare_md_second_half(self.handle, *B.row_ptrs(vel), *B.row_ptrs(f),
+                                                  B.ptr(self.species), B.ptr(MASSES), float(dt)))
 
     def md_step(self, pos, vel, out, dt, rebuild, want_var=True):
         """One NVE step in one call (flare_md_step): out["f"] holds the forces at the current
         positions on entry and at the new ones on return; e, E (and var, sigma) are refreshed."""
         f = out["f"]
-        with torch.cuda.stream(self.stream):
+        with self._on_device():
             B.check(self.lib.flare_md_step(
-                self.handle, B.ptr(pos[0]), B.ptr(pos[1]), B.ptr(pos[2]), B.ptr(vel[0]), B.ptr(vel[1]),
-                B.ptr(vel[2]), B.ptr(f[0]), B.ptr(f[1]), B.ptr(f[2]), B.ptr(self.species), B.ptr(MASSES),
+                self.handle, *B.row_ptrs(pos), *B.row_ptrs(vel), *B.row_ptrs(f), B.ptr(self.species), B.ptr(MASSES),
                 float(dt), 1 if rebuild else 0, B.ptr(out["e"]), B.ptr(out["E"]),
                 B.ptr(out["var"]) if want_var else None, B.ptr(out["sigma"]) if want_var else None))
 
@@ -266,23 +280,21 @@ class Evaluator:
         return thermo
 
     def kinetic(self, vel, thermo):
-        with torch.cuda.stream(self.stream):
-            B.check(self.lib.flare_kinetic(self.handle, B.ptr(vel[0]), B.ptr(vel[1]), B.ptr(vel[2]),
-                                           B.ptr(self.species), B.ptr(MASSES), B.ptr(thermo)))
+        with self._on_device():
+            B.check(self.lib.flare_kinetic(self.handle, *B.row_ptrs(vel), B.ptr(self.species), B.ptr(MASSES),
+                                           B.ptr(thermo)))
 
     def nvt_first_half(self, pos, vel, f, dt, t_target, tau, thermo):
-        with torch.cuda.stream(self.stream):
-            B.check(self.lib.flare_nvt_first_half(self.handle, B.ptr(pos[0]), B.ptr(pos[1]), B.ptr(pos[2]),
-                                                  B.ptr(vel[0]), B.ptr(vel[1]), B.ptr(vel[2]), B.ptr(f[0]),
-                                                  B.ptr(f[1]), B.ptr(f[2]), B.ptr(self.species), B.ptr(MASSES),
-                                                  float(dt), float(t_target), float(tau), B.ptr(thermo)))
+        with self._on_device():
+            B.check(self.lib.flare_nvt_first_half(self.handle, *B.row_ptrs(pos), *B.row_ptrs(vel), *B.row_ptrs(f),
+                                                  B.ptr(self.species), B.ptr(MASSES), float(dt), float(t_target),
+                                                  float(tau), B.ptr(thermo)))
 
     def nvt_second_half(self, vel, f, dt, t_target, tau, thermo):
-        with torch.cuda.stream(self.stream):
-            B.check(self.lib.flare_nvt_second_half(self.handle, B.ptr(vel[0]), B.ptr(vel[1]), B.ptr(vel[2]),
-                                                   B.ptr(f[0]), B.ptr(f[1]), B.ptr(f[2]), B.ptr(self.species),
-                                                   B.ptr(MASSES), float(dt), float(t_target), float(tau),
-                                                   B.ptr(thermo)))
+        with self._on_device():
+            B.check(self.lib.flare_nvt_second_half(self.handle, *B.row_ptrs(vel), *B.row_ptrs(f),
+                                                   B.ptr(self.species), B.ptr(MASSES), float(dt), float(t_target),
+                                                   float(tau), B.ptr(thermo)))
 
     def quadratic_forms(self, bucket, d_rows):
         """e = d^T beta d and V = d^T Sigma d of given FP32 vectors (device [n, 144 or 544])
@@ -291,7 +303,7 @@ class Evaluator:
         n = d_rows.shape[0]
         e = torch.empty(n, dtype=torch.float32, device=self.device)
         v = torch.empty(n, dtype=torch.float32, device=self.device)
-        with torch.cuda.stream(self.stream):
+        with self._on_device():
             B.check(self.lib.flare_quadratic_forms(self.handle, int(bucket), n, B.ptr(d_rows), B.ptr(e), B.ptr(v)))
         return e, v
 
@@ -301,9 +313,9 @@ class Evaluator:
         recombination) counts per cell."""
         coord = torch.empty(self.n, dtype=torch.int32, device=self.device)
         events = torch.zeros((self.n_struct, 2), dtype=torch.int64, device=self.device) if prev is not None else None
-        with torch.cuda.stream(self.stream):
-            B.check(self.lib.flare_coordination(self.handle, B.ptr(pos[0]), B.ptr(pos[1]), B.ptr(pos[2]),
-                                                B.ptr(coord), B.ptr(prev), B.ptr(events)))
+        with self._on_device():
+            B.check(self.lib.flare_coordination(self.handle, *B.row_ptrs(pos), B.ptr(coord), B.ptr(prev),
+                                                B.ptr(events)))
         return coord, events
 
 
