@@ -49,17 +49,27 @@ __device__ inline int floor_div(int u, int n) { return u >= 0 ? u / n : -((-u + 
 
 // Caller order: wrap into the cell, bin, one 64-byte record per atom, bin counts; the
 // positions themselves are kept (xb) as the reference of the per-step displacements.
-__global__ __launch_bounds__(NT) void k_wrap_bin(int n, const double* __restrict__ x,
-                                                 const double* __restrict__ y,
-                                                 const double* __restrict__ z,
-                                                 const int32_t* __restrict__ species,
-                                                 const int* __restrict__ cell_off, int n_cell,
-                                                 const CellGrid* __restrict__ grids,
-                                                 CallerRec* __restrict__ rec, double* __restrict__ xb,
-                                                 int* __restrict__ bin_count, int* __restrict__ status) {
+struct WrapArgs {
+  int n;
+  const double *x, *y, *z;
+  const int32_t* species;
+  const int* cell_off;
+  int n_cell;
+  const CellGrid* grids;
+  CallerRec* rec;
+  double* xb;
+  int* status;
+};
+__device__ __forceinline__ int wrap_atom(const WrapArgs& q, int a) {
 #pragma clang fp contract(off)
-  const int a = blockIdx.x * NT + threadIdx.x;
-  if (a >= n) return;
+  const int n = q.n, n_cell = q.n_cell;
+  const int* __restrict__ cell_off = q.cell_off;
+  const CellGrid* __restrict__ grids = q.grids;
+  const double *__restrict__ x = q.x, *__restrict__ y = q.y, *__restrict__ z = q.z;
+  const int32_t* __restrict__ species = q.species;
+  CallerRec* __restrict__ rec = q.rec;
+  double* __restrict__ xb = q.xb;
+  int* __restrict__ status = q.status;
   int lo = 0, hi = n_cell - 1;
   while (lo < hi) {
     int mid = (lo + hi + 1) >> 1;
@@ -101,7 +111,11 @@ __global__ __launch_bounds__(NT) void k_wrap_bin(int n, const double* __restrict
   xb[a] = p[0];
   xb[(size_t)n + a] = p[1];
   xb[2 * (size_t)n + a] = p[2];
-  atomicAdd(&bin_count[r.bin], 1);
+  return r.bin;
+}
+__global__ __launch_bounds__(NT) void k_wrap_bin(WrapArgs q, int* __restrict__ bin_count) {
+  const int a = blockIdx.x * NT + threadIdx.x;
+  if (a < q.n) atomicAdd(&bin_count[wrap_atom(q, a)], 1);
 }
 
 __global__ __launch_bounds__(NT) void k_bin_scatter(int n, const CallerRec* __restrict__ rec,
@@ -118,34 +132,40 @@ __global__ __launch_bounds__(NT) void k_bin_scatter(int n, const CallerRec* __re
 // atom's place is the number of smaller indices among its bin's atoms). One caller record (a
 // 64-byte line) per atom; the species rides in w.w, so that a neighbour's position and
 // species are one load.
-__global__ __launch_bounds__(NT) void k_to_internal(int n, const int* __restrict__ sorted,
-                                                    const int* __restrict__ start,
-                                                    const CallerRec* __restrict__ rec,
-                                                    const int32_t* __restrict__ species,
-                                                    int* __restrict__ perm, int* __restrict__ inv_perm,
-                                                    int* __restrict__ sp,
-                                                    int* __restrict__ sid, int* __restrict__ bin,
-                                                    double4* __restrict__ w, float4* __restrict__ wf,
-                                                    double* __restrict__ off) {
+struct InternalArgs {
+  int n;
+  const CallerRec* rec;
+  const int32_t* species;
+  int *perm, *inv_perm, *sp, *sid, *bin;
+  double4* w;
+  float4* wf;
+  double* off;
+};
+__device__ __forceinline__ void place_atom(const InternalArgs& q, int a, const CallerRec& r, int i) {
+  const int n = q.n;
+  q.perm[i] = a;
+  q.inv_perm[a] = i;
+  const int s = q.species[a];
+  const int sc = (s < 0 || s >= NS) ? 0 : s;
+  q.sp[i] = sc;
+  q.sid[i] = r.cell;
+  q.bin[i] = r.bin;
+  q.w[i] = make_double4(r.wx, r.wy, r.wz, (double)sc);
+  q.wf[i] = make_float4((float)r.wx, (float)r.wy, (float)r.wz, (float)sc);
+  q.off[i] = r.ox;
+  q.off[(size_t)n + i] = r.oy;
+  q.off[2 * (size_t)n + i] = r.oz;
+}
+__global__ __launch_bounds__(NT) void k_to_internal(InternalArgs q, const int* __restrict__ sorted,
+                                                    const int* __restrict__ start) {
   const int t = blockIdx.x * NT + threadIdx.x;
-  if (t >= n) return;
+  if (t >= q.n) return;
   const int a = sorted[t];
-  const CallerRec r = rec[a];
+  const CallerRec r = q.rec[a];
   const int lo = start[r.bin], hi = start[r.bin + 1];
   int i = lo;
   for (int k = lo; k < hi; ++k) i += sorted[k] < a ? 1 : 0;
-  perm[i] = a;
-  inv_perm[a] = i;
-  const int s = species[a];
-  const int sc = (s < 0 || s >= NS) ? 0 : s;
-  sp[i] = sc;
-  sid[i] = r.cell;
-  bin[i] = r.bin;
-  w[i] = make_double4(r.wx, r.wy, r.wz, (double)sc);
-  wf[i] = make_float4((float)r.wx, (float)r.wy, (float)r.wz, (float)sc);
-  off[i] = r.ox;
-  off[(size_t)n + i] = r.oy;
-  off[2 * (size_t)n + i] = r.oz;
+  place_atom(q, a, r, i);
 }
 
 // Row order inside a bucket: by neighbour count, largest first (counts of NCK - 1 and more
@@ -598,22 +618,29 @@ __global__ __launch_bounds__(NT) void k_rows(int row_max, int nrows, const int* 
 
 // Row of every atom in caller order and the slot of its first pair in internal order (-1:
 // no listed pair, no row); the first work-item also records the slots of the build.
-__global__ __launch_bounds__(NT) void k_atom_rows(int n, const int* __restrict__ bucket,
-                                                  const int* __restrict__ row_of, int* __restrict__ layout,
-                                                  const int* __restrict__ perm, const int* __restrict__ slice_base,
-                                                  int slice_max, long long slot_cap,
-                                                  int* __restrict__ row_caller, int* __restrict__ slot0) {
+struct AtomRowArgs {
+  int n;
+  const int *bucket, *row_of;
+  int* layout;
+  const int* perm;
+  int slice_max;
+  long long slot_cap;
+  int *row_caller, *slot0;
+};
+__device__ __forceinline__ void slots_total(const AtomRowArgs& q, int groups) {
+  q.layout[LY_SLOTS32] = groups;
+  if ((long long)groups * 32 > q.slot_cap) q.layout[LY_FLAGS] |= 2;
+}
+__device__ __forceinline__ void atom_row(const AtomRowArgs& q, int i, const int* slice_base) {
+  const int b = q.bucket[i];
+  const int R = b < 0 ? -1 : global_row(b, q.row_of[i], q.layout[LY_ROWS1]);
+  q.row_caller[q.perm[i]] = R;
+  q.slot0[i] = R < 0 ? -1 : slot_of(slice_base, R, 0);
+}
+__global__ __launch_bounds__(NT) void k_atom_rows(AtomRowArgs q, const int* __restrict__ slice_base) {
   const int i = blockIdx.x * NT + threadIdx.x;
-  if (i == 0) {
-    const int groups = slice_base[slice_max];
-    layout[LY_SLOTS32] = groups;
-    if ((long long)groups * 32 > slot_cap) layout[LY_FLAGS] |= 2;
-  }
-  if (i >= n) return;
-  const int b = bucket[i];
-  const int R = b < 0 ? -1 : global_row(b, row_of[i], layout[LY_ROWS1]);
-  row_caller[perm[i]] = R;
-  slot0[i] = R < 0 ? -1 : slot_of(slice_base, R, 0);
+  if (i == 0) slots_total(q, slice_base[q.slice_max]);
+  if (i < q.n) atom_row(q, i, slice_base);
 }
 
 // The sliced pair layout in one pass, a work-group per 32-row slice: thread (h, l) of 8 x 32
@@ -692,8 +719,7 @@ struct ClearArgs {
   int* status;    // [0] the caller-visible word, [1] the build's; the layout record follows
   int* layout;
 };
-__global__ __launch_bounds__(NT) void k_clear(ClearArgs a) {
-  const long long t = (long long)blockIdx.x * NT + threadIdx.x;
+__device__ __forceinline__ void clear_all(const ClearArgs& a, long long t, long long stride) {
   if (t == 0) {
     // the caller-visible status word moves to the layout record (read by the host at the end
     // of the build) and is cleared: no flag of the ended interval is lost
@@ -702,7 +728,6 @@ __global__ __launch_bounds__(NT) void k_clear(ClearArgs a) {
     a.status[0] = 0;
     a.status[1] = 0;
   }
-  const long long stride = (long long)gridDim.x * NT;
   for (int k = 0; k < a.nseg; ++k) {
     int* __restrict__ p = a.seg[k].p;
     const long long n = a.seg[k].n;
@@ -710,6 +735,102 @@ __global__ __launch_bounds__(NT) void k_clear(ClearArgs a) {
     for (long long i = t; i < n; i += stride) p[i] = v;
   }
 }
+__global__ __launch_bounds__(NT) void k_clear(ClearArgs a) {
+  clear_all(a, (long long)blockIdx.x * NT + threadIdx.x, (long long)gridDim.x * NT);
+}
+
+// Builds of up to ONE_ATOMS atoms and ONE_BINS bins (what LDS holds beside the order): the passes that need little more than a
+// launch each run as phases of one work-group, with bin counts and the bin order in LDS. k_first:
+// the fills, wrap and bin, scan, scatter, internal order (five launches); k_last_rows: the slice
+// scan and the atoms' rows (two). Each launch taken out is 3 us of the stream and as much of the
+// host's time; one CU pays for it with about 10 us a thousand atoms. A whole build in us, general
+// passes -> here: 72 atoms 85 -> 60, 540 85 -> 66, 1,215 86 -> 73, 1,980 86 -> 80, but 3,024
+// 86 -> 90, 4,032 88 -> 102.
+constexpr int NT1 = 1024;
+constexpr int ONE_ATOMS = 2048, ONE_BINS = 8192, ONE_PER = ONE_ATOMS / NT1;
+
+// Exclusive prefix of one value a thread over the work-group; total: the sum over all.
+__device__ __forceinline__ int group_scan(int v, int* wsum, int& total) {
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  int incl = v;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int t = __shfl_up(incl, d, 64);
+    if (lane >= d) incl += t;
+  }
+  if (lane == 63) wsum[w] = incl;
+  __syncthreads();
+  int before = 0;
+  total = 0;
+  for (int k = 0; k < NT1 / 64; ++k) {
+    if (k < w) before += wsum[k];
+    total += wsum[k];
+  }
+  return before + incl - v;
+}
+
+__global__ __launch_bounds__(NT1) void k_first(ClearArgs c, WrapArgs q, InternalArgs o, int nbins,
+                                               int* __restrict__ bin_start) {
+  __shared__ int start[ONE_BINS];       // counts, then first places, then (scattered) ends
+  __shared__ int sorted[ONE_ATOMS];
+  __shared__ int wsum[NT1 / 64];
+  const int t = threadIdx.x;
+  clear_all(c, t, NT1);
+  for (int b = t; b < nbins; b += NT1) start[b] = 0;
+  __syncthreads();
+  int bin[ONE_PER];
+#pragma unroll
+  for (int u = 0; u < ONE_PER; ++u) {
+    const int a = u * NT1 + t;
+    bin[u] = a < q.n ? wrap_atom(q, a) : -1;
+    if (bin[u] >= 0) atomicAdd(&start[bin[u]], 1);
+  }
+  __syncthreads();
+  const int per = (nbins + NT1 - 1) / NT1, base = t * per;
+  int sum = 0, total;
+  for (int k = base; k < min(base + per, nbins); ++k) sum += start[k];
+  int run = group_scan(sum, wsum, total);
+  for (int k = base; k < min(base + per, nbins); ++k) {
+    const int m = start[k];
+    start[k] = run;
+    bin_start[k] = run;
+    run += m;
+  }
+  if (t == 0) bin_start[nbins] = total;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < ONE_PER; ++u)
+    if (bin[u] >= 0) sorted[atomicAdd(&start[bin[u]], 1)] = u * NT1 + t;
+  __syncthreads();
+  // inside a bin by caller index (the scatter order is racy), as in k_to_internal
+#pragma unroll
+  for (int u = 0; u < ONE_PER; ++u) {
+    if (bin[u] < 0) continue;
+    const int a = u * NT1 + t;
+    const int lo = bin[u] > 0 ? start[bin[u] - 1] : 0, hi = start[bin[u]];
+    int i = lo;
+    for (int k = lo; k < hi; ++k) i += sorted[k] < a ? 1 : 0;
+    place_atom(o, a, q.rec[a], i);
+  }
+}
+
+__global__ __launch_bounds__(NT1) void k_last_rows(AtomRowArgs q, const int* __restrict__ slice_len,
+                                                   int* __restrict__ slice_base) {
+  __shared__ int base[NT1];
+  __shared__ int wsum[NT1 / 64];
+  const int t = threadIdx.x;
+  int total;
+  const int first = group_scan(t < q.slice_max ? slice_len[t] : 0, wsum, total);
+  base[t] = first;
+  if (t < q.slice_max) slice_base[t] = first;
+  if (t == 0) {
+    slice_base[q.slice_max] = total;
+    slots_total(q, total);
+  }
+  __syncthreads();
+  for (int i = t; i < q.n; i += NT1) atom_row(q, i, base);
+}
+static_assert((ONE_ATOMS + NBUCKET * TILE_ROWS + 31) / 32 <= NT1, "a slice a thread");
 
 inline int grid_of(long long n) { return (int)((n + NT - 1) / NT); }
 
@@ -771,6 +892,9 @@ int build_list(flare_state* s, const double* x, const double* y, const double* z
   // rows of this many atoms: every bucket's padding included
   const int row_max = std::min(s->row_cap, (n + NBUCKET * TILE_ROWS + 31) / 32 * 32);
   const int slice_max = row_max / 32;
+  const bool one = n > 0 && n <= ONE_ATOMS && nbins <= ONE_BINS;
+  const WrapArgs wq{n, x, y, z, species, s->d_struct_off, nc, s->d_grids, s->crec, s->xb, bst};
+  const InternalArgs io{n, s->crec, species, s->perm, s->inv_perm, s->sp, s->sid, s->bin, s->w, s->wf, s->off};
   {
     // everything the build starts from: its status word and layout record, the bin and key
     // counters, no atom in any row, zero energies, variances and norms (atoms without a
@@ -779,8 +903,10 @@ int build_list(flare_state* s, const double* x, const double* y, const double* z
     c.status = s->d_status;
     c.layout = s->d_layout;
     auto seg = [&](int* p, long long cnt, int v) { c.seg[c.nseg++] = ClearSeg{p, cnt, v}; };
-    seg(s->bin_count, (long long)nbins + 1, 0);
-    seg(s->bin_fill, (long long)nbins + 1, 0);
+    if (!one) {
+      seg(s->bin_count, (long long)nbins + 1, 0);
+      seg(s->bin_fill, (long long)nbins + 1, 0);
+    }
     if (n <= FEW_ATOMS) seg(s->blk_bucket, (long long)NKEY * nblk, 0);
     seg(s->atom_of_row1, row_max, -1);
     seg(s->atom_of_rowx, row_max, -1);
@@ -789,16 +915,16 @@ int build_list(flare_state* s, const double* x, const double* y, const double* z
     seg(reinterpret_cast<int*>(s->nrm), n, 0);
     long long longest = 1;
     for (int k = 0; k < c.nseg; ++k) longest = std::max(longest, c.seg[k].n);
-    k_clear<<<(int)std::min<long long>(grid_of(longest), 2048), NT, 0, st>>>(c);
+    if (one) k_first<<<1, NT1, 0, st>>>(c, wq, io, nbins, s->bin_start);
+    else k_clear<<<(int)std::min<long long>(grid_of(longest), 2048), NT, 0, st>>>(c);
   }
-  if (n > 0)
-    k_wrap_bin<<<grid_of(n), NT, 0, st>>>(n, x, y, z, species, s->d_struct_off, nc, s->d_grids, s->crec, s->xb,
-                                          s->bin_count, bst);
-  scan_exclusive(s->bin_count, s->bin_start, nbins, s->scan_scratch, st);
-  if (n > 0) {
-    k_bin_scatter<<<grid_of(n), NT, 0, st>>>(n, s->crec, s->bin_start, s->bin_fill, s->sorted);
-    k_to_internal<<<grid_of(n), NT, 0, st>>>(n, s->sorted, s->bin_start, s->crec, species, s->perm, s->inv_perm,
-                                             s->sp, s->sid, s->bin, s->w, s->wf, s->off);
+  if (!one) {
+    if (n > 0) k_wrap_bin<<<grid_of(n), NT, 0, st>>>(wq, s->bin_count);
+    scan_exclusive(s->bin_count, s->bin_start, nbins, s->scan_scratch, st);
+    if (n > 0) {
+      k_bin_scatter<<<grid_of(n), NT, 0, st>>>(n, s->crec, s->bin_start, s->bin_fill, s->sorted);
+      k_to_internal<<<grid_of(n), NT, 0, st>>>(io, s->sorted, s->bin_start);
+    }
   }
   const double rl2 = s->r_list * s->r_list;
   // Band of the FP32 first test. Wrapped coordinates lie in [0, W] (W the largest box side),
@@ -836,9 +962,13 @@ int build_list(flare_state* s, const double* x, const double* y, const double* z
   k_rows<<<nrows + ngroup, NT, 0, st>>>(row_max, nrows, s->d_layout, bst, s->atom_of_row1, s->atom_of_rowx, s->nl_cnt,
                                        s->sid, s->cnt_row, s->sid_row, s->slice_len, n, s->nl_off, s->nl_j, s->nl_s,
                                        s->nl_rev);
-  scan_exclusive(s->slice_len, s->slice_base, slice_max, s->scan_scratch, st);
-  k_atom_rows<<<std::max(nblk, 1), NT, 0, st>>>(n, s->bucket, s->row_of, s->d_layout, s->perm, s->slice_base,
-                                                slice_max, s->slot_cap, s->row_caller, s->slot0);
+  const AtomRowArgs ar{n, s->bucket, s->row_of, s->d_layout, s->perm, slice_max, s->slot_cap, s->row_caller, s->slot0};
+  if (one) {
+    k_last_rows<<<1, NT1, 0, st>>>(ar, s->slice_len, s->slice_base);
+  } else {
+    scan_exclusive(s->slice_len, s->slice_base, slice_max, s->scan_scratch, st);
+    k_atom_rows<<<std::max(nblk, 1), NT, 0, st>>>(ar, s->slice_base);
+  }
   k_slots<<<slice_max, NT, 0, st>>>(s->d_layout, s->atom_of_row1, s->atom_of_rowx, s->nl_off, s->nl_j, s->nl_s,
                                     s->nl_rev, s->slot0, s->slice_base, s->w, s->sid, s->d_grids, s->slot_rev,
                                     s->slot_d0, bst);
