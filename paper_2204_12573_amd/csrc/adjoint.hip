@@ -15,7 +15,8 @@ namespace {
 constexpr int TA = 256;   // threads of the 144-row adjoint kernel (128 rows, 2 lanes each)
 
 // One row per lane pair (see half.h and adjoint.h), reading g from the tile-transposed
-// G[tile][k][128] written by the quadratic-form kernel.
+// G[tile][k][128] written by the quadratic-form kernel. FP8: the form's order of sums.
+template <bool FP8>
 __global__ __launch_bounds__(TA) void k_adjoint144(SlotView v, const int* __restrict__ atom_of_row,
                                                    const float* __restrict__ G, float4* __restrict__ f_own) {
   const int tile = xcd_remap(blockIdx.x, gridDim.x);
@@ -28,7 +29,7 @@ __global__ __launch_bounds__(TA) void k_adjoint144(SlotView v, const int* __rest
 #pragma unroll
     for (int q = 0; q < NQ; ++q) c[n][q] = 0.f;
   const int R = tile * 128 + rl;
-  accumulate_half(v, R, i, h, false, c);
+  accumulate_half<FP8>(v, R, i, h, false, c);
   u_transform_half(G + (size_t)tile * ND1 * 128 + rl, 128, h, c);
   adjoint_pairs_half(v, R, h, c, f_own);
 }
@@ -161,7 +162,9 @@ __global__ __launch_bounds__(MTHREADS) void k_adjoint_mixed(SlotView v, int rows
 void adjoint_rows144(flare_state* s) {
   const SlotView v = slot_view(s);
   StageTimer tm(s, FLARE_T_FORCE1);
-  if (s->rows1 > 0) k_adjoint144<<<s->rows1 / 128, TA, 0, s->stream>>>(v, s->atom_of_row1, s->G1, s->f_own);
+  if (s->rows1 == 0) return;
+  auto adjoint144 = s->model->precision == FLARE_FP8_SPLIT ? k_adjoint144<true> : k_adjoint144<false>;
+  adjoint144<<<s->rows1 / 128, TA, 0, s->stream>>>(v, s->atom_of_row1, s->G1, s->f_own);
 }
 
 void adjoint_mixed_chunk(flare_state* s, int r0, int nr, bool want_v) {

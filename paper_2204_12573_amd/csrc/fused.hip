@@ -548,18 +548,20 @@ struct RowScalars {
 
 // 1. descriptors of the tile's rows into the LDS tile (thread t of 256: row t/2, half t&1);
 // the densities are left in c for the adjoint phase of the same rows. With given
-// descriptors (D_in) the lane pair copies its row instead and c stays zero.
+// descriptors (D_in) the lane pair copies its row instead and c stays zero. The FP8 form has
+// its own order of sums (half.h).
 template <int PREC, bool GIVEN>
 __device__ __forceinline__ void desc_phase(const FusedArgs& a, float* As, const RowScalars& rs, int row0,
                                            int t, float (&c)[NR][NQ]) {
 #pragma clang fp contract(off)
+  constexpr bool FP8 = PREC == FLARE_FP8_SPLIT;
   const int rl = t >> 1, h = t & 1;
   const int i = atom_of<GIVEN>(a, row0 + rl);
 #pragma unroll
   for (int n = 0; n < NR; ++n)
 #pragma unroll
     for (int q = 0; q < NQ; ++q) c[n][q] = 0.f;
-  if (i >= 0 && !GIVEN) accumulate_half(a.v, row0 + rl, i, h, a.mode & 1, c);
+  if (i >= 0 && !GIVEN) accumulate_half<FP8>(a.v, row0 + rl, i, h, a.mode & 1, c);
   // one B2 pass: the unnormalised d~ goes into the tile; 1/|d~| is applied in the
   // epilogue (Y is linear in the row, so Y(d) = Y(d~)/|d~|)
   // |d~|^2: FP64 in the split forms (their norms stay FP64), FP32 in the FP32 form (144
@@ -595,7 +597,7 @@ __device__ __forceinline__ void desc_phase(const FusedArgs& a, float* As, const 
       for (int na = 0; na < NR; ++na) {
 #pragma unroll
         for (int nb = na; nb < NR; ++nb) {
-          const float2 mine = b2_half(c[na], c[nb], h);    // this lane's two components
+          const float2 mine = b2_half<FP8>(c[na], c[nb], h, nb == NR - 1);   // this lane's two components
           nrm2 += (NormT)fmaf(mine.x, mine.x, mine.y * mine.y);
           if (PREC == FLARE_FP8_SPLIT) amax = fmaxf(amax, fmaxf(fabsf(mine.x), fabsf(mine.y)));
           *reinterpret_cast<float2*>(rowp + 4 * k) = mine;
