@@ -76,6 +76,17 @@ __device__ __forceinline__ void desc_mixed_block(const MixedDescArgs& q, int blo
     }
   }
   nrm2 = sum16d(nrm2);                    // the row's 16 lanes form one DPP row
+  if (nrm2 < 0x1p-60) {
+    // a row whose only neighbours inside the cutoff are just inside it has components down to
+    // 1e-27, which FP32 holds, but not their squares: squared in FP64 (all 16 lanes together)
+    nrm2 = 0.0;
+#pragma unroll
+    for (int k = 0; k < NQP; ++k) {
+      const double d0 = d[k].x, d1 = d[k].y, d2 = d[k].z, d3 = d[k].w;
+      nrm2 += fma(d0, d0, d1 * d1) + fma(d2, d2, d3 * d3);
+    }
+    nrm2 = sum16d(nrm2);
+  }
   const float nrm = (float)sqrt(nrm2);
   const float scale = nrm > 0.f ? 1.f / nrm : 0.f;
   float4* out = reinterpret_cast<float4*>(q.D + (size_t)local * ND);
