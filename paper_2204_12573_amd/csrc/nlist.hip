@@ -859,10 +859,12 @@ int build_list(flare_state* s, const double* x, const double* y, const double* z
   // reduction tasks: contiguous internal ranges of one cell, at most 2048 atoms each (one
   // work-group per task); cell c owns tasks [first_task[c], first_task[c + 1])
   s->tasks.clear();
+  s->longest_task = 0;
   s->first_task.assign(nc + 1, 0);
   for (int c = 0; c < nc; ++c) {
     s->first_task[c] = (int)s->tasks.size();
     const int a = s->struct_off[c], b = s->struct_off[c + 1];
+    s->longest_task = std::max(s->longest_task, std::min(b - a, 2048));
     if (a == b) s->tasks.push_back({c, a, a});
     for (int k = a; k < b; k += 2048) s->tasks.push_back({c, k, std::min(b, k + 2048)});
   }

@@ -223,9 +223,11 @@ __global__ __launch_bounds__(NT) void k_outputs_atoms(OutArgs o) {
 // pairs; the reverse q of p has Delta_q = -Delta_p and w_in(slot p) = w_q, so relabelling the
 // sum gives W = sum_p Delta_p (x) w_in(slot p), which each atom forms from its own slots
 // (Delta = r u from the geometry). red_w [tasks][9] holds the task sums.
-// 1,024 threads a task, two atoms each: a task is one work-group, so a cell of a few thousand
-// atoms has few of them (256 threads of eight atoms each took 65 us for 7.7 k atoms).
-constexpr int NV = 1024;
+// An order of its own for every task, whatever the work-group's size: the atoms go in groups of
+// 64, group g taking atoms 64 g + 1024 k, one a lane; each 16 lanes are summed in a fixed tree,
+// and these sums in order.
+constexpr int VG = 16;                       // groups of a task
+template <int NV>
 __global__ __launch_bounds__(NV) void k_virial_tasks(const RedTask* __restrict__ tasks,
                                                      const int* __restrict__ bucket,
                                                      const int* __restrict__ row_of, int rows1,
@@ -234,56 +236,56 @@ __global__ __launch_bounds__(NV) void k_virial_tasks(const RedTask* __restrict__
                                                      const float4* __restrict__ w_in,
                                                      const int* __restrict__ cnt,
                                                      double* __restrict__ red_w) {
-  __shared__ double sw[NV / 64][9];
+  __shared__ double sw[VG * 4][9];
   const RedTask tk = tasks[blockIdx.x];
-  double acc[9];
+  const int groups = min(VG, (tk.end - tk.begin + 63) / 64);
+  for (int g = threadIdx.x >> 6; g < groups; g += NV / 64) {
+    double acc[9];
 #pragma unroll
-  for (int c = 0; c < 9; ++c) acc[c] = 0.0;
-  for (int i = tk.begin + threadIdx.x; i < tk.end; i += NV) {
-    const int b = bucket[i];
-    if (b < 0) continue;
-    const int R = b < 4 ? row_of[i] : rows1 + row_of[i];
-    const int base = slice_base[R >> 5], len = cnt[i];
-    float va[9];
+    for (int c = 0; c < 9; ++c) acc[c] = 0.0;
+    for (int i = tk.begin + g * 64 + (threadIdx.x & 63); i < tk.end; i += VG * 64) {
+      const int b = bucket[i];
+      if (b < 0) continue;
+      const int R = b < 4 ? row_of[i] : rows1 + row_of[i];
+      const int base = slice_base[R >> 5], len = cnt[i];
+      float va[9];
 #pragma unroll
-    for (int c = 0; c < 9; ++c) va[c] = 0.f;
-    const size_t s0 = (size_t)base * 32 + (R & 31);
-    for (int k0 = 0; k0 < len; k0 += 4) {
-      // four slots' loads together (past the list its last slot again, unused)
-      float4 gq[4], wq[4];
+      for (int c = 0; c < 9; ++c) va[c] = 0.f;
+      const size_t s0 = (size_t)base * 32 + (R & 31);
+      for (int k0 = 0; k0 < len; k0 += 4) {
+        // four slots' loads together (past the list its last slot again, unused)
+        float4 gq[4], wq[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const size_t slot = s0 + (size_t)min(k0 + u, len - 1) * 32;
-        gq[u] = geom[slot];
-        wq[u] = w_in[slot];
+        for (int u = 0; u < 4; ++u) {
+          const size_t slot = s0 + (size_t)min(k0 + u, len - 1) * 32;
+          gq[u] = geom[slot];
+          wq[u] = w_in[slot];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          if (k0 + u >= len) break;
+          const float r = fabsf(gq[u].w);      // 0 outside the cutoff: no contribution
+          const float d[3] = {r * gq[u].x, r * gq[u].y, r * gq[u].z};
+          const float ww[3] = {wq[u].x, wq[u].y, wq[u].z};
+#pragma unroll
+          for (int x = 0; x < 3; ++x)
+#pragma unroll
+            for (int y = 0; y < 3; ++y) va[3 * x + y] += d[x] * ww[y];
+        }
       }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (k0 + u >= len) break;
-        const float r = fabsf(gq[u].w);      // 0 outside the cutoff: no contribution
-        const float d[3] = {r * gq[u].x, r * gq[u].y, r * gq[u].z};
-        const float ww[3] = {wq[u].x, wq[u].y, wq[u].z};
-#pragma unroll
-        for (int x = 0; x < 3; ++x)
-#pragma unroll
-          for (int y = 0; y < 3; ++y) va[3 * x + y] += d[x] * ww[y];
-      }
+      for (int c = 0; c < 9; ++c) acc[c] += (double)va[c];
     }
 #pragma unroll
-    for (int c = 0; c < 9; ++c) acc[c] += (double)va[c];
+    for (int c = 0; c < 9; ++c) acc[c] = sum16d(acc[c]);
+    if ((threadIdx.x & 15) == 0)
+#pragma unroll
+      for (int c = 0; c < 9; ++c) sw[g * 4 + ((threadIdx.x >> 4) & 3)][c] = acc[c];
   }
-  // the wave's lanes in a fixed tree, then the waves in order
-#pragma unroll
-  for (int c = 0; c < 9; ++c)
-#pragma unroll
-    for (int h = 32; h > 0; h >>= 1) acc[c] += __shfl_down(acc[c], h, 64);
-  if ((threadIdx.x & 63) == 0)
-#pragma unroll
-    for (int c = 0; c < 9; ++c) sw[threadIdx.x >> 6][c] = acc[c];
   __syncthreads();
   if (threadIdx.x < 9) {
     double t = 0.0;
-    for (int w = 0; w < NV / 64; ++w) t += sw[w][threadIdx.x];
+    for (int k = 0; k < 4 * groups; ++k) t += sw[k][threadIdx.x];
     red_w[(size_t)blockIdx.x * 9 + threadIdx.x] = t;
   }
 }
@@ -448,9 +450,16 @@ void reduce_cells(flare_state* s, const Reduction& red) {
 
 void virial_cells(flare_state* s, double* virial_struct, double* red_w) {
   const int nt = (int)s->tasks.size();
+  // as many threads as the longest task has atoms, up to 1,024: a task is one work-group, so a
+  // cell of a few thousand atoms has few of them (7.7 k atoms: 46 us with 256 threads, 30 with
+  // 1,024; 100 cells of 800: 28 and 14), and a batch of small cells has many nearly empty ones
+  // (20,000 cells of 4: 181 us with 1,024 threads, 72 with 256, 46 with 64; 500 cells of 100:
+  // 12, 12 and 18)
+  const int nv = s->longest_task <= 64 ? 64 : s->longest_task <= 256 ? 256 : 1024;
+  auto tasks = nv == 64 ? k_virial_tasks<64> : nv == 256 ? k_virial_tasks<256> : k_virial_tasks<1024>;
   if (nt > 0)
-    k_virial_tasks<<<nt, NV, 0, s->stream>>>(s->d_tasks, s->bucket, s->row_of, s->rows1, s->slice_base,
-                                             s->geom, s->w_in, s->nl_cnt, red_w);
+    tasks<<<nt, nv, 0, s->stream>>>(s->d_tasks, s->bucket, s->row_of, s->rows1, s->slice_base, s->geom, s->w_in,
+                                    s->nl_cnt, red_w);
   if (s->n_struct > 0)
     k_virial_cells<<<s->n_struct, NC, 0, s->stream>>>(red_w, s->d_first_task, virial_struct);
 }

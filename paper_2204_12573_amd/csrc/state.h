@@ -151,6 +151,7 @@ struct flare_state {
   std::vector<flare::CellGrid> grids;
   std::vector<int> struct_off;
   std::vector<flare::RedTask> tasks;
+  int longest_task = 0;                    // atoms
   std::vector<int> first_task;
 
   // ---- capacities, fixed at flare_state_create (no device allocation after it) ----
