@@ -54,14 +54,14 @@ void gather_positions(flare_state* s, const double* x, const double* y, const do
                                                      s->d_status);
 }
 
-MixedDescArgs mixed_desc_args(flare_state* s, int r0, int nr, float* d_out, bool keep_geom) {
+MixedDescArgs mixed_desc_args(flare_state* s, int r0, int nr, float* d_out, bool keep) {
   return MixedDescArgs{slot_view(s), s->rows1, r0, s->atom_of_rowx, s->perm, s->Dx, nr <= FEW_ROWS ? s->D6x : nullptr,
-                       s->Cx, s->nrm, d_out, keep_geom};
+                       keep ? s->Cx : nullptr, s->nrm, d_out, keep};
 }
 
-void desc_mixed_chunk(flare_state* s, int r0, int nr, float* d_out, bool keep_geom) {
+void desc_mixed_chunk(flare_state* s, int r0, int nr, float* d_out, bool keep) {
   StageTimer tm(s, FLARE_T_DESCX);
-  if (nr > 0) k_desc_mixed<<<nr / MROWS, MTHREADS, 0, s->stream>>>(mixed_desc_args(s, r0, nr, d_out, keep_geom));
+  if (nr > 0) k_desc_mixed<<<nr / MROWS, MTHREADS, 0, s->stream>>>(mixed_desc_args(s, r0, nr, d_out, keep));
 }
 
 void export_norms(flare_state* s, float* norm_out) {

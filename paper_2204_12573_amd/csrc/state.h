@@ -297,7 +297,7 @@ bool few_single_rows(const flare_state* s);   // whether it will take the route 
 // mixed rows [r0, r0 + nr) of the 544-wide class (nr <= mix_cap, r0 a multiple of mix_cap),
 // in the chunk workspace Dx/Cx/Yx/Px: descriptors (and their export to caller order),
 // quadratic forms, adjoint terms
-void desc_mixed_chunk(flare_state* s, int r0, int nr, float* d_out, bool keep_geom);
+void desc_mixed_chunk(flare_state* s, int r0, int nr, float* d_out, bool keep);
 void forms_mixed_chunk(flare_state* s, int r0, int nr, bool want_e, bool want_v, bool finish);
 void adjoint_mixed_chunk(flare_state* s, int r0, int nr, bool want_v);
 // |d~| of every atom in caller order
