@@ -22,9 +22,9 @@ struct MixedDescArgs {
   bool keep_geom;            // with Cx
 };
 
-// LDS of a work-group: the slots' basis values, then the channels
-constexpr int MIXED_LDS = MROWS * 16 * PBS;
-static_assert(MROWS * MSTRIDE <= MIXED_LDS, "the channels reuse the basis block");
+// LDS of a work-group: the slots' basis values, then the channels, then the finished rows
+constexpr int MIXED_LDS = MROWS * ND;
+static_assert(MROWS * 16 * PBS <= MIXED_LDS && MROWS * MSTRIDE <= MIXED_LDS, "one block of LDS for all three");
 
 // One mixed row per 16 lanes (mixed.h): channel densities into LDS, then the 136 B2 channel
 // pairs spread over the row's lanes, the norm summed in FP64 across the lanes, and the
@@ -89,16 +89,28 @@ __device__ __forceinline__ void desc_mixed_block(const MixedDescArgs& q, int blo
   }
   const float nrm = (float)sqrt(nrm2);
   const float scale = nrm > 0.f ? 1.f / nrm : 0.f;
-  float4* out = reinterpret_cast<float4*>(q.D + (size_t)local * ND);
-  float4* ext = q.d_out && i >= 0 ? reinterpret_cast<float4*>(q.d_out + (size_t)q.perm[i] * ND) : nullptr;
+  // The lanes' pairs are scattered over the row, so it leaves through LDS in whole lines (each
+  // pair stored from its lane: the descriptors of 1,500 cells of 64 atoms written out in 262 us
+  // in place of 212, of 256 cells of 80 in 75 in place of 64)
+  __syncthreads();                        // the channels have been read
+  float4* rows = reinterpret_cast<float4*>(lds);
 #pragma unroll
   for (int k = 0; k < NQP; ++k) {
     if (k < 8 || L < 8) {
       const int P = mixed_pair_index(L, (L + k) & 15);
       const float4 o = make_float4(d[k].x * scale, d[k].y * scale, d[k].z * scale, d[k].w * scale);
-      out[P] = o;
+      rows[rl * (ND / 4) + P] = o;
       if (q.D6) store_d6(q.D6, local, P, o);
-      if (ext) ext[P] = o;
+    }
+  }
+  __syncthreads();
+  float4* out = reinterpret_cast<float4*>(q.D) + (size_t)block * MROWS * (ND / 4);
+  for (int k = threadIdx.x; k < MROWS * (ND / 4); k += MTHREADS) {
+    const float4 o = rows[k];
+    out[k] = o;
+    if (q.d_out) {
+      const int r = k / (ND / 4), a = q.atom_of_row[q.r0 + block * MROWS + r];
+      if (a >= 0) reinterpret_cast<float4*>(q.d_out)[(size_t)q.perm[a] * (ND / 4) + (k - r * (ND / 4))] = o;
     }
   }
   if (L == 0 && i >= 0) q.nrm_out[i] = nrm;
