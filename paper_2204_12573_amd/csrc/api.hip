@@ -155,18 +155,27 @@ void bf16_fragments(const std::vector<double>& M, uint16_t* out /* [5][9][2][64]
 std::vector<uint16_t> bf16x3_fragments(const double* M, int ld, int n) {
   const int nks = (n + 31) / 32, ncb = n / 16;
   std::vector<uint16_t> out((size_t)nks * ncb * 3 * 64 * 8, 0);
-  for (int k = 0; k < n; ++k)
+  uint16_t part[3][8][16];
+  // eight rows x 16 columns at a time: the fragments are written in order (row by row, in
+  // strides of 16 bytes, a 544-wide matrix took 1.4 ms in place of 0.9)
+  for (int kb = 0; kb < n / 8; ++kb)
     for (int cb = 0; cb < ncb; ++cb) {
-      uint16_t* p = &out[(((size_t)(k / 32) * ncb + cb) * 3 * 64 + 16 * (k % 32 / 8)) * 8 + k % 8];
-      for (int c = 0; c < 16; ++c, p += 8) {
-        const float v = (float)M[(size_t)k * ld + cb * 16 + c];
-        const uint16_t x0 = bf16_rne(v);
-        const float r1 = v - bf16_to_f32(x0);
-        const uint16_t x1 = bf16_rne(r1);
-        p[0] = x0;
-        p[64 * 8] = x1;
-        p[2 * 64 * 8] = bf16_rne(r1 - bf16_to_f32(x1));
+      for (int t = 0; t < 8; ++t) {
+        const double* row = M + (size_t)(8 * kb + t) * ld + cb * 16;
+        for (int c = 0; c < 16; ++c) {
+          const float v = (float)row[c];
+          const uint16_t x0 = bf16_rne(v);
+          const float r1 = v - bf16_to_f32(x0);
+          const uint16_t x1 = bf16_rne(r1);
+          part[0][t][c] = x0;
+          part[1][t][c] = x1;
+          part[2][t][c] = bf16_rne(r1 - bf16_to_f32(x1));
+        }
       }
+      uint16_t* p = &out[(((size_t)(kb / 4) * ncb + cb) * 3 * 64 + 16 * (kb % 4)) * 8];
+      for (int q = 0; q < 3; ++q)
+        for (int c = 0; c < 16; ++c)
+          for (int t = 0; t < 8; ++t) p[(q * 64 + c) * 8 + t] = part[q][t][c];
     }
   return out;
 }
