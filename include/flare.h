@@ -161,9 +161,10 @@ int flare_descriptor_dim(const flare_model* model, int* n_d);
  * first flare_virial (its task sums; flare_virial_noalloc allocates nothing).
  * flare_memory_bytes reports the total. One state serves one stream; calls on one state
  * must not overlap. The state also creates one internal stream (default priority, on the
- * current device) and two events: with forces, unless the rows are few, the 544-wide rows run
- * on it beside the single-species kernel, forked from and joined back into the caller's stream inside the
- * call, so the caller's stream alone orders every result, as with one stream.
+ * current device) and two events: with forces, and rows of both widths that are not few, the
+ * 544-wide rows run on it beside the single-species kernel, forked from and joined back into
+ * the caller's stream inside the call, so the caller's stream alone orders every result, as
+ * with one stream.
  */
 int flare_state_create(flare_state** out, const flare_model* model, int max_atoms,
                        long long max_pairs, void* stream);

@@ -722,13 +722,14 @@ int flare_descriptors(flare_state* s, const double* x, const double* y, const do
 // Energies (and gradients), forces and variances of the positions staged last, up to the
 // per-row results (row_out is formed by the output kernels).
 static int evaluate_forms(flare_state* s, bool want_f, bool want_v) {
-  // With forces the mixed rows run on a second stream beside the fused kernel: both read
-  // the step's pair geometry and write disjoint rows and disjoint slots of w_in, so the
-  // mixed rows' kernels fill the fused kernel's tail. The main stream waits for them
-  // before anything that reads their results. With the stage timers on, everything runs
-  // in order on the one stream, and few rows in any case: their descriptors are formed beside
-  // the fused kernel's work-groups in one launch, and an event costs more than the rest.
-  const bool beside = want_f && s->rowsx > 0 && !s->timers.on && !few_single_rows(s);
+  // With forces the mixed rows run on a second stream beside the fused kernel: each kernel forms
+  // the pair geometry of its own rows, and the two write disjoint rows and disjoint slots of
+  // geom and w_in, so the mixed rows' kernels fill the fused kernel's tail. The main stream waits
+  // for them before anything that reads their results. With the stage timers on, everything
+  // runs in order on the one stream, and in any case few rows (their descriptors are formed
+  // beside the fused kernel's work-groups in one launch, and an event costs more than the rest)
+  // and mixed rows alone, which have nothing to run beside.
+  const bool beside = want_f && s->rows1 > 0 && s->rowsx > 0 && !s->timers.on && !few_single_rows(s);
   if (beside) {
     CHK(hipEventRecord(s->ev_fork, s->stream));
     CHK(hipStreamWaitEvent(s->side, s->ev_fork, 0));
