@@ -679,14 +679,13 @@ int flare_neighbors_export(flare_state* s, long long* offsets, int32_t* j_out, i
   return FLARE_OK;
 }
 
-// The mixed (544-wide) rows in chunks of mix_cap rows: descriptors (exported to d_out in
-// caller order when given), quadratic forms (energies and gradients when want_e or want_f,
-// variances when want_v), adjoint terms when want_f.
+// The mixed (544-wide) rows in chunks of mix_cap rows: descriptors, quadratic forms (energies
+// and gradients when want_e or want_f, variances when want_v), adjoint terms when want_f.
 // have_desc: the descriptors are in the workspace already (one chunk).
-static void mixed_rows(flare_state* s, bool have_desc, float* d_out, bool want_e, bool want_v, bool want_f) {
+static void mixed_rows(flare_state* s, bool have_desc, bool want_e, bool want_v, bool want_f) {
   for (int r0 = 0; r0 < s->rowsx; r0 += s->mix_cap) {
     const int nr = std::min(s->mix_cap, s->rowsx - r0);
-    if (!have_desc) desc_mixed_chunk(s, r0, nr, d_out, want_e || want_f);
+    if (!have_desc) desc_mixed_chunk(s, r0, nr, want_e || want_f);
     forms_mixed_chunk(s, r0, nr, want_e || want_f, want_v, !want_f);
     if (want_f) adjoint_mixed_chunk(s, r0, nr, want_v);
   }
@@ -707,10 +706,12 @@ int flare_descriptors(flare_state* s, const double* x, const double* y, const do
     gather_positions(s, x, y, z);
   }
   if (d_out || norm_out) {
-    // the single-species rows come from the fused kernel run without quadratic forms
+    // the single-species rows come from the fused kernel run without quadratic forms (few rows:
+    // the mixed ones as well)
     if (d_out) CHK(hipMemsetAsync(d_out, 0, (size_t)s->n_atoms * ND * sizeof(float), s->stream));
     const bool both = fused_quadratic_forms(s, FORMS_DESCRIPTORS, d_out);
-    mixed_rows(s, both, d_out, false, false, false);
+    for (int r0 = 0; r0 < s->rowsx && !both; r0 += s->mix_cap)
+      export_mixed_chunk(s, r0, std::min(s->mix_cap, s->rowsx - r0), d_out);
     export_norms(s, norm_out);
   }
   CHK(hipGetLastError());
@@ -743,12 +744,12 @@ static int evaluate_forms(flare_state* s, bool want_f, bool want_v) {
   if (beside) {
     hipStream_t main = s->stream;
     s->stream = s->side;
-    mixed_rows(s, false, nullptr, true, want_v, want_f);
+    mixed_rows(s, false, true, want_v, want_f);
     s->stream = main;
     CHK(hipEventRecord(s->ev_join, s->side));
     CHK(hipStreamWaitEvent(s->stream, s->ev_join, 0));
   } else {
-    mixed_rows(s, both, nullptr, true, want_v, want_f);
+    mixed_rows(s, both, true, want_v, want_f);
   }
   if (want_f) {
     s->w_gen = s->pos_gen;
@@ -794,7 +795,7 @@ int flare_forces(flare_state* s, const double* cell_scale, float* fx, float* fy,
     // recomputed chunk by chunk
     adjoint_rows144(s);
     if (s->gx_gen == s->pos_gen) adjoint_mixed_chunk(s, 0, s->rowsx, false);
-    else mixed_rows(s, false, nullptr, true, false, true);
+    else mixed_rows(s, false, true, false, true);
     s->w_gen = s->pos_gen;
   }
   {
@@ -832,7 +833,7 @@ int flare_variance(flare_state* s, float* var_atom, float* sigma_atom, float* si
       StageTimer tm(s, FLARE_T_QFORM1);
       both = fused_quadratic_forms(s, 2, nullptr);
     }
-    mixed_rows(s, both, nullptr, false, true, false);
+    mixed_rows(s, both, false, true, false);
     s->v_gen = s->pos_gen;
   }
   {
@@ -876,7 +877,7 @@ int flare_uncertainty_monitor(flare_state* s, double threshold, float* sigma_max
       StageTimer tm(s, FLARE_T_QFORM1);
       both = fused_quadratic_forms(s, 2, nullptr);
     }
-    mixed_rows(s, both, nullptr, false, true, false);
+    mixed_rows(s, both, false, true, false);
     s->v_gen = s->pos_gen;
   }
   {

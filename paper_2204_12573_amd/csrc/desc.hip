@@ -14,9 +14,10 @@
 namespace flare {
 namespace {
 
+template <bool EXPORT>
 __global__ __launch_bounds__(MTHREADS) void k_desc_mixed(MixedDescArgs q) {
   __shared__ __attribute__((aligned(16))) float lds[MIXED_LDS];
-  desc_mixed_block(q, blockIdx.x, lds);
+  desc_mixed_block<EXPORT>(q, blockIdx.x, lds);
 }
 
 constexpr int NTG = 256;
@@ -59,9 +60,15 @@ MixedDescArgs mixed_desc_args(flare_state* s, int r0, int nr, float* d_out, bool
                        keep ? s->Cx : nullptr, s->nrm, d_out, keep};
 }
 
-void desc_mixed_chunk(flare_state* s, int r0, int nr, float* d_out, bool keep) {
+void desc_mixed_chunk(flare_state* s, int r0, int nr, bool keep) {
   StageTimer tm(s, FLARE_T_DESCX);
-  if (nr > 0) k_desc_mixed<<<nr / MROWS, MTHREADS, 0, s->stream>>>(mixed_desc_args(s, r0, nr, d_out, keep));
+  if (nr > 0)
+    k_desc_mixed<false><<<nr / MROWS, MTHREADS, 0, s->stream>>>(mixed_desc_args(s, r0, nr, nullptr, keep));
+}
+
+void export_mixed_chunk(flare_state* s, int r0, int nr, float* d_out) {
+  StageTimer tm(s, FLARE_T_DESCX);
+  if (nr > 0) k_desc_mixed<true><<<nr / MROWS, MTHREADS, 0, s->stream>>>(mixed_desc_args(s, r0, nr, d_out, false));
 }
 
 void export_norms(flare_state* s, float* norm_out) {

@@ -890,7 +890,8 @@ __global__ __launch_bounds__(FW, 1) void k_fused144_few(FusedArgs a, int nsub, i
   __shared__ float scale2_s[WR];
   __shared__ double ss_s[64][8];           // FP64 variance: row sums handed from group to group
   if ((int)blockIdx.x >= nsub) {
-    desc_mixed_block(md, blockIdx.x - nsub, lds);
+    if (a.mode & 3) desc_mixed_block<false>(md, blockIdx.x - nsub, lds);
+    else desc_mixed_block<true>(md, blockIdx.x - nsub, lds);
     return;
   }
   static_assert(FW == MTHREADS, "a work-group takes a block of mixed rows");

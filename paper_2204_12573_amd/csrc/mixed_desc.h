@@ -22,15 +22,16 @@ struct MixedDescArgs {
   bool keep_geom;            // with Cx
 };
 
-// LDS of a work-group: the slots' basis values, then the channels, then the finished rows
-constexpr int MIXED_LDS = MROWS * ND;
-static_assert(MROWS * 16 * PBS <= MIXED_LDS && MROWS * MSTRIDE <= MIXED_LDS, "one block of LDS for all three");
+// LDS of a work-group: the slots' basis values, then the channels, then (export) finished rows
+constexpr int MIXED_LDS = MROWS * 16 * PBS;
+static_assert(MROWS * MSTRIDE <= MIXED_LDS && MROWS / 2 * ND <= MIXED_LDS, "one block of LDS for all three");
 
 // One mixed row per 16 lanes (mixed.h): channel densities into LDS, then the 136 B2 channel
 // pairs spread over the row's lanes, the norm summed in FP64 across the lanes, and the
 // normalised row written as float4 per pair: into the chunk's workspace D (row - r0, the
-// densities beside it in Cx; few rows also split, in D6) and, when exporting, into d_out at
-// the atom's caller index.
+// densities beside it in Cx; few rows also split, in D6), or (EXPORT) into d_out at the atom's
+// caller index, the workspace left alone.
+template <bool EXPORT>
 __device__ __forceinline__ void desc_mixed_block(const MixedDescArgs& q, int block, float* __restrict__ lds) {
 #pragma clang fp contract(off)
   const int rl = threadIdx.x >> 4, L = threadIdx.x & 15;
@@ -43,7 +44,7 @@ __device__ __forceinline__ void desc_mixed_block(const MixedDescArgs& q, int blo
 #pragma unroll
   for (int lm = 0; lm < NLM; ++lm) crow[cidx(L, lm)] = c[lm];
   __syncthreads();
-  if (q.Cx) {
+  if (!EXPORT && q.Cx) {
     float4* to = reinterpret_cast<float4*>(q.Cx + (size_t)block * MROWS * MSTRIDE);
     for (int k = threadIdx.x; k < MROWS * MSTRIDE / 4; k += MTHREADS) to[k] = reinterpret_cast<const float4*>(lds)[k];
   }
@@ -89,28 +90,37 @@ __device__ __forceinline__ void desc_mixed_block(const MixedDescArgs& q, int blo
   }
   const float nrm = (float)sqrt(nrm2);
   const float scale = nrm > 0.f ? 1.f / nrm : 0.f;
-  // The lanes' pairs are scattered over the row, so it leaves through LDS in whole lines (each
-  // pair stored from its lane: the descriptors of 1,500 cells of 64 atoms written out in 262 us
-  // in place of 212, of 256 cells of 80 in 75 in place of 64)
-  __syncthreads();                        // the channels have been read
-  float4* rows = reinterpret_cast<float4*>(lds);
+  if (!EXPORT) {
+    float4* out = reinterpret_cast<float4*>(q.D + (size_t)local * ND);
 #pragma unroll
-  for (int k = 0; k < NQP; ++k) {
-    if (k < 8 || L < 8) {
-      const int P = mixed_pair_index(L, (L + k) & 15);
-      const float4 o = make_float4(d[k].x * scale, d[k].y * scale, d[k].z * scale, d[k].w * scale);
-      rows[rl * (ND / 4) + P] = o;
-      if (q.D6) store_d6(q.D6, local, P, o);
+    for (int k = 0; k < NQP; ++k) {
+      if (k < 8 || L < 8) {
+        const int P = mixed_pair_index(L, (L + k) & 15);
+        const float4 o = make_float4(d[k].x * scale, d[k].y * scale, d[k].z * scale, d[k].w * scale);
+        out[P] = o;
+        if (q.D6) store_d6(q.D6, local, P, o);
+      }
     }
-  }
-  __syncthreads();
-  float4* out = reinterpret_cast<float4*>(q.D) + (size_t)block * MROWS * (ND / 4);
-  for (int k = threadIdx.x; k < MROWS * (ND / 4); k += MTHREADS) {
-    const float4 o = rows[k];
-    out[k] = o;
-    if (q.d_out) {
-      const int r = k / (ND / 4), a = q.atom_of_row[q.r0 + block * MROWS + r];
-      if (a >= 0) reinterpret_cast<float4*>(q.d_out)[(size_t)q.perm[a] * (ND / 4) + (k - r * (ND / 4))] = o;
+  } else if (q.d_out) {
+    // The lanes' pairs are scattered over the row, so it leaves through LDS in whole lines, eight
+    // rows at a time (each pair stored from its lane, to the workspace too: the descriptors of
+    // 1,500 cells of 64 atoms in 262 us in place of 208, of 256 cells of 80 in 75 in place of
+    // 62; the workspace's rows stay in L2 and do not gain by it)
+    float4* rows = reinterpret_cast<float4*>(lds);
+    for (int half = 0; half < 2; ++half) {
+      __syncthreads();                    // the channels, or the first eight rows, have been read
+      if ((rl >> 3) == half) {
+#pragma unroll
+        for (int k = 0; k < NQP; ++k)
+          if (k < 8 || L < 8)
+            rows[(rl & 7) * (ND / 4) + mixed_pair_index(L, (L + k) & 15)] =
+                make_float4(d[k].x * scale, d[k].y * scale, d[k].z * scale, d[k].w * scale);
+      }
+      __syncthreads();
+      for (int k = threadIdx.x; k < MROWS / 2 * (ND / 4); k += MTHREADS) {
+        const int r = k / (ND / 4), a = q.atom_of_row[q.r0 + block * MROWS + half * (MROWS / 2) + r];
+        if (a >= 0) reinterpret_cast<float4*>(q.d_out)[(size_t)q.perm[a] * (ND / 4) + (k - r * (ND / 4))] = rows[k];
+      }
     }
   }
   if (L == 0 && i >= 0) q.nrm_out[i] = nrm;

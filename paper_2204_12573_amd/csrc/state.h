@@ -295,9 +295,10 @@ constexpr int FORMS_DESCRIPTORS = 8;
 bool fused_quadratic_forms(flare_state* s, int mode, float* d_out);
 bool few_single_rows(const flare_state* s);   // whether it will take the route for few rows
 // mixed rows [r0, r0 + nr) of the 544-wide class (nr <= mix_cap, r0 a multiple of mix_cap),
-// in the chunk workspace Dx/Cx/Yx/Px: descriptors (and their export to caller order),
-// quadratic forms, adjoint terms
-void desc_mixed_chunk(flare_state* s, int r0, int nr, float* d_out, bool keep);
+// in the chunk workspace Dx/Cx/Yx/Px: descriptors, quadratic forms, adjoint terms;
+// export_mixed_chunk: norms, and descriptors to caller order, without the workspace
+void desc_mixed_chunk(flare_state* s, int r0, int nr, bool keep);
+void export_mixed_chunk(flare_state* s, int r0, int nr, float* d_out);
 void forms_mixed_chunk(flare_state* s, int r0, int nr, bool want_e, bool want_v, bool finish);
 void adjoint_mixed_chunk(flare_state* s, int r0, int nr, bool want_v);
 // |d~| of every atom in caller order
