@@ -228,7 +228,9 @@ def form_roofline(prec, fused_work, t_launch):
     and vector instructions share the SIMD datapath). Per row: the energy pass takes
     `products` part products of 2*144^2 flop (BF16 x3: 3, FP8 x3: 3, BF16 x6: 6) on the
     form's matrix type; the variance |L^T d|^2 takes 144*145 flop on FP64 matrix cores, or with
-    FLARE_VAR_FP32 to FP32 accuracy, counted at the FP32 matrix peak."""
+    FLARE_VAR_FP32 to FP32 accuracy, counted at the FP32 matrix peak. That pass runs as six
+    BF16 part products of each FP32 product, as the FP32 form's: `six_products` gives its bound
+    and fraction with the variance at a sixth of the BF16 peak, to be read beside the FP32 leg's."""
     from paper_2204_12573_amd import binding as B
     base = prec & ~B.VAR_FP32
     products, peak, kind = {B.BF16_SPLIT: (3, PEAK_BF16_MFMA, "bf16"), B.FP8_SPLIT: (3, PEAK_FP8_MFMA, "fp8"),
@@ -240,13 +242,19 @@ def form_roofline(prec, fused_work, t_launch):
     parts = {"energy_pass_us": e_flops / peak * 1e6, "variance_pass_us": v_flops / var_peak * 1e6,
              "vector_us": fused_work["valu_flops"] / PEAK_FP32_VALU * 1e6}
     t_min = sum(parts.values()) * 1e-6
-    return {"bound": "alu", "t_min_us": round(t_min * 1e6, 1), "avg_launch_us": round(t_launch * 1e6, 1),
-            "frac": round(t_min / t_launch, 3), "parts_us": {k: round(v, 1) for k, v in parts.items()},
-            "peak_derivation": f"energy pass {products} products on {kind} matrix cores "
-                               f"({peak / 1e12:.0f} TFLOP/s), variance on "
-                               f"{'FP32' if prec & B.VAR_FP32 else 'FP64'} matrix cores "
-                               f"({var_peak / 1e12:.1f} TFLOP/s), vector work at 78.6 TFLOP/s, summed "
-                               f"(one datapath)"}
+    out = {"bound": "alu", "t_min_us": round(t_min * 1e6, 1), "avg_launch_us": round(t_launch * 1e6, 1),
+           "frac": round(t_min / t_launch, 3), "parts_us": {k: round(v, 1) for k, v in parts.items()},
+           "peak_derivation": f"energy pass {products} products on {kind} matrix cores "
+                              f"({peak / 1e12:.0f} TFLOP/s), variance "
+                              f"{'to FP32 accuracy, at the FP32 matrix peak' if prec & B.VAR_FP32 else 'on FP64 matrix cores'} "
+                              f"({var_peak / 1e12:.1f} TFLOP/s), vector work at 78.6 TFLOP/s, summed "
+                              f"(one datapath)"}
+    if prec & B.VAR_FP32:
+        t_v = v_flops / (PEAK_BF16_MFMA / 6)
+        t6 = t_min - parts["variance_pass_us"] * 1e-6 + t_v
+        out["six_products"] = {"variance_pass_us": round(t_v * 1e6, 1), "t_min_us": round(t6 * 1e6, 1),
+                               "frac": round(t6 / t_launch, 3)}
+    return out
 
 
 def measured_ceilings(torch):
@@ -649,8 +657,8 @@ def main():
                                                 binding.BF16X6_SPLIT | binding.VAR_FP32, tg, ref),
             "stage_us_per_launch": {k: round(ms / max(c, 1) * 1e3, 1) for k, (ms, c) in tm7.items() if c},
             "roofline": form_roofline(binding.BF16X6_SPLIT | binding.VAR_FP32, fused_work, tm7["qform144"][0] / tm7["qform144"][1] * 1e-3),
-            "note": "the three-way BF16 energy pass with the variance through the FP32 factor on FP32 "
-                    "matrix cores (FLARE_VAR_FP32: the plain form's variance error, not FP64)"}
+            "note": "the three-way BF16 energy pass with the variance through the FP32 factor "
+                    "as in the plain form (FLARE_VAR_FP32: its variance error, not FP64)"}
         if not args.no_huge:
             log("precision forms at ~16 M atoms ...")
             out["precision_16m"] = precision_16m(engine, torch, st, beta, sigma)

@@ -403,9 +403,9 @@ int flare_coordination(flare_state* state, const double* x, const double* y, con
  */
 #define FLARE_NTIMERS 9
 #define FLARE_T_LIST      0  /* flare_neighbors device work                    */
-#define FLARE_T_DESC1     1  /* position gather + descriptors, 144-wide rows    */
-#define FLARE_T_DESCX     2  /* descriptors, 544-wide (mixed) rows              */
-#define FLARE_T_QFORM1    3  /* quadratic forms on the matrix cores, 144 rows   */
+#define FLARE_T_DESC1     1  /* displacements of flare_descriptors              */
+#define FLARE_T_DESCX     2  /* descriptors, 544-wide rows (few: in QFORM1)     */
+#define FLARE_T_QFORM1    3  /* 144 rows: descriptors, forms, adjoint if fused  */
 #define FLARE_T_QFORMX    4  /* quadratic forms, 544 rows (GEMM + finish)       */
 #define FLARE_T_FORCE1    5  /* adjoint forces, 144 rows (incl. force clear)    */
 #define FLARE_T_FORCEX    6  /* adjoint forces, 544 rows                        */

@@ -171,8 +171,8 @@ void adjoint_mixed_chunk(flare_state* s, int r0, int nr, bool want_v) {
   const SlotView v = slot_view(s);
   StageTimer tm(s, FLARE_T_FORCEX);
   const bool v64 = s->model->var64;
-  MixedForms q{s->Cx, s->Dx, s->Yx, want_v && !v64 ? s->Px : nullptr, want_v && v64 ? s->Px64 : nullptr, s->nrm, s->e_int, s->v_int, s->e_row + s->rows1,
-               s->v_row + s->rows1};
+  const MixedForms q{s->Cx, s->Dx, s->Yx, want_v && !v64 ? s->Px : nullptr, want_v && v64 ? s->Px64 : nullptr,
+                     s->nrm, s->e_int, s->v_int, s->e_row + s->rows1, s->v_row + s->rows1};
   if (nr > 0)
     k_adjoint_mixed<<<nr / MROWS, MTHREADS, 0, s->stream>>>(v, s->rows1, r0, s->atom_of_rowx, q, s->f_own);
 }

@@ -7,8 +7,9 @@
 // This file holds the mixed-environment rows (544 components, 16 lanes per row, see
 // mixed.h). Single-species rows are formed inside the fused quadratic-form kernel
 // (fused.hip).
-// Pair geometry: positions are FP64; Delta = (x_j - x_i) + s*L is formed in FP64 and
-// rounded to FP32 before the basis is evaluated.
+// Pair geometry: Delta = [(w_j - w_i) + s*L] + (delta_j - delta_i), the bracket formed in FP64 at
+// the list build and kept in FP32, the displacements since then (FP64 differences, kept in FP32)
+// added in FP32 (pair.h).
 #include "mixed_desc.h"
 
 namespace flare {

@@ -98,7 +98,6 @@ __device__ __forceinline__ void split8(const float* p, bool zero, bf8& hi, bf8& 
   lo = __builtin_bit_cast(bf8, pl);
 }
 
-template <int PART>
 __device__ __forceinline__ void mfma_pass_bf16(const float* As, const uint4* __restrict__ W, int wave,
                                                int lane, f4 (&acc)[2][NCB]) {
   const int l16 = lane & 15, grp = lane >> 4;
@@ -722,7 +721,7 @@ __device__ __forceinline__ void forms_phase(const FusedArgs& a, float* As, const
     f4 acc[2][NCB];
     float dots[2][4];
     if (PREC == FLARE_BF16_SPLIT) {
-      mfma_pass_bf16<0>(As, tm.Wb, wave, lane, acc);
+      mfma_pass_bf16(As, tm.Wb, wave, lane, acc);
     } else if (PREC == FLARE_FP8_SPLIT) {
       energy_pass_fp8(As, rs.rsc, tm, wave, lane, acc);
     } else {
@@ -849,11 +848,10 @@ __global__ __launch_bounds__(WW * 64, 1) void k_fused144_w(FusedArgs a, int nsub
     const int row0 = st * WR;
     float c[NR][NQ];
     // wave priorities by phase, for when both waves of a SIMD can issue: the matrix-core
-    // phase first (its MFMAs keep the shared datapath busy 32 cycles each and the other
-    // wave fills the gaps), then the descriptor phase (its pair loads start early), the
-    // adjoint phase last; measured 811 -> 786 us against the matrix phase alone raised,
-    // no gain with the adjoint level with the descriptors, a loss with the descriptors
-    // above the matrix phase
+    // phase first (an MFMA issues in a few cycles and runs 16, in which the other wave's vector
+    // work fills the gaps), then the descriptor phase (its pair loads start early), the adjoint
+    // phase last. A launch on 1.0 M atoms: 703 us without, 683 with the matrix phase alone
+    // raised, 674 so
     __builtin_amdgcn_s_setprio(1);
     desc_phase<PREC, false>(a, A, rs, row0, lane, c);
     wave_phase_fence();
@@ -876,7 +874,7 @@ __global__ __launch_bounds__(WW * 64, 1) void k_fused144_w(FusedArgs a, int nsub
 // and the pair terms' eight lanes set the registers (one wave a SIMD): nothing else is there to
 // hide behind, so latency alone counts. With the mixed rows' descriptors in the same launch no
 // second stream is needed, whose two events cost 20-40 us a call. A cell of 80 atoms with its
-// list 200 -> 144 us, ten steps of 1,200 atoms 940 -> 655.
+// list 200 -> 154 us, ten steps of 1,200 atoms 940 -> 740.
 constexpr int FW = 256;
 
 template <int PREC, bool V64>
@@ -930,7 +928,7 @@ __global__ __launch_bounds__(FW, 1) void k_fused144_few(FusedArgs a, int nsub, i
       j1 = wave < 3 ? j0 + 3 : NCB;
     } else if (wave == 0) {
       if (X6) mfma_pass_bf16x6<false>(As, tm.W6, 0, lane, acc);
-      else if (PREC == FLARE_BF16_SPLIT) mfma_pass_bf16<0>(As, tm.Wb, 0, lane, acc);
+      else if (PREC == FLARE_BF16_SPLIT) mfma_pass_bf16(As, tm.Wb, 0, lane, acc);
       else energy_pass_fp8(As, rsc_s, tm, 0, lane, acc);
       j1 = NCB;
     }

@@ -189,7 +189,8 @@ __device__ inline int row_key(int b, int c) { return b * NCK + (NCK - 1 - min(c,
 // one), the FP64 test the rest. Returns the pair count and the species seen.
 // (One thread an atom, walking 27 bins through dependent loads, took 58 us for 80 atoms and
 // 244 us for 1.0 M.)
-constexpr int SA = NT / 16;                  // atoms per work-group at 16 lanes an atom
+constexpr int SL = 16;                       // lanes an atom
+constexpr int SA = NT / SL;                  // atoms per work-group
 
 struct PairSearch {
   const CellGrid* grids;
@@ -202,7 +203,7 @@ struct PairSearch {
   float lo2, hi2;
 };
 
-template <int SL, class Emit>
+template <class Emit>
 __device__ __forceinline__ void search_atom(const PairSearch& q, int i, int& cnt_out, int& mask_out, Emit emit) {
 #pragma clang fp contract(off)
   const int l = threadIdx.x & (SL - 1);
@@ -299,15 +300,14 @@ constexpr int FEW_ATOMS = 81920;
 constexpr int MANY_AW = 64;
 
 // Up to FEW_ATOMS 16 lanes an atom (blk cleared at the build's start).
-template <int SL>
 __global__ __launch_bounds__(NT) void k_search(int n, PairSearch q, int* __restrict__ cnt_out,
                                                int* __restrict__ bucket, int* __restrict__ blk, int nblk,
                                                int2* __restrict__ cache, int* __restrict__ build_status) {
-  const int i = blockIdx.x * (NT / SL) + threadIdx.x / SL;
+  const int i = blockIdx.x * SA + threadIdx.x / SL;
   if (i >= n) return;
   int cnt, mask;
   int2* mine = cache + (size_t)i * PAIR_CACHE;
-  search_atom<SL>(q, i, cnt, mask, [&](int k, int j, int shift) {
+  search_atom(q, i, cnt, mask, [&](int k, int j, int shift) {
     if (k < PAIR_CACHE) mine[k] = make_int2(j, shift);
   });
   if ((threadIdx.x & (SL - 1)) == 0) {
@@ -526,7 +526,7 @@ __global__ __launch_bounds__(NT) void k_lists(int n, int nlist, PairSearch q, co
         const int p0 = offs[k];
         if (offs[k + 1] - p0 <= PAIR_CACHE) continue;
         int c, m;
-        search_atom<16>(q, a0 + k, c, m, [&](int pos, int j, int shift) {
+        search_atom(q, a0 + k, c, m, [&](int pos, int j, int shift) {
           nl_j[p0 + pos] = j;
           nl_s[p0 + pos] = shift;
           nl_rev[p0 + pos] = -1;
@@ -970,7 +970,7 @@ int build_list(flare_state* s, const double* x, const double* y, const double* z
   if (many)
     k_search_many<<<nblk, NT, 0, st>>>(n, q, s->nl_cnt, s->bucket, s->blk_bucket, nblk, s->pair_cache, bst);
   else if (n > 0)
-    k_search<16><<<ngroup, NT, 0, st>>>(n, q, s->nl_cnt, s->bucket, s->blk_bucket, nblk, s->pair_cache, bst);
+    k_search<<<ngroup, NT, 0, st>>>(n, q, s->nl_cnt, s->bucket, s->blk_bucket, nblk, s->pair_cache, bst);
   scan_exclusive2(s->nl_cnt, s->nl_off, n, s->blk_bucket, s->blk_bucket_scan, NKEY * nblk, s->scan_scratch, bst,
                   BUILD_OVERFLOW, st);
   const int nlist = many ? (n + MANY_AW - 1) / MANY_AW : ngroup;
@@ -1030,8 +1030,6 @@ int build_list(flare_state* s, const double* x, const double* y, const double* z
   }
   s->rows1 = L[LY_ROWS1];
   s->rowsx = L[LY_ROWSX];
-  s->n_slices = L[LY_SLICES];
-  s->n_slots = 32LL * L[LY_SLOTS32];
   return FLARE_OK;
 }
 

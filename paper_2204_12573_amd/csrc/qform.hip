@@ -478,7 +478,7 @@ int forms_given_544(flare_state* s, int bucket, int n, const float* d, float* e,
     // bucket 5, the H-centre one throughout for bucket 4
     const int split = bucket == 5 ? 0 : rows;
     XArgs q{};
-      q.D = s->Dx;
+    q.D = s->Dx;
     q.D6 = s->D6x;
     q.n_given = nc;
     q.rows = rows;

@@ -228,8 +228,6 @@ struct flare_state {
   double* Px64 = nullptr;               // [mix_cap][17] the same in FP64 (split forms)
 
   // ---- sliced pair layout (capacity slot_cap) ----
-  int n_slices = 0;
-  long long n_slots = 0;
   int* slice_len = nullptr;             // [slice_cap + 1]
   int* slice_base = nullptr;
   int* slot_rev = nullptr;
