@@ -42,3 +42,26 @@ def test_variance_and_monitor_before_the_backward(name):
     f = ev.forces()
     assert torch.equal(e, ref["e"]) and torch.equal(var, ref["var"]) and torch.equal(f, ref["f"])
     assert torch.equal(ev.virial(), w)
+
+
+def test_export_over_chunks():
+    """Descriptors and norms written out: the same bits from one chunk of mixed rows and from two,
+    norms alone the same as beside the descriptors, and an evaluation after them undisturbed."""
+    cells = _alloy(300)
+    model = engine.Model(*S.random_model(544))
+    got = []
+    for n in (20, 300):
+        b = S.concat(cells[:n])
+        print(f"case: {b.n} atoms", flush=True)
+        ev = engine.Evaluator(model, max_atoms=b.n, max_pairs=100 * b.n)
+        p, s = engine.to_device(b.pos, b.species)
+        ev.neighbors(p, s, b.offsets, b.boxes, 0.2)
+        d, norm = ev.descriptors(p, want_d=True, want_norm=True)
+        alone = ev.descriptors(p, want_norm=True)[1]
+        f = ev.energy_forces()["f"]
+        m = 20 * 64
+        assert torch.equal(norm, alone)
+        assert float((d.double().square().sum(1) - 1).abs().max()) < 1e-6
+        got.append((d[:m].clone(), norm[:m].clone(), f[:, :m].clone()))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
